@@ -49,9 +49,9 @@ struct aslam_policy {
   // recurrent handle: the GRU's weight copies and the sequence minibatch's buffers
   bool rec = false;
   uint16_t *wihb = nullptr, *whhb = nullptr, *wiht = nullptr, *whht = nullptr;
-  float *hst = nullptr, *g_r = nullptr, *g_z = nullptr, *g_n = nullptr, *g_ghn = nullptr, *hp_used = nullptr;
-  float *dh_head = nullptr, *dh_buf = nullptr;
-  uint16_t *hp_bf = nullptr, *dgi = nullptr, *dgh = nullptr;
+  float *hst = nullptr, *g_r = nullptr, *g_z = nullptr, *g_n = nullptr, *g_ghn = nullptr;
+  float* dh_head = nullptr;
+  uint16_t *hp_bf = nullptr, *dg = nullptr;   // dg: the gate gradients dgi and dgh; before them, the FP32 input products
   int32_t* rows = nullptr;
 };
 
@@ -93,7 +93,7 @@ int64_t part_need(const aslam_policy* p) {
   int64_t need = kFc1Splits * 256 * k1;                      // FC1 weight partials
   need = std::max<int64_t>(need, kFc2Splits * kHid * kHid);   // FC2 weight partials
   if (p->rec) need = std::max<int64_t>(need, (int64_t)kFc2Splits * kGates * kHid);   // GRU weight partials
-  if (p->rec) need = std::max<int64_t>(need, (int64_t)kBiasBlocks * kGates);         // GRU bias partials
+  if (p->rec) need = std::max<int64_t>(need, std::max<int64_t>(256, (p->max_b + 15) / 16) * 2 * kGates);   // GRU bias partials
   need = std::max<int64_t>(need, (int64_t)kConvBwdGrid * kConvPart);   // encoder backward partials
   need = std::max<int64_t>(need, (int64_t)kBiasBlocks * 256);
   need = std::max<int64_t>(need, (int64_t)kFc1MinBlocks * 64 * kHid);   // FC1 forward split-K: S * B <= 512 * 64
@@ -351,8 +351,8 @@ int aslam_policy_create(const aslam_policy_config* cfg, aslam_policy** out) {
     struct A rl[] = {
         {(void**)&p->wihb, w}, {(void**)&p->whhb, w}, {(void**)&p->wiht, w}, {(void**)&p->whht, w},
         {(void**)&p->hst, f}, {(void**)&p->g_r, f}, {(void**)&p->g_z, f}, {(void**)&p->g_n, f},
-        {(void**)&p->g_ghn, f}, {(void**)&p->hp_used, f}, {(void**)&p->dh_head, f}, {(void**)&p->dh_buf, 2 * f},
-        {(void**)&p->hp_bf, h}, {(void**)&p->dgi, g}, {(void**)&p->dgh, g},
+        {(void**)&p->g_ghn, f}, {(void**)&p->dh_head, f},
+        {(void**)&p->hp_bf, h}, {(void**)&p->dg, 2 * g},
         {(void**)&p->rows, 4 * (size_t)Bm},
     };
     for (auto& a : rl) {
@@ -360,6 +360,17 @@ int aslam_policy_create(const aslam_policy_config* cfg, aslam_policy** out) {
         aslam_policy_destroy(p);
         return pfail(ASL_ENOMEM, "hipMalloc of policy workspace failed");
       }
+    }
+    hipError_t e = hipSuccess;
+    for (const void* f : {reinterpret_cast<const void*>(&k_gru_seq_fwd<1>), reinterpret_cast<const void*>(&k_gru_seq_fwd<2>),
+                          reinterpret_cast<const void*>(&k_gru_seq_fwd<4>)})
+      if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kGruSeqFwdLds);
+    for (const void* f : {reinterpret_cast<const void*>(&k_gru_seq_bwd<1>), reinterpret_cast<const void*>(&k_gru_seq_bwd<2>),
+                          reinterpret_cast<const void*>(&k_gru_seq_bwd<4>)})
+      if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kGruSeqBwdLds);
+    if (e != hipSuccess) {
+      aslam_policy_destroy(p);
+      return pfail(ASL_EHIP, hipGetErrorString(e));
     }
   }
   *out = p;
@@ -375,8 +386,8 @@ int aslam_policy_destroy(aslam_policy* p) {
   if (!p) return pfail(ASL_EINVAL, "policy is NULL");
   void* ptrs[] = {p->x, p->h1, p->dz2, p->dz1, p->dz2c, p->z2, p->part, p->hpart,
                   p->w1b, p->w1t, p->w2b, p->w2t, p->cfrag,
-                  p->wihb, p->whhb, p->wiht, p->whht, p->hst, p->g_r, p->g_z, p->g_n, p->g_ghn, p->hp_used,
-                  p->dh_head, p->dh_buf, p->hp_bf, p->dgi, p->dgh, p->rows, p->x_lo, p->h1_lo, p->w1b_lo,
+                  p->wihb, p->whhb, p->wiht, p->whht, p->hst, p->g_r, p->g_z, p->g_n, p->g_ghn,
+                  p->dh_head, p->hp_bf, p->dg, p->rows, p->x_lo, p->h1_lo, p->w1b_lo,
                   p->w2b_lo};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
@@ -682,12 +693,12 @@ int aslam_policy_act_rnn(aslam_policy* P, const float* params, int32_t prepared,
   }
   // the step writes the new state to a workspace (h_out may alias h_in); the heads copy it out
   GruFwdArgs a{};
-  a.prm = params; a.o = P->off; a.rows = batch; a.s0 = 0;
+  a.prm = params; a.o = P->off; a.rows = batch;
   a.h1 = P->h1;
   a.wih = P->wihb; a.whh = P->whhb;
-  a.hp = h_in; a.hp_map = nullptr; a.first = first; a.first_map = nullptr;
+  a.hp = h_in; a.first = first;
   a.h_out = P->hst;
-  k_gru_fwd<false><<<dim3((batch + kGruRows - 1) / kGruRows, kGruSlices), 256, 0, st>>>(a);
+  k_gru_fwd<<<dim3((batch + kGruRows - 1) / kGruRows, kGruSlices), 256, 0, st>>>(a);
   PCHK(hipGetLastError());
   k_gru_heads<<<(batch + 3) / 4, 256, 0, st>>>(params, P->off, P->hst, batch, h_out, mu, value,
                                                 ActDraws{eps, seed, counter}, act, logp);
@@ -721,21 +732,20 @@ int aslam_policy_backward_seq(aslam_policy* P, const float* params, const int16_
         P->part, S, B, kHid, params + o.f1b, P->h1, kHid);
     PCHK(hipGetLastError());
   }
-  // the GRU over the T steps, keeping what the backward reads
-  const dim3 grid((nb + kGruRows - 1) / kGruRows, kGruSlices);
-  for (int t = 0; t < T; ++t) {
-    GruFwdArgs a{};
-    a.prm = params; a.o = o; a.rows = nb; a.s0 = (int64_t)t * nb;
-    a.h1 = P->h1;
-    a.wih = P->wihb; a.whh = P->whhb;
-    a.hp = t == 0 ? h0 : P->hst + (int64_t)(t - 1) * nb * kHid;
-    a.hp_map = t == 0 ? robots : nullptr;
-    a.first = first + (int64_t)t * N; a.first_map = robots;
-    a.h_out = P->hst;
-    a.g_r = P->g_r; a.g_z = P->g_z; a.g_n = P->g_n; a.g_ghn = P->g_ghn; a.hp_used = P->hp_used; a.hp_bf = P->hp_bf;
-    k_gru_fwd<true><<<grid, 256, 0, st>>>(a);
-    PCHK(hipGetLastError());
-  }
+  // the GRU over the T steps: the input products of every sample at once, then the recurrence, keeping
+  // what the backward reads
+  GruSeqArgs a{};
+  a.prm = params; a.o = o;
+  a.nb = nb; a.T = T; a.N = N;
+  a.robots = robots; a.h0 = h0; a.first = first;
+  a.gi = reinterpret_cast<const float*>(P->dg); a.whh = P->whhb;
+  a.hst = P->hst; a.g_r = P->g_r; a.g_z = P->g_z; a.g_n = P->g_n; a.g_ghn = P->g_ghn; a.hp_bf = P->hp_bf;
+  const int rpl = gru_seq_rows(nb);
+  const unsigned tiles = (unsigned)((nb + 4 * rpl - 1) / (4 * rpl));
+  PCHK((gemm::run<128, 128, 64, 2, 2>(LdBF16K{P->h1, kHid, B, kHid}, LdBF16K{P->wihb, kHid, kGates, kHid},
+                                     EpiPartial{reinterpret_cast<float*>(P->dg), kGates, 0}, B, kGates, kHid, 1, st)));
+  (rpl == 1 ? k_gru_seq_fwd<1> : rpl == 2 ? k_gru_seq_fwd<2> : k_gru_seq_fwd<4>)<<<tiles, kGruSeqThreads, kGruSeqFwdLds, st>>>(a);
+  PCHK(hipGetLastError());
   // heads + loss on every sample -> dh (FP32), head / log-std partial sums
   const int nh = (B + kHeadRows - 1) / kHeadRows;
   LossCoef lc{P->cfg.clip_eps, P->cfg.c_value, P->cfg.c_entropy, 1.0f / (float)B};
@@ -743,40 +753,29 @@ int aslam_policy_backward_seq(aslam_policy* P, const float* params, const int16_
                                           lc, nullptr, P->hpart, P->dh_head);
   PCHK(hipGetLastError());
   PCHK(launch_reduce_heads(P->hpart, nh, params, o, grads, loss, P->cfg.c_value, P->cfg.c_entropy, st));
-  // backpropagation through time
-  for (int t = T - 1; t >= 0; --t) {
-    GruBwdArgs b{};
-    b.rows = nb; b.s0 = (int64_t)t * nb;
-    b.dh_head = P->dh_head;
-    b.dh_next = t == T - 1 ? nullptr : P->dh_buf + (int64_t)((t + 1) & 1) * nb * kHid;
-    b.g_r = P->g_r; b.g_z = P->g_z; b.g_n = P->g_n; b.g_ghn = P->g_ghn; b.hp_used = P->hp_used;
-    b.first = first + (int64_t)t * N; b.first_map = robots;
-    b.whht = P->whht; b.dgi = P->dgi; b.dgh = P->dgh;
-    b.dh_prev = P->dh_buf + (int64_t)(t & 1) * nb * kHid;
-    k_gru_bwd_step<<<grid, 256, 0, st>>>(b);
-    PCHK(hipGetLastError());
-  }
+  // backpropagation through time, and the GRU biases' column sums
   float* part = P->part;
-  // GRU weights: dW_ih = sum_s dgi[s] h1[s]^T, dW_hh = sum_s dgh[s] hp[s]^T; biases: column sums
+  uint16_t* const dgi = P->dg;
+  uint16_t* const dgh = P->dg + (int64_t)B * kGates;
+  a.whh = P->whht; a.dh_head = P->dh_head; a.dgi = dgi; a.dgh = dgh; a.part = part;
+  (rpl == 1 ? k_gru_seq_bwd<1> : rpl == 2 ? k_gru_seq_bwd<2> : k_gru_seq_bwd<4>)<<<tiles, kGruSeqThreads, kGruSeqBwdLds, st>>>(a);
+  PCHK(hipGetLastError());
+  PCHK(launch_reduce_segs(part, (int)tiles, grads, ReduceSegs{{kGates, kGates, 0, 0}, {0, 0, 0, 0}, {o.gbi, o.gbh, 0, 0}},
+                          2 * kGates, st));
+  // GRU weights: dW_ih = sum_s dgi[s] h1[s]^T, dW_hh = sum_s dgh[s] hp[s]^T
   {
     const int64_t S2 = splits_for(B, 256, kFc2Splits);
     const int S2u = slices_used(B, S2, 64);
     const int64_t n = (int64_t)kGates * kHid;
-    PCHK((gemm::run<128, 128, 64, 2, 2>(LdBF16I{P->dgi, kGates, kGates, B}, LdBF16I{P->h1, kHid, kHid, B},
+    PCHK((gemm::run<128, 128, 64, 2, 2>(LdBF16I{dgi, kGates, kGates, B}, LdBF16I{P->h1, kHid, kHid, B},
                                        EpiPartial{part, kHid, n}, kGates, kHid, B, (int)S2, st)));
     PCHK(launch_reduce(part, S2u, n, grads + o.gih, 0, n, st));
-    PCHK((gemm::run<128, 128, 64, 2, 2>(LdBF16I{P->dgh, kGates, kGates, B}, LdBF16I{P->hp_bf, kHid, kHid, B},
+    PCHK((gemm::run<128, 128, 64, 2, 2>(LdBF16I{dgh, kGates, kGates, B}, LdBF16I{P->hp_bf, kHid, kHid, B},
                                        EpiPartial{part, kHid, n}, kGates, kHid, B, (int)S2, st)));
     PCHK(launch_reduce(part, S2u, n, grads + o.ghh, 0, n, st));
-    k_colsum_bf16<<<kBiasBlocks, 256, 0, st>>>(P->dgi, B, kGates, part);
-    PCHK(hipGetLastError());
-    PCHK(launch_reduce(part, kBiasBlocks, kGates, grads + o.gbi, 0, kGates, st));
-    k_colsum_bf16<<<kBiasBlocks, 256, 0, st>>>(P->dgh, B, kGates, part);
-    PCHK(hipGetLastError());
-    PCHK(launch_reduce(part, kBiasBlocks, kGates, grads + o.gbh, 0, kGates, st));
   }
   // FC1 output gradient: dz1 = (dgi W_ih) * [h1 > 0]
-  PCHK((gemm::run<128, 128, 64, 2, 2>(LdBF16K{P->dgi, kGates, B, kGates}, LdBF16K{P->wiht, kGates, kHid, kGates},
+  PCHK((gemm::run<128, 128, 64, 2, 2>(LdBF16K{dgi, kGates, B, kGates}, LdBF16K{P->wiht, kGates, kHid, kGates},
                                      EpiReluGradBF16{P->dz1, P->h1, kHid, kHid}, B, kHid, kGates, 1, st)));
   return backward_fc1_encoder(P, params, crop, P->rows, B, grads, st);
 }

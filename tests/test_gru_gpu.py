@@ -235,3 +235,10 @@ def test_bptt_gradient_against_central_differences():
         say(f"[gru] central differences {name:10s} {e:.2e}")
         assert e < 1e-2, (name, fd, nd)
         o += n
+
+
+@pytest.mark.parametrize("T,N,nb", [(5, 9, 7), (3, 1030, 1027), (2, 2060, 2051)])
+def test_bptt_gradient_at_sequence_tile_edges(T, N, nb):
+    """The sequence kernels' one, two and four robots per lane group, each with a partly filled last tile
+    (the same bar)."""
+    test_bptt_gradient_matches_workload_precision(T, N, nb)
