@@ -82,6 +82,7 @@ struct aslam_env {
   void* d_raylen = nullptr;
   void* d_dirtab = nullptr;
   void* d_hq_lut = nullptr;
+  void* d_miss_tab = nullptr;
   void* d_visit_last = nullptr;
   void* d_prev_vcell = nullptr;
   void* d_u_prev = nullptr;
@@ -103,7 +104,7 @@ namespace {
 void free_env(aslam_env* e) {
   void** ptrs[] = {&e->d_meta, &e->d_order, &e->d_cost, &e->d_world, &e->d_belief, &e->d_pose, &e->d_est, &e->d_cov,
                    &e->d_hq_total, &e->d_step, &e->d_last_lc, &e->d_visit_t, &e->d_visit_xy, &e->d_rho,
-                   &e->d_hitc, &e->d_flags, &e->d_terms, &e->d_counters, &e->d_raylen, &e->d_dirtab, &e->d_hq_lut,
+                   &e->d_hitc, &e->d_flags, &e->d_terms, &e->d_counters, &e->d_raylen, &e->d_dirtab, &e->d_hq_lut, &e->d_miss_tab,
                    &e->d_visit_last, &e->d_prev_vcell, &e->d_u_prev, &e->d_dcells, &e->d_dmin, &e->d_draws};
   for (void** p : ptrs) {
     if (*p) (void)hipFree(*p);
@@ -142,6 +143,20 @@ void build_entropy_lut(int32_t lc, std::vector<uint32_t>& h) {
     const double ent = -(p * std::log(p) + q * std::log(q));
     h[L + lc] = (uint32_t)std::llround(ent * 4294967296.0);
   }
+}
+
+// The table the map update's apply pass reads (EnvParams::miss_tab), and whether it holds changes.
+bool build_miss_table(int32_t lc, int32_t lmiss, const std::vector<uint32_t>& h, std::vector<uint32_t>& t) {
+  t.assign(2 * lc + 2, 0u);
+  bool narrow = lmiss >= -32768 && lmiss <= 32767 && (2 * lc + 2) * 4 <= 65536;
+  for (int32_t L = -lc; L <= lc; ++L) {
+    const int64_t n = std::min<int64_t>(std::max<int64_t>((int64_t)L + lmiss, -lc), lc);
+    const int64_t d = (int64_t)h[n + lc] - (int64_t)h[L + lc];
+    if (d <= -(1 << 30) || d >= (1 << 30)) narrow = false;
+    t[L + lc] = (uint32_t)(int32_t)d;
+  }
+  if (!narrow) std::copy(h.begin(), h.end(), t.begin());
+  return narrow;
 }
 
 // Ray fan width in heading steps: the configured fov, or the full circle.
@@ -220,14 +235,16 @@ int plan_lds(aslam_env* e, const aslam_exec_config& ex, LdsPlan& L) {
   const int64_t free_bytes = budget - L.off_union;
   if (world_max > free_bytes)
     return fail(ASL_ENOTIMPL, "world window of the largest grid does not fit the LDS budget");
-  int64_t band = ex.band_rows > 0 ? ex.band_rows : free_bytes / (8 * nw_max);
-  band = std::min<int64_t>(band, rows_max);
-  // bitmaps: 2 x band x nw words, cleared with 16-byte stores (+16 B slack)
-  if (band > 8 && 8 * band * nw_max + 16 > free_bytes) band = (free_bytes - 16) / (8 * nw_max);
-  if (band < 8 || 8 * band * nw_max + 16 > free_bytes)
+  // bitmap: band x nw words, cleared with 16-byte stores (+16 B slack), then the waves' octet lists.  A
+  // budget holds a band of 8 rows when 64 bytes for each word of a row are left.
+  const int64_t list_bytes = (int64_t)(ex.threads / 64) * kApplyList * 2;
+  const int64_t fit = std::max<int64_t>((free_bytes - list_bytes - 32) / (4 * nw_max), (free_bytes - 16) / (8 * nw_max));
+  int64_t band = std::min<int64_t>({ex.band_rows > 0 ? (int64_t)ex.band_rows : fit, fit, rows_max});
+  if (band < 8 || 64 * nw_max + 16 > free_bytes)
     return fail(ASL_EINVAL, "band_rows does not fit the LDS budget (need >= 8 rows)");
   L.band_rows = (int32_t)band;
-  L.union_bytes = (int32_t)std::max<int64_t>(world_max, 8 * band * nw_max + 16);
+  L.list_off = (int32_t)align_up(4 * band * nw_max, 16);
+  L.union_bytes = (int32_t)std::max<int64_t>(world_max, L.list_off + list_bytes);
   L.total = L.off_union + L.union_bytes;
   L.record = ex.record_rays;
   L.mark_seg = ex.mark_seg;
@@ -381,6 +398,7 @@ int aslam_env_create(const aslam_env_config* cfg, int32_t n_robots, const int32_
       {&e->d_raylen, sizeof(int16_t) * (size_t)(R * n_robots)},
       {&e->d_dirtab, sizeof(int32_t) * (size_t)kNang},
       {&e->d_hq_lut, sizeof(uint32_t) * (size_t)(2 * quantise_logodds(cfg->l_clamp) + 1)},
+      {&e->d_miss_tab, sizeof(uint32_t) * (size_t)(2 * quantise_logodds(cfg->l_clamp) + 2)},
       {&e->d_visit_last, sizeof(int32_t) * (size_t)std::max<int64_t>(e->visits, 1)},
       {&e->d_prev_vcell, sizeof(int32_t) * (size_t)n_robots},
       {&e->d_u_prev, sizeof(double) * (size_t)n_robots},
@@ -410,6 +428,9 @@ int aslam_env_create(const aslam_env_config* cfg, int32_t n_robots, const int32_
   if (he == hipSuccess) he = hipMemcpy(e->d_cost, cost0.data(), sizeof(int32_t) * n_robots, hipMemcpyHostToDevice);
   if (he == hipSuccess) he = hipMemcpy(e->d_dirtab, dirtab.data(), sizeof(int32_t) * kNang, hipMemcpyHostToDevice);
   if (he == hipSuccess) he = hipMemcpy(e->d_hq_lut, lut.data(), sizeof(uint32_t) * lut.size(), hipMemcpyHostToDevice);
+  std::vector<uint32_t> tab;
+  const bool narrow = build_miss_table(lc, quantise_logodds(cfg->l_miss), lut, tab);
+  if (he == hipSuccess) he = hipMemcpy(e->d_miss_tab, tab.data(), sizeof(uint32_t) * tab.size(), hipMemcpyHostToDevice);
   if (he == hipSuccess) he = hipMemset(e->d_draws, 0, sizeof(uint64_t) * (size_t)n_robots);
   if (he == hipSuccess) he = hipDeviceSynchronize();
   if (he == hipSuccess) he = hipStreamCreateWithFlags(&e->capture_stream, hipStreamNonBlocking);
@@ -494,6 +515,8 @@ int aslam_env_create(const aslam_env_config* cfg, int32_t n_robots, const int32_
   P.raylen = (int16_t*)e->d_raylen;
   P.dirtab = (const int32_t*)e->d_dirtab;
   P.hq_lut = (const uint32_t*)e->d_hq_lut;
+  P.miss_tab = (const uint32_t*)e->d_miss_tab;
+  P.narrow = narrow ? 1 : 0;
   P.visit_last = (int32_t*)e->d_visit_last;
   P.prev_vcell = (int32_t*)e->d_prev_vcell;
   P.u_prev = (double*)e->d_u_prev;

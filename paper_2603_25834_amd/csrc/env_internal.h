@@ -82,6 +82,8 @@ struct EnvParams {
   int16_t* raylen;       // [n,R] steps of each ray's last LiDAR walk (lane-order key)
   const int32_t* dirtab; // [kNang] (cos & 0xffff) | (sin << 16), Q14
   const uint32_t* hq_lut;// [2*lclamp+1] binary entropy, 2^-32 nat
+  int32_t narrow;        // 1: miss_tab holds the entropy change of a MISS (int32) at each log-odds, then a 0;
+  const uint32_t* miss_tab;  // 0 (changes beyond 2^30, log-odds beyond 16 bits): the entropies [2*lclamp+2]
   int32_t* visit_last;   // [sum v^2] last step the robot was in each visit cell, -1 never
   int32_t* prev_vcell;   // [n] visit cell of the previous step, -1 after reset
   double* u_prev;        // [n] U_{t-1} = cbrt(det Sigma) of the previous step
@@ -132,10 +134,14 @@ struct LdsPlan {
   int32_t total;
   int32_t union_bytes;
   int32_t band_rows;      // code-window rows per pass
+  int32_t list_off;       // the waves' octet lists of the apply pass, bytes into the union
   int32_t world_halo;     // rows staged around the robot: rhat_cells + 3
   int32_t record;         // fused: write rho / hitc to the state
   int32_t mark_seg;       // map update's walk: 0 one lane per ray, else segments of this many steps
 };
+
+// Entries of a wave's octet list (uint16): the octets of 64 bitmap words.
+constexpr int kApplyList = 256;
 
 struct ExecState;
 

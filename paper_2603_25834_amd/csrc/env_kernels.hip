@@ -12,9 +12,9 @@
 // spread over the workgroup's lanes; each lane walks its ray through the grid
 // with an exact integer DDA (32-bit decision variable, no division in the
 // loop).  The LiDAR march reads the robot's world bits from LDS.  The map
-// update marks a per-scan code window in LDS (two bitmaps: MISS and HIT;
-// OR-ing bits makes the result independent of ray and lane order), then a
-// coalesced pass applies one saturating int16 add to each coded cell and
+// update marks a per-scan bitmap of visited cells in LDS (OR-ing bits makes
+// the result independent of ray and lane order), takes the hit cells out of
+// it, then applies one saturating int16 add to each coded cell and
 // accumulates the exact entropy change in int64.
 #include <algorithm>
 
@@ -361,13 +361,13 @@ struct RobotShared {
 
 // Pointers into the dynamic LDS of a per-robot kernel.
 struct LdsView {
-  uint32_t* lut;     // binary entropy table
+  uint32_t* lut;     // EnvParams::miss_tab
   int32_t* rho;      // [R] range (Q16) | bit 31 = hit
   int32_t* perm;     // [R] ray of each lane slot, longest walk first (march); steps of each ray (mark)
   int32_t* seg;      // [R] first walk segment of each ray (mark)
   int32_t* hist;     // [64] sort buckets
   RobotShared* sh;
-  uint32_t* uni;     // world rows, then the code bitmaps
+  uint32_t* uni;     // world rows, then the code bitmap and the waves' octet lists
 };
 
 __device__ __forceinline__ LdsView lds_view(unsigned char* smem, const LdsPlan& L) {
@@ -400,6 +400,17 @@ struct RaySetup {
   int32_t gend;            // 1: the walk ends by leaving the grid (else by the limit)
 };
 
+// floor(n / d) for n < 2^28 and 0 < d <= 2^15 when the quotient is at most 2^14 (the estimate's relative
+// error is below 2^-21, so it is one off at most and the remainder corrects it); a larger quotient
+// comes out larger than 2^13.  A 32-bit integer division by a variable is three times as long, a 64-bit
+// one ten times, and a ray's set-up and end take two of them.
+__device__ __forceinline__ int32_t div_small(int32_t n, int32_t d) {
+  int32_t q = (int32_t)((float)n * __builtin_amdgcn_rcpf((float)d));
+  const int32_t r = n - q * d;
+  q += r < 0 ? -1 : (r >= d ? 1 : 0);
+  return q;
+}
+
 __device__ __forceinline__ RaySetup ray_setup(int32_t ox, int32_t oy, int32_t a, int32_t b, int32_t lim,
                                               int32_t s) {
   RaySetup q;
@@ -429,32 +440,47 @@ __device__ __forceinline__ RaySetup ray_setup(int32_t ox, int32_t oy, int32_t a,
   } else if (bb == 0) {
     q.kx = q.nx; q.ky = 0; q.gend = q.gx;
   } else {
-    const int64_t Tx = (int64_t)(ex0 + (int64_t)q.nx * kQ16) * bb;
-    const int64_t Ty = (int64_t)(ey0 + (int64_t)q.ny * kQ16) * aa;
-    if (Tx <= Ty) {
-      // y crossings j strictly before it: (ey0 + j*65536)*aa < Tx
-      const int64_t X = Tx - (int64_t)ey0 * aa;
-      const int64_t den = (int64_t)aa << 16;
-      const int32_t cnt = X <= 0 ? 0 : (int32_t)((X + den - 1) / den);
-      q.kx = q.nx; q.ky = min(cnt, q.ny); q.gend = q.gx;
-    } else {
-      // x crossings k at or before it: (ex0 + k*65536)*bb <= Ty
-      const int64_t Y = Ty - (int64_t)ex0 * bb;
-      const int64_t den = (int64_t)bb << 16;
-      const int32_t cnt = Y < 0 ? 0 : (int32_t)(Y / den) + 1;
-      q.kx = min(cnt, q.nx); q.ky = q.ny; q.gend = q.gy;
-    }
+    const int64_t Tx = (int64_t)(ex0 + q.nx * kQ16) * bb;
+    const int64_t Ty = (int64_t)(ey0 + q.ny * kQ16) * aa;
+    // x first: the y crossings j strictly before it, (ey0 + j*65536)*aa < Tx; else the x crossings k at or
+    // before it, (ex0 + k*65536)*bb <= Ty.  floor(v / (65536 d)) = floor(floor(v / 65536) / d); a count
+    // above the allowed steps (at most 4096) is cut to them.
+    const bool xf = Tx <= Ty;
+    const int64_t v = xf ? Tx - (int64_t)ey0 * aa - 1 : Ty - (int64_t)ex0 * bb;
+    const int32_t cnt = v < 0 ? 0 : div_small((int32_t)(v >> 16), xf ? aa : bb) + 1;
+    q.kx = xf ? q.nx : min(cnt, q.nx);
+    q.ky = xf ? min(cnt, q.ny) : q.ny;
+    q.gend = xf ? q.gx : q.gy;
   }
   q.n = q.kx + q.ky;
   return q;
 }
 
-// Entry axis of the cell reached after at least one step: with D in
-// (-DY, DX], an x step leaves D in (DX-DY, DX] and a y step in (-DY, DX-DY].
-__device__ __forceinline__ bool last_step_x(const RaySetup& q, int32_t D) {
+// x steps among the first i >= 1 steps of a walk with start value D0: with the decision variable after
+// them in (-DY, DX] and equal to D0 + kx DX - (i - kx) DY, kx = floor((i DY - D0 + DX) / (DX + DY)).  In 32
+// bits: with D0 = 65536 q + rr (0 <= rr < 65536) and M = i aa + bb - q >= 0 it is floor(M / (aa + bb)) when
+// rr = 0, else floor((M - 1) / (aa + bb)); axis rays take x steps only (D0 = -1) or y steps only (D0 = 1).
+__device__ __forceinline__ int32_t x_steps(int32_t i, int32_t D0, int32_t aa, int32_t bb) {
+  if (aa == 0 || bb == 0) return D0 <= 0 ? i : 0;
+  const int32_t M = i * aa + bb - (D0 >> 16) - ((D0 & 0xffff) != 0 ? 1 : 0);
+  return div_small(M, aa + bb);
+}
+
+// Entry axis of the cell reached after i >= 1 steps, kx of them along x: the decision variable before
+// the last step was <= 0 iff that step went along x; with D in (-DY, DX] after it, an x step leaves
+// D in (DX-DY, DX] and a y step in (-DY, DX-DY].
+__device__ __forceinline__ bool last_step_x(const RaySetup& q, int32_t i, int32_t kx) {
   if (q.aa == 0) return false;
   if (q.bb == 0) return true;
+  const int32_t D = q.D + (int32_t)((uint32_t)(kx * q.bb - (i - kx) * q.aa) << 16);
   return D > q.DX - q.DY;
+}
+
+// Range (Q16) to the entry face at axis distance E (Q16) along an axis whose direction component is d:
+// ceil(E 2^14 / d), at most 2^28, in two divisions with quotients up to 2^14.
+__device__ __forceinline__ int32_t face_range(int32_t E, int32_t d) {
+  const int32_t q = div_small(E, d);
+  return (q << 14) + div_small(((E - q * d) << 14) + d - 1, d);
 }
 
 __device__ __forceinline__ int32_t wave_max_i32(int32_t v) {
@@ -617,7 +643,7 @@ __device__ void march_rays(const EnvParams& P, const RobotMeta& m, const LdsView
     // words around the staged rows) but never count as hits.
     while (__builtin_amdgcn_ballot_w64(!done) != 0) {
       if (!done) {
-        int32_t l[kLook], d[kLook];
+        int32_t l[kLook];
         int32_t lc = li, dc = D;
 #pragma unroll
         for (int u = 0; u < kLook; ++u) {
@@ -625,7 +651,6 @@ __device__ void march_rays(const EnvParams& P, const RobotMeta& m, const LdsView
           lc += stepx ? sx : sy;
           dc += stepx ? q.DX : -q.DY;
           l[u] = lc;
-          d[u] = dc;
         }
         uint32_t wd[kLook];
 #pragma unroll
@@ -635,44 +660,25 @@ __device__ void march_rays(const EnvParams& P, const RobotMeta& m, const LdsView
         for (int u = 0; u < kLook; ++u) bits |= __builtin_amdgcn_ubfe(wd[u], (uint32_t)l[u], 1u) << u;
         const int32_t rem = q.n - i;   // >= 1 while the lane walks
         bits &= rem >= kLook ? (1u << kLook) - 1u : ((1u << rem) - 1u);
-        if (bits) {
-          const int32_t u = __builtin_ctz(bits);
-#pragma unroll
-          for (int j = 0; j < kLook; ++j) {
-            if (u == j) {
-              li = l[j];
-              D = d[j];
-            }
-          }
-          i += u + 1;
-          hit = true;
-          done = true;
-        } else {
-          li = l[kLook - 1];
-          D = d[kLook - 1];
-          i = min(i + kLook, q.n);
-          done = i >= q.n;
-        }
+        // a hit ends the walk at its step; where that is follows from the step count below
+        hit = bits != 0u;
+        i = hit ? i + __builtin_ctz(bits) + 1 : min(i + kLook, q.n);
+        done = hit || i >= q.n;
+        li = lc;
+        D = dc;
       }
     }
     if (active) {
       visits += i + 1;
       raylen[k] = (int16_t)min(i, 32767);
       if (hit) {
-        cell = li + wy0 * s;
+        cell = cy0 * s + cx0;
+        rq = 0;
         if (i > 0) {
-          const int32_t row = li / s;
-          if (last_step_x(q, D)) {
-            const int32_t kx = abs(li - row * s - cx0);
-            const int64_t E = (int64_t)q.ex0 + (int64_t)(kx - 1) * kQ16;
-            rq = (int32_t)((E * kDirOne + q.aa - 1) / q.aa);
-          } else {
-            const int32_t ky = abs(row + wy0 - cy0);
-            const int64_t E = (int64_t)q.ey0 + (int64_t)(ky - 1) * kQ16;
-            rq = (int32_t)((E * kDirOne + q.bb - 1) / q.bb);
-          }
-        } else {
-          rq = 0;
+          const int32_t kx = x_steps(i, q.D, q.aa, q.bb), ky = i - kx;
+          cell += kx * sx + ky * sy;
+          rq = last_step_x(q, i, kx) ? face_range(q.ex0 + (kx - 1) * kQ16, q.aa)
+                                     : face_range(q.ey0 + (ky - 1) * kQ16, q.bb);
         }
       }
     }
@@ -711,83 +717,151 @@ __device__ __forceinline__ long long wave_sum_i64(long long v) {
   return v;
 }
 
-// One saturating add per coded cell of a band of the code window.  The band
-// is split into octets (8 cells, one 16-byte access, 16-byte aligned because
-// the window starts on a 32-cell boundary); each thread keeps U octets in
-// flight, so a band costs few HBM round trips.  An octet is owned by one
-// thread, so the read-modify-write is race-free; uncoded cells of a touched
-// octet are written back unchanged, untouched octets are neither read nor
-// written.
-template <int NT, int U>
-__device__ __forceinline__ void apply_band(const EnvParams& P, const uint32_t* miss, const uint32_t* hitm,
-                                           int32_t rows, int32_t nw, int16_t* band_base, int32_t s,
-                                           const uint32_t* lut, long long& dh, int32_t& ncoded) {
-  const int32_t lpr = nw * 4;  // octets per row
-  const int32_t total = rows * lpr;
-  int32_t row = (int32_t)threadIdx.x / lpr;
-  int32_t col = (int32_t)threadIdx.x - row * lpr;
-  const int32_t qa = NT / lpr, ra = NT - qa * lpr;
-  const int32_t lc = P.lclamp;
-  for (int32_t o = threadIdx.x; o < total; o += U * NT) {
-    uint32_t code[U];   // miss bits | hit bits << 8
-    int32_t off[U];
+// Row of word w of a bitmap with nw words a row, magic = floor((2^32 - 1) / nw) + 1 mod 2^32 (0 for one
+// word a row): exact while w nw < 2^32.
+__device__ __forceinline__ int32_t word_row(uint32_t w, uint32_t magic) {
+  return (int32_t)(magic ? __umulhi(w, magic) : w);
+}
+
+typedef int16_t i16x2 __attribute__((ext_vector_type(2)));
+
+// One saturating add per MISS cell of a band of the code window (the hit cells are not in the bitmap
+// any more, take_hits).  Cells are read and written in octets (8 cells, one 16-byte access, 16-byte
+// aligned because the window starts on a 32-cell boundary); only octets with a coded cell are touched,
+// their other cells are written back unchanged.  An octet is owned by one lane, so the
+// read-modify-write is race-free.  About a third of the window's octets hold a coded cell (the box
+// around a star-shaped scan), so each wave first gathers those of its 64 words into a list of its own
+// in LDS (256 entries: octet | MISS bits << 8), then takes the list a lane per octet; with a lane per
+// octet of the box the pass issued 2.5 times the instructions.  The adds run on two cells at a
+// time (packed int16), and the entropy change of a MISS is one table read per cell (index (L + lc) * 4,
+// entry 2 lc + 1 = 0 for the octet's uncoded cells).  750 robots, first steps: 16.3 -> 6.4 us of a workgroup.
+template <int NT>
+__device__ __forceinline__ void apply_band(const EnvParams& P, const uint32_t* miss, int32_t rows, int32_t nw,
+                                           uint32_t nw_magic, int16_t* band_base, int32_t s, const uint32_t* tab,
+                                           uint16_t* list, long long& dh, int32_t& ncoded) {
+  const int32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int32_t words = rows * nw, lc = P.lclamp;
+  list += wave * kApplyList;
+  const i16x2 lcp = {(int16_t)lc, (int16_t)lc}, lmp = {(int16_t)P.lmiss, (int16_t)P.lmiss};
+  const i16x2 zero_entry = {(int16_t)(2 * lc + 1), (int16_t)(2 * lc + 1)};
+  for (int32_t w0 = wave * 64; w0 < words; w0 += NT) {
+    const uint32_t m = w0 + lane < words ? miss[w0 + lane] : 0u;
+    ncoded += __builtin_popcount(m);
+    int32_t total = 0;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      uint32_t wm = 0u, wh = 0u;
-      if (o + u * NT < total) {
-        wm = miss[row * nw + (col >> 2)];
-        wh = hitm[row * nw + (col >> 2)];
+    for (int b = 0; b < 4; ++b) {
+      const uint32_t code = (m >> (8 * b)) & 0xffu;
+      const uint64_t some = __builtin_amdgcn_ballot_w64(code != 0u);
+      const int32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(some >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)some, total));
+      if (code) list[pos] = (uint16_t)((lane * 4 + b) | (code << 8));
+      total += __builtin_popcountll(some);
+    }
+    __builtin_amdgcn_wave_barrier();
+    for (int32_t e0 = 0; e0 < total; e0 += 128) {
+      uint32_t code[2];
+      int4* at[2];
+      int4 v[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int32_t e = e0 + 64 * u + lane;
+        const uint32_t ent = e < total ? list[e] : 0u;
+        code[u] = ent >> 8;
+        const uint32_t w = (uint32_t)w0 + ((ent & 0xffu) >> 2);
+        const int32_t row = word_row(w, nw_magic);
+        const int32_t col = (int32_t)w - row * nw;
+        at[u] = reinterpret_cast<int4*>(band_base + (row * s + col * 32 + (int32_t)(ent & 3u) * 8));
+        if (code[u]) v[u] = *at[u];
       }
-      const int32_t sh = (col & 3) * 8;
-      code[u] = ((wm >> sh) & 0xffu) | (((wh >> sh) & 0xffu) << 8);
-      off[u] = row * s + col * 8;
-      col += ra;
-      row += qa;
-      if (col >= lpr) { col -= lpr; ++row; }
-    }
-    int4 v[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (code[u]) v[u] = *reinterpret_cast<const int4*>(band_base + off[u]);
-    }
+      for (int u = 0; u < 2; ++u) {
+        if (!code[u]) continue;
+        int32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+        if (P.narrow) {
+          int32_t d[8];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const uint32_t ch = code[u] >> 8;
-      const uint32_t any = (code[u] | ch) & 0xffu;
-      if (!any) continue;
-      ncoded += __builtin_popcount(any);
-      int32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+          for (int j = 0; j < 4; ++j) {
+            const i16x2 l = __builtin_bit_cast(i16x2, w[j]);
+            const uint32_t two = code[u] >> (2 * j);
+            const i16x2 any = i16x2{0, 0} - __builtin_bit_cast(i16x2, (two | (two << 15)) & 0x10001u);
+            const i16x2 n = __builtin_elementwise_min(
+                __builtin_elementwise_max(__builtin_elementwise_add_sat(l, any & lmp), -lcp), lcp);
+            w[j] = __builtin_bit_cast(int32_t, n);
+            const uint32_t i4 =
+                __builtin_bit_cast(uint32_t, (((l + lcp) & any) | (zero_entry & ~any)) << i16x2{2, 2});
+            d[2 * j] = *reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(tab) + (i4 & 0xffffu));
+            d[2 * j + 1] = *reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(tab) + (i4 >> 16));
+          }
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int32_t l0 = (int16_t)(w[j] & 0xffff), l1 = w[j] >> 16;
-        int32_t n0 = l0, n1 = l1;
-        if ((any >> (2 * j)) & 1u) {
-          n0 = min(max(l0 + (((ch >> (2 * j)) & 1u) ? P.lhit : P.lmiss), -lc), lc);
-          dh += (long long)lut[n0 + lc] - (long long)lut[l0 + lc];
+          for (int j = 0; j < 4; ++j) dh += d[2 * j] + d[2 * j + 1];   // |entries| < 2^30
+        } else {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            if (!((code[u] >> j) & 1u)) continue;
+            const int32_t sh = (j & 1) * 16;
+            const int32_t l = (int16_t)(w[j >> 1] >> sh);
+            const int32_t n = min(max(l + P.lmiss, -lc), lc);
+            dh += (long long)tab[n + lc] - (long long)tab[l + lc];
+            w[j >> 1] = (w[j >> 1] & ~(0xffff << sh)) | ((n & 0xffff) << sh);
+          }
         }
-        if ((any >> (2 * j + 1)) & 1u) {
-          n1 = min(max(l1 + (((ch >> (2 * j + 1)) & 1u) ? P.lhit : P.lmiss), -lc), lc);
-          dh += (long long)lut[n1 + lc] - (long long)lut[l1 + lc];
-        }
-        w[j] = (n0 & 0xffff) | (n1 << 16);
+        *at[u] = make_int4(w[0], w[1], w[2], w[3]);
       }
-      *reinterpret_cast<int4*>(band_base + off[u]) = make_int4(w[0], w[1], w[2], w[3]);
     }
+    __builtin_amdgcn_wave_barrier();   // the list is read before the next words overwrite it
   }
 }
 
-constexpr int kApplyInFlight = 4;
+// A hit cell this lane owns: its belief cell and the value before the scan (NULL: none).
+struct HitCell {
+  int16_t* at;
+  int32_t l;
+};
 
-// The map update's mark pass over one band: the MISS bit of every cell the walks of all rays visit
-// inside the band and the HIT bit of each hit's last cell, for rays from the Q16 origin (eox, eoy)
+// The last cell of a ray whose walk ended at its hit (bit we of the band's bitmap, -1: none): HIT beats
+// MISS, so its bit is taken out of the bitmap; the lane that finds it still set (every walk marked its
+// last cell) owns the cell and reads its value, however many rays end there.
+__device__ __forceinline__ HitCell take_hit(int32_t we, uint32_t* miss, int32_t nw, uint32_t nw_magic,
+                                            int16_t* band_base, int32_t s) {
+  HitCell h{nullptr, 0};
+  if (we < 0) return h;
+  const uint32_t bit = 1u << (we & 31), w = (uint32_t)we >> 5;
+  if (!(atomicAnd(&miss[w], ~bit) & bit)) return h;
+  const int32_t row = word_row(w, nw_magic);
+  h.at = band_base + (row * s + ((int32_t)w - row * nw) * 32 + (we & 31));
+  h.l = *h.at;
+  return h;
+}
+
+__device__ __forceinline__ void apply_hit(const EnvParams& P, const HitCell& h, long long& dh, int32_t& ncoded) {
+  if (!h.at) return;
+  const int32_t lc = P.lclamp;
+  const int32_t n = min(max(h.l + P.lhit, -lc), lc);
+  *h.at = (int16_t)n;
+  ++ncoded;
+  dh += (long long)P.hq_lut[n + lc] - (long long)P.hq_lut[h.l + lc];
+}
+
+// Bitmap index of the last cell of ray k's walk when it is a hit inside the band, else -1.
+__device__ __forceinline__ int32_t hit_bit(const EnvParams& P, int32_t pk, int32_t k, int32_t s, int32_t eox,
+                                           int32_t eoy, int32_t ib, int32_t w0, int32_t rowbits, uint32_t band_bits) {
+  if (pk >= 0) return -1;
+  const int32_t dv = ray_dir(P, ib, k);
+  const int32_t a = (int16_t)(dv & 0xffff), b = dv >> 16;
+  const RaySetup q = ray_setup(eox, eoy, a, b, pk & 0x7fffffff, s);
+  const int32_t we = w0 + q.kx * (a > 0 ? 1 : -1) + q.ky * (b > 0 ? rowbits : -rowbits);
+  return !q.gend && (uint32_t)we < band_bits ? we : -1;
+}
+
+// The map update's mark pass over one band: the bit of every cell the walks of all rays visit inside
+// the band, for rays from the Q16 origin (eox, eoy)
 // with heading index ib of ray 0 and the ranges of rho_lds; bit index (cy - by0) * rowbits + (cx - x0w).
 // Two forms with identical results.  One lane per ray (mark_rays): lane slots ordered by the walk
 // length, so a wave's trip count stays close to its lanes' own; the pass lasts as long as the longest
 // walk.  Segments (mark_segments): a ray of n steps is cut into ceil(n / seg) segments and the lanes
 // take the segments of all rays in turn, so the pass lasts about (total steps / lanes) steps plus a
-// setup per segment; a segment starts from the DDA state after i0 steps in closed form: with the
-// decision variable after i >= 1 steps in (-DY, DX] and equal to D0 + kx DX - (i - kx) DY, kx (the
-// x steps among them) is floor((i DY - D0 + DX) / (DX + DY)).  Which is faster depends on how many
+// setup per segment; a segment starts from the DDA state after i0 steps in closed form (x_steps).  Each
+// leaves in `we` the bitmap index of the last cell of the thread's first ray if that is a hit in the
+// band, else -1.  Which is faster depends on how many
 // robots share a CU (measured by the autotuner).
 // Lane slots ordered by the walk length estimated from the range (once for all bands of mark_rays).
 template <int NT>
@@ -803,7 +877,8 @@ __device__ void sort_mark_rays(const EnvParams& P, const int32_t* rho_lds, int32
 template <int NT>
 __device__ void mark_rays(const EnvParams& P, const int32_t* rho_lds, const int32_t* perm, int32_t s, int32_t eox,
                           int32_t eoy, int32_t ib, int32_t by0, int32_t x0w, int32_t rowbits, uint32_t band_bits,
-                          bool one_band, bool count_visits, uint32_t* miss, uint32_t* hitm, int32_t& uvisits) {
+                          bool one_band, bool count_visits, uint32_t* miss, int32_t& uvisits, int32_t& we0) {
+  we0 = -1;
   const int32_t ecx = eox >> 16, ecy = eoy >> 16;
   for (int32_t k0 = 0; k0 < P.R; k0 += NT) {
     const int32_t j = k0 + (int32_t)threadIdx.x;
@@ -851,7 +926,7 @@ __device__ void mark_rays(const EnvParams& P, const int32_t* rho_lds, const int3
     if (valid) {
       if (count_visits) uvisits += n + 1;
       const int32_t we = w0 + q.kx * sx + q.ky * sy;   // last visited cell
-      if (hit && !q.gend && (uint32_t)we < band_bits) atomicOr(&hitm[we >> 5], 1u << (we & 31));
+      if (k0 == 0 && hit && !q.gend && (uint32_t)we < band_bits) we0 = we;
     }
   }
 }
@@ -861,12 +936,13 @@ template <int NT>
 __device__ void mark_segments(const EnvParams& P, const int32_t* rho_lds, int32_t* nray, int32_t* segoff,
                               int32_t* hist, int32_t s, int32_t eox, int32_t eoy, int32_t ib, int32_t by0, int32_t x0w,
                               int32_t rowbits, uint32_t band_bits, bool one_band, bool count_visits, int32_t seg,
-                              uint32_t* miss, uint32_t* hitm, int32_t& uvisits) {
+                              uint32_t* miss, int32_t& uvisits, int32_t& we0) {
+  we0 = -1;
   constexpr int NWAVE = NT / 64;
   const int32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int32_t R = P.R;
   const int32_t w0 = ((eoy >> 16) - by0) * rowbits + ((eox >> 16) - x0w);   // the origin cell
-  // per ray: its step count, the HIT bit of its last cell, its visits
+  // per ray: its step count, its last cell, its visits
   for (int32_t k = tid; k < R; k += NT) {
     const int32_t pk = rho_lds[k];
     const int32_t dv = ray_dir(P, ib, k);
@@ -874,7 +950,7 @@ __device__ void mark_segments(const EnvParams& P, const int32_t* rho_lds, int32_
     const RaySetup q = ray_setup(eox, eoy, a, b, pk & 0x7fffffff, s);
     nray[k] = q.n;
     const int32_t we = w0 + q.kx * (a > 0 ? 1 : -1) + q.ky * (b > 0 ? rowbits : -rowbits);   // last visited cell
-    if (pk < 0 && !q.gend && (uint32_t)we < band_bits) atomicOr(&hitm[we >> 5], 1u << (we & 31));
+    if (k == tid && pk < 0 && !q.gend && (uint32_t)we < band_bits) we0 = we;
     if (count_visits) uvisits += q.n + 1;
   }
   if (tid == 0 && (uint32_t)w0 < band_bits) atomicOr(&miss[w0 >> 5], 1u << (w0 & 31));   // every walk's first cell
@@ -883,7 +959,7 @@ __device__ void mark_segments(const EnvParams& P, const int32_t* rho_lds, int32_
   const int32_t per = (R + NT - 1) / NT;
   const int32_t k0 = min(R, tid * per), k1 = min(R, k0 + per);
   int32_t loc = 0;
-  for (int32_t k = k0; k < k1; ++k) loc += (nray[k] + seg - 1) / seg;
+  for (int32_t k = k0; k < k1; ++k) loc += div_small(nray[k] + seg - 1, seg);
   int32_t inc = loc;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
@@ -901,7 +977,7 @@ __device__ void mark_segments(const EnvParams& P, const int32_t* rho_lds, int32_
   }
   for (int32_t k = k0; k < k1; ++k) {
     segoff[k] = run;
-    run += (nray[k] + seg - 1) / seg;
+    run += div_small(nray[k] + seg - 1, seg);
   }
   __syncthreads();
   const uint32_t last_word = (band_bits >> 5) - 1u;
@@ -935,22 +1011,10 @@ __device__ void mark_segments(const EnvParams& P, const int32_t* rho_lds, int32_
       }
       sx = a > 0 ? 1 : -1;
       sy = b > 0 ? rowbits : -rowbits;
-      int32_t kx = 0;
-      if (i0 > 0) {
-        if (DX + DY == 0) {
-          kx = D0 <= 0 ? i0 : 0;   // axis rays: x steps only (D = -1) or y steps only (D = 1)
-        } else {
-          // floor((i0 DY - D0 + DX) / (DX + DY)) in 32 bits: with D0 = 65536 q + rr (0 <= rr < 65536) and
-          // M = i0 aa + bb - q >= 0 it is floor(M / (aa + bb)) when rr = 0, else floor((M - 1) / (aa + bb))
-          const int32_t aa = DY >> 16, bb = DX >> 16;
-          const int32_t q = D0 >> 16, rr = D0 & 0xffff;
-          const int32_t M = i0 * aa + bb - q - (rr != 0 ? 1 : 0);
-          kx = (int32_t)((uint32_t)M / (uint32_t)(aa + bb));
-        }
-      }
+      const int32_t kx = i0 > 0 ? x_steps(i0, D0, aa, bb) : 0;
       const int32_t ky = i0 - kx;
       wi = w0 + kx * sx + ky * sy;
-      D = D0 + (int32_t)((uint32_t)(kx * (DX >> 16) - ky * (DY >> 16)) << 16);
+      D = D0 + (int32_t)((uint32_t)(kx * bb - ky * aa) << 16);
     }
     // Uniform trip counts over the wave.  While every lane is within its own segment and the band
     // holds the whole window, every step lands in the bitmap (the window holds every visited cell),
@@ -998,7 +1062,8 @@ __device__ void update_and_reward(const EnvParams& P, const StepArgs& A, const R
     const int32_t rowbits = nw << 5;
     const int32_t band = L.band_rows;
     uint32_t* miss = uni;
-    uint32_t* hitm = uni + band * nw;
+    uint16_t* list = reinterpret_cast<uint16_t*>(reinterpret_cast<unsigned char*>(uni) + L.list_off);
+    const uint32_t nw_magic = 0xffffffffu / (uint32_t)nw + 1u;
     const int64_t base = m.cell_off;
     if (!SEG) sort_mark_rays<NT>(P, rho_lds, V.perm, V.hist, ib);
     for (int32_t by0 = y0; by0 <= y1; by0 += band) {
@@ -1007,21 +1072,33 @@ __device__ void update_and_reward(const EnvParams& P, const StepArgs& A, const R
       const bool one_band = y1 - y0 + 1 <= band;
       {
         uint4* u4 = reinterpret_cast<uint4*>(uni);
-        const int32_t nclr = (2 * band * nw + 3) >> 2;
+        const int32_t nclr = (rows * nw + 3) >> 2;
         for (int32_t k = threadIdx.x; k < nclr; k += NT) u4[k] = make_uint4(0u, 0u, 0u, 0u);
       }
       __syncthreads();
+      int32_t we0;
       if (SEG)
         mark_segments<NT>(P, rho_lds, V.perm, V.seg, V.hist, s, eox, eoy, ib, by0, x0w, rowbits, band_bits, one_band,
-                          by0 == y0, L.mark_seg, miss, hitm, uvisits);
+                          by0 == y0, L.mark_seg, miss, uvisits, we0);
       else
         mark_rays<NT>(P, rho_lds, V.perm, s, eox, eoy, ib, by0, x0w, rowbits, band_bits, one_band, by0 == y0, miss,
-                      hitm, uvisits);
+                      uvisits, we0);
       __syncthreads();
-      // apply: each coded cell once (8 cells = one 16-byte access per octet)
-      apply_band<NT, kApplyInFlight>(P, miss, hitm, rows, nw, P.belief + base + (int64_t)by0 * s + x0w, s, V.lut, dh,
-                                     ncoded);
+      // the hit cells leave the bitmap; each one's owner reads its value now and adds to it after the
+      // MISS cells are done (whose octets may hold it), so the read's latency passes meanwhile
+      int16_t* const base_cell = P.belief + base + (int64_t)by0 * s + x0w;
+      const HitCell h0 = take_hit(we0, miss, nw, nw_magic, base_cell, s);
+      const int32_t w0 = (ecy - by0) * rowbits + (ecx - x0w);
+      for (int32_t j = (int32_t)threadIdx.x + NT; j < P.R; j += NT) {   // more rays than threads: from scratch
+        const int32_t k = SEG ? j : V.perm[j];
+        const HitCell h = take_hit(hit_bit(P, rho_lds[k], k, s, eox, eoy, ib, w0, rowbits, band_bits), miss, nw,
+                                   nw_magic, base_cell, s);
+        apply_hit(P, h, dh, ncoded);
+      }
       __syncthreads();
+      apply_band<NT>(P, miss, rows, nw, nw_magic, base_cell, s, V.lut, list, dh, ncoded);
+      __syncthreads();
+      apply_hit(P, h0, dh, ncoded);
     }
   }
   dh = wave_sum_i64(dh);
@@ -1133,7 +1210,7 @@ __global__ __launch_bounds__(NT) void k_update(EnvParams P, StepArgs A, LdsPlan 
   RobotShared* sh = V.sh;
   const int32_t r = blockIdx.x;
   const RobotMeta m = P.meta[r];
-  for (int32_t i = threadIdx.x; i < 2 * P.lclamp + 1; i += NT) V.lut[i] = P.hq_lut[i];
+  for (int32_t i = threadIdx.x; i < 2 * P.lclamp + 2; i += NT) V.lut[i] = P.miss_tab[i];
   if (threadIdx.x == 0) {
     const float* e = P.est + 3 * (int64_t)r;
     sh->eox = to_q16(e[0], P.inv_c16);
@@ -1246,7 +1323,7 @@ template <int NT, bool SEG>
 __global__ __launch_bounds__(NT, SEG ? 6 : 1) void k_fused(EnvParams P, StepArgs A, LdsPlan L) {
   extern __shared__ __align__(16) unsigned char smem[];
   const LdsView V = lds_view(smem, L);
-  for (int32_t i = threadIdx.x; i < 2 * P.lclamp + 1; i += NT) V.lut[i] = P.hq_lut[i];
+  for (int32_t i = threadIdx.x; i < 2 * P.lclamp + 2; i += NT) V.lut[i] = P.miss_tab[i];
   fused_robot<NT, SEG>(P, A, L, V, P.order[blockIdx.x]);
 }
 
@@ -1257,7 +1334,7 @@ template <int NT, bool SEG>
 __global__ __launch_bounds__(NT, 4) void k_fused_persist(EnvParams P, StepArgs A, LdsPlan L) {
   extern __shared__ __align__(16) unsigned char smem[];
   const LdsView V = lds_view(smem, L);
-  for (int32_t i = threadIdx.x; i < 2 * P.lclamp + 1; i += NT) V.lut[i] = P.hq_lut[i];
+  for (int32_t i = threadIdx.x; i < 2 * P.lclamp + 2; i += NT) V.lut[i] = P.miss_tab[i];
   for (int32_t w = blockIdx.x; w < P.n; w += gridDim.x) {
     fused_robot<NT, SEG>(P, A, L, V, P.order[w]);
     __syncthreads();

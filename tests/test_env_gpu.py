@@ -228,3 +228,22 @@ def test_full_batch_sampled(name, steps, exec_kw):
     offs = np.concatenate([[0], np.cumsum(full.b.sides.astype(np.int64) ** 2)])
     got = np.concatenate([bel[offs[i]:offs[i + 1]] for i in pick])
     assert np.array_equal(got, orc.belief)
+
+
+@pytest.mark.parametrize("over", [dict(), dict(l_miss=-3.0, l_hit=6.0, l_clamp=12.0),
+                                  dict(l_clamp=40.0), dict(l_miss=0.4)],
+                         ids=["table", "large_changes", "wide_clamp", "positive_miss"])
+@pytest.mark.parametrize("exec_kw", [dict(form=1, threads=128, record_rays=1), dict(form=0, threads=128, mark_seg=8)],
+                         ids=["fused_rays", "plain_segments"])
+def test_map_update_forms(monkeypatch, over, exec_kw):
+    """The apply pass with the MISS table of entropy changes and without it (changes beyond 2^30, log-odds
+    beyond 16 bits); one bitmap word per row (32-cell grids) and several; more rays than threads, many of
+    them ending on one cell (coarse cells)."""
+    monkeypatch.setitem(synth.WORKLOADS, "mixed_12x32", synth.Workload(
+        "mixed_12x32", 12, (32, 64, 96), 0.25, 360, 10.0, 30, 0, rects=(2, 4), rect_side=(3, 8), thin_walls=(0, 0),
+        thin_len=(0, 0), scale_counts=False))
+    pr = Pair("mixed_12x32", 3, exec_kw=exec_kw, steps=30, params_over=over)
+    for t in range(30):
+        o = pr.step()
+        if t % 3 == 0 or t == 29:
+            pr.compare(o)
