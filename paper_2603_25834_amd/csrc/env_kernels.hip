@@ -26,6 +26,29 @@ namespace aslam {
 
 namespace {
 
+// The arguments of the per-robot kernels, as they lie in the kernel's argument segment.  A phase of a
+// step takes them through fresh(), which hides from the compiler that they are the same ones as before:
+// it then loads what a phase uses at that phase.  Seen as one set, all of them were loaded at the top of
+// the fused kernel and kept over every phase, 150 spilled scalars that came back through 1127
+// v_readlane (of 4877 vector instructions); 19 of them are left.
+struct StepKernelArgs {
+  EnvParams P;
+  StepArgs A;
+  LdsPlan L;
+};
+
+typedef const StepKernelArgs __attribute__((address_space(4)))* KernArgPtr;
+
+__device__ __forceinline__ const StepKernelArgs& step_kernel_args() {
+  return *(const StepKernelArgs*)(KernArgPtr)__builtin_amdgcn_kernarg_segment_ptr();
+}
+
+__device__ __forceinline__ const StepKernelArgs& fresh(const StepKernelArgs& K) {
+  KernArgPtr p = (KernArgPtr)&K;
+  asm volatile("" : "+s"(p));
+  return *(const StepKernelArgs*)p;
+}
+
 __device__ __forceinline__ int32_t heading_index(float th, float k_ang) {
   float t = th * k_ang;
   if (!(t > -1.0e9f && t < 1.0e9f)) t = 0.0f;
@@ -1041,9 +1064,12 @@ __device__ void mark_segments(const EnvParams& P, const int32_t* rho_lds, int32_
 // Map update from the estimated pose with the measured ranges, then the
 // reward.  rho_lds[k]: range (Q16) with bit 31 set when ray k hit.
 template <int NT, bool SEG>
-__device__ void update_and_reward(const EnvParams& P, const StepArgs& A, const RobotMeta& m, const LdsView& V,
-                                  const LdsPlan& L, int32_t r) {
+__device__ __forceinline__ void update_and_reward(const StepKernelArgs& K0, const RobotMeta& m, const LdsView& V,
+                                                  int32_t r) {
   constexpr int NWAVE = NT / 64;
+  const StepKernelArgs& K1 = fresh(K0);
+  const EnvParams& P = K1.P;
+  const LdsPlan& L = K1.L;
   RobotShared* sh = V.sh;
   const int32_t* rho_lds = V.rho;
   uint32_t* uni = V.uni;
@@ -1096,9 +1122,10 @@ __device__ void update_and_reward(const EnvParams& P, const StepArgs& A, const R
         apply_hit(P, h, dh, ncoded);
       }
       __syncthreads();
-      apply_band<NT>(P, miss, rows, nw, nw_magic, base_cell, s, V.lut, list, dh, ncoded);
+      const EnvParams& PA = fresh(K0).P;
+      apply_band<NT>(PA, miss, rows, nw, nw_magic, base_cell, s, V.lut, list, dh, ncoded);
       __syncthreads();
-      apply_hit(P, h0, dh, ncoded);
+      apply_hit(PA, h0, dh, ncoded);
     }
   }
   dh = wave_sum_i64(dh);
@@ -1111,6 +1138,9 @@ __device__ void update_and_reward(const EnvParams& P, const StepArgs& A, const R
   }
   __syncthreads();
   if (threadIdx.x == 0) {
+    const StepKernelArgs& K2 = fresh(K0);
+    const EnvParams& P = K2.P;
+    const StepArgs& A = K2.A;
     long long tot = 0;
     int64_t dsum = 0;
     for (int w = 0; w < NWAVE; ++w) {
@@ -1204,8 +1234,11 @@ __device__ __forceinline__ void init_bbox(RobotShared* sh) {
 
 // SEG: the map update's walk in segments (its own instance: the two forms differ in register use).
 template <int NT, bool SEG>
-__global__ __launch_bounds__(NT) void k_update(EnvParams P, StepArgs A, LdsPlan L) {
+__global__ __launch_bounds__(NT) void k_update(EnvParams, StepArgs, LdsPlan) {
   extern __shared__ __align__(16) unsigned char smem[];
+  const StepKernelArgs& K0 = step_kernel_args();
+  const EnvParams& P = K0.P;
+  const LdsPlan& L = K0.L;
   const LdsView V = lds_view(smem, L);
   RobotShared* sh = V.sh;
   const int32_t r = blockIdx.x;
@@ -1230,16 +1263,18 @@ __global__ __launch_bounds__(NT) void k_update(EnvParams P, StepArgs A, LdsPlan 
   __syncthreads();
   endpoint_bbox<NT>(P, V.rho, sh->eox, sh->eoy, sh->ib_e, sh);
   __syncthreads();
-  update_and_reward<NT, SEG>(P, A, m, V, L, r);
+  update_and_reward<NT, SEG>(K0, m, V, r);
 }
 
 // One robot of the fused step (motion, march, update, reward) by the whole workgroup.
 template <int NT, bool SEG>
-__device__ __forceinline__ void fused_robot(const EnvParams& P, const StepArgs& A, const LdsPlan& L,
-                                            const LdsView& V, int32_t r) {
+__device__ __forceinline__ void fused_robot(const StepKernelArgs& K0, const LdsView& V, int32_t r) {
   RobotShared* sh = V.sh;
-  const RobotMeta m = P.meta[r];
+  const RobotMeta m = K0.P.meta[r];
   if (threadIdx.x < 64) {   // wave 0: lanes 0..4 draw the normals, lane 0 moves the robot
+    const StepKernelArgs& K = fresh(K0);
+    const EnvParams& P = K.P;
+    const StepArgs& A = K.A;
     const MotionDraws g = motion_draws(P, A, r, true, 0);
     if (threadIdx.x == 0) {
       const MotionOut o = robot_motion(P, A, r, g);
@@ -1254,6 +1289,10 @@ __device__ __forceinline__ void fused_robot(const EnvParams& P, const StepArgs& 
     }
   }
   __syncthreads();
+  const StepKernelArgs& K = fresh(K0);
+  const EnvParams& P = K.P;
+  const StepArgs& A = K.A;
+  const LdsPlan& L = K.L;
   // the paper's proximity collision (the move stands), one cell per thread
   const bool prox = P.crash_q > 0 && !sh->collided;
   if (prox) near_obstacle_wg<NT>(P.world + m.world_off, m.side, sh->tox, sh->toy, P.crash_q, &sh->near);
@@ -1266,9 +1305,9 @@ __device__ __forceinline__ void fused_robot(const EnvParams& P, const StepArgs& 
     P.flags[2 * (int64_t)r] = 1;
   }
   march_rays<NT>(P, m, V, sw, wy0, A.ranges, step_noise(P, A, r), L.record != 0, r);
-  endpoint_bbox<NT>(P, V.rho, sh->eox, sh->eoy, sh->ib_e, sh);
+  endpoint_bbox<NT>(fresh(K0).P, V.rho, sh->eox, sh->eoy, sh->ib_e, sh);
   __syncthreads();
-  update_and_reward<NT, SEG>(P, A, m, V, L, r);
+  update_and_reward<NT, SEG>(K0, m, V, r);
 }
 
 // The fused step's order of robots, the most work first (largest-processing-time order): a counting
@@ -1320,23 +1359,25 @@ __global__ __launch_bounds__(kOrderThreads) void k_order(int32_t n, const int32_
 // 750-robot batch resident at once); unbounded it takes 89 and fits two, which costs more than the
 // few spilled values do.
 template <int NT, bool SEG>
-__global__ __launch_bounds__(NT, SEG ? 6 : 1) void k_fused(EnvParams P, StepArgs A, LdsPlan L) {
+__global__ __launch_bounds__(NT, SEG ? 6 : 1) void k_fused(EnvParams, StepArgs, LdsPlan) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const LdsView V = lds_view(smem, L);
-  for (int32_t i = threadIdx.x; i < 2 * P.lclamp + 2; i += NT) V.lut[i] = P.miss_tab[i];
-  fused_robot<NT, SEG>(P, A, L, V, P.order[blockIdx.x]);
+  const StepKernelArgs& K0 = step_kernel_args();
+  const LdsView V = lds_view(smem, K0.L);
+  for (int32_t i = threadIdx.x; i < 2 * K0.P.lclamp + 2; i += NT) V.lut[i] = K0.P.miss_tab[i];
+  fused_robot<NT, SEG>(K0, V, K0.P.order[blockIdx.x]);
 }
 
 // Fused persistent step on a smaller grid: workgroups pull robots in largest-grid-first
 // order.  The register budget is capped at four waves per SIMD (128 VGPRs); the
 // loop-carried state would otherwise double it.
 template <int NT, bool SEG>
-__global__ __launch_bounds__(NT, 4) void k_fused_persist(EnvParams P, StepArgs A, LdsPlan L) {
+__global__ __launch_bounds__(NT, 4) void k_fused_persist(EnvParams, StepArgs, LdsPlan) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const LdsView V = lds_view(smem, L);
-  for (int32_t i = threadIdx.x; i < 2 * P.lclamp + 2; i += NT) V.lut[i] = P.miss_tab[i];
-  for (int32_t w = blockIdx.x; w < P.n; w += gridDim.x) {
-    fused_robot<NT, SEG>(P, A, L, V, P.order[w]);
+  const StepKernelArgs& K0 = step_kernel_args();
+  const LdsView V = lds_view(smem, K0.L);
+  for (int32_t i = threadIdx.x; i < 2 * K0.P.lclamp + 2; i += NT) V.lut[i] = K0.P.miss_tab[i];
+  for (int32_t w = blockIdx.x; w < K0.P.n; w += gridDim.x) {
+    fused_robot<NT, SEG>(K0, V, fresh(K0).P.order[w]);
     __syncthreads();
   }
 }
