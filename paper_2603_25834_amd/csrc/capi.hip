@@ -210,7 +210,7 @@ int validate_config(const aslam_env_config* c) {
   return ASL_OK;
 }
 
-// LDS plan: lut | rho | perm | seg | shared | union(world rows, code bitmaps of one band).
+// LDS plan: lut | rho | perm | seg | hist | shared | world rows and one band's code bitmap.
 int plan_lds(aslam_env* e, const aslam_exec_config& ex, LdsPlan& L) {
   const int32_t lc = e->P.lclamp;
   const int32_t rhat_cells = e->P.rhat_cells;
@@ -243,8 +243,18 @@ int plan_lds(aslam_env* e, const aslam_exec_config& ex, LdsPlan& L) {
   if (band < 8 || 64 * nw_max + 16 > free_bytes)
     return fail(ASL_EINVAL, "band_rows does not fit the LDS budget (need >= 8 rows)");
   L.band_rows = (int32_t)band;
-  L.list_off = (int32_t)align_up(4 * band * nw_max, 16);
-  L.union_bytes = (int32_t)std::max<int64_t>(world_max, L.list_off + list_bytes);
+  // The octet lists lie over perm and seg where those are free by then (the segmented walk) and large
+  // enough, else after the bitmap.  The bitmap takes the world rows' place, or its own where three
+  // workgroups still share a CU (their most: 80 registers a lane): cleared before the march then, a phase
+  // less between the march and the walk.
+  const int64_t bits = align_up(4 * band * nw_max, 16), world = align_up(world_max, 16);
+  const bool over = ex.mark_seg > 0 && L.off_hist - L.off_perm >= list_bytes;
+  const int64_t tail = bits + (over ? 0 : list_bytes);
+  L.cleared = L.off_union + world + tail <= std::min<int64_t>(budget, e->lds_max / 3 / 1280 * 1280) ? 1 : 0;
+  L.off_bits = L.off_union + (L.cleared ? (int32_t)world : 0);
+  L.off_list = over ? L.off_perm : L.off_bits + (int32_t)bits;
+  L.clear_vecs = (int32_t)(bits / 16);
+  L.union_bytes = (int32_t)(L.cleared ? world + tail : std::max<int64_t>(world_max, tail));
   L.total = L.off_union + L.union_bytes;
   L.record = ex.record_rays;
   L.mark_seg = ex.mark_seg;

@@ -134,7 +134,10 @@ struct LdsPlan {
   int32_t total;
   int32_t union_bytes;
   int32_t band_rows;      // code-window rows per pass
-  int32_t list_off;       // the waves' octet lists of the apply pass, bytes into the union
+  int32_t off_bits;       // code bitmap
+  int32_t off_list;       // the waves' octet lists of the apply pass
+  int32_t cleared;        // 1: the bitmap has its own space and is cleared (clear_vecs 16-byte vectors) before the march
+  int32_t clear_vecs;
   int32_t world_halo;     // rows staged around the robot: rhat_cells + 3
   int32_t record;         // fused: write rho / hitc to the state
   int32_t mark_seg;       // map update's walk: 0 one lane per ray, else segments of this many steps

@@ -238,7 +238,15 @@ __device__ __forceinline__ MotionDraws motion_draws(const EnvParams& P, const St
 __device__ MotionOut robot_motion(const EnvParams& P, const StepArgs& A, int32_t r, const MotionDraws& g) {
   const RobotMeta m = P.meta[r];
   const int32_t s = m.side;
+  // the robot's state, read up front: one memory round trip, not one behind each store
   const float a0 = A.actions[2 * r], a1 = A.actions[2 * r + 1];
+  float* e = P.est + 3 * (int64_t)r;
+  float* c = P.cov + 6 * (int64_t)r;
+  float ex = e[0], ey = e[1], eth = e[2];
+  float c0 = c[0], c1 = c[1], c2 = c[2], c3 = c[3], c4 = c[4], c5 = c[5];
+  const int32_t t = P.step[r];
+  const int32_t last_lc = P.loop_closure ? P.last_lc[r] : 0;
+  const int32_t prev_vcell = P.reward_mode == 1 ? P.prev_vcell[r] : 0;
   float v = fminf(fmaxf(a0, 0.0f), P.v_max);
   float w = fminf(fmaxf(a1, -P.w_max), P.w_max);
   if (v != v) v = 0.0f;
@@ -249,6 +257,7 @@ __device__ MotionOut robot_motion(const EnvParams& P, const StepArgs& A, int32_t
   float* p = P.pose + 3 * (int64_t)r;
   float px = p[0], py = p[1], pth = p[2];
   const int32_t dt_ = P.dirtab[heading_index(pth, P.k_ang)];
+  const int32_t de = P.dirtab[heading_index(eth, P.k_ang)];   // for the EKF
   const float nx = (px + d * dir_cos(dt_)) + P.sigma_x * g(0);
   const float ny = (py + d * dir_sin(dt_)) + P.sigma_y * g(1);
   const float nth = wrap_pi((pth + phi) + P.sigma_th * g(2));
@@ -269,12 +278,7 @@ __device__ MotionOut robot_motion(const EnvParams& P, const StepArgs& A, int32_t
   const int32_t collided = col;
 
   // EKF predict; F uses the estimated heading before the step.
-  float* e = P.est + 3 * (int64_t)r;
-  float* c = P.cov + 6 * (int64_t)r;
-  float ex = e[0], ey = e[1], eth = e[2];
-  float c0 = c[0], c1 = c[1], c2 = c[2], c3 = c[3], c4 = c[4], c5 = c[5];
   {
-    const int32_t de = P.dirtab[heading_index(eth, P.k_ang)];
     const float ch = dir_cos(de), sh = dir_sin(de);
     const float fa = -(d * sh);
     const float fb = d * ch;
@@ -290,7 +294,6 @@ __device__ MotionOut robot_motion(const EnvParams& P, const StepArgs& A, int32_t
     eth = wrap_pi(eth + phi);
   }
 
-  const int32_t t = P.step[r];
   // visit cell of the true position (loop closure, exploration novelty)
   int32_t vcell = -1;
   int64_t vk = 0;
@@ -307,7 +310,7 @@ __device__ MotionOut robot_motion(const EnvParams& P, const StepArgs& A, int32_t
   // fraction since the last visit on re-entering one, 0 while staying
   if (P.reward_mode == 1) {
     double dcells = 0.0;
-    if (vcell != P.prev_vcell[r]) {
+    if (vcell != prev_vcell) {
       const int32_t last = P.visit_last[vk];
       dcells = last < 0 ? 1.0 : fmin(1.0, 0.5 * (double)(t - last) / (double)P.tep);
     }
@@ -325,7 +328,7 @@ __device__ MotionOut robot_motion(const EnvParams& P, const StepArgs& A, int32_t
     } else {
       const float dx = px - P.visit_xy[2 * vk];
       const float dy = py - P.visit_xy[2 * vk + 1];
-      if (t - t0 >= P.lc_gap && t - P.last_lc[r] >= P.lc_gap && (dx * dx + dy * dy) <= P.lc_r2) {
+      if (t - t0 >= P.lc_gap && t - last_lc >= P.lc_gap && (dx * dx + dy * dy) <= P.lc_r2) {
         const float zx = px + P.lc_sigma * g(3);
         const float zy = py + P.lc_sigma * g(4);
         const float s00 = c0 + P.lc_var, s01 = c1, s11 = c3 + P.lc_var;
@@ -378,9 +381,12 @@ struct RobotShared {
   int32_t bx0, bx1, by0, by1;   // cell bounding box of the ray end points (estimated pose)
   int32_t dmin_bits;            // FP32 bits of the smallest reported range (non-negative)
   int32_t near;                 // proximity collision found by the workgroup
-  long long part[16];
-  int32_t dpart[16];
+  long long part[8];            // a wave's entropy change and coded cells
+  int32_t dpart[8];
+  // formed beside the march (reward_inputs): ln det Sigma, U_t, and for Eq. (7) U_{t-1} and the novelty
+  double ld, u, u_prev, dcells;
 };
+static_assert(sizeof(RobotShared) <= 256, "the plan's share");
 
 // Pointers into the dynamic LDS of a per-robot kernel.
 struct LdsView {
@@ -390,7 +396,9 @@ struct LdsView {
   int32_t* seg;      // [R] first walk segment of each ray (mark)
   int32_t* hist;     // [64] sort buckets
   RobotShared* sh;
-  uint32_t* uni;     // world rows, then the code bitmap and the waves' octet lists
+  uint32_t* uni;     // world rows
+  uint32_t* bits;    // code bitmap (over the world rows, or beside them: LdsPlan::cleared)
+  uint16_t* list;    // the waves' octet lists
 };
 
 __device__ __forceinline__ LdsView lds_view(unsigned char* smem, const LdsPlan& L) {
@@ -402,6 +410,8 @@ __device__ __forceinline__ LdsView lds_view(unsigned char* smem, const LdsPlan& 
   v.hist = reinterpret_cast<int32_t*>(smem + L.off_hist);
   v.sh = reinterpret_cast<RobotShared*>(smem + L.off_misc);
   v.uni = reinterpret_cast<uint32_t*>(smem + L.off_union);
+  v.bits = reinterpret_cast<uint32_t*>(smem + L.off_bits);
+  v.list = reinterpret_cast<uint16_t*>(smem + L.off_list);
   return v;
 }
 
@@ -568,29 +578,51 @@ __device__ void sort_rays(int32_t R, int32_t* perm, int32_t* hist, KeyFn key_of)
   __syncthreads();
 }
 
+// The same sort by the calling wave alone, for the march of the fused step: it runs beside the motion of
+// wave 0, so no other wave waits for it (2.0 us of the step when the whole workgroup did it).
+template <typename KeyFn>
+__device__ __forceinline__ void sort_rays_wave(int32_t R, int32_t* perm, int32_t* hist, KeyFn key_of) {
+  const int32_t lane = threadIdx.x & 63;
+  hist[lane] = 0;
+  __builtin_amdgcn_wave_barrier();
+  for (int32_t k = lane; k < R; k += 64) atomicAdd(&hist[63 - min(max(key_of(k), 0), 63)], 1);
+  __builtin_amdgcn_wave_barrier();
+  const int32_t v = hist[lane];
+  int32_t x = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int32_t y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
+  }
+  hist[lane] = x - v;
+  __builtin_amdgcn_wave_barrier();
+  for (int32_t k = lane; k < R; k += 64) perm[atomicAdd(&hist[63 - min(max(key_of(k), 0), 63)], 1)] = k;
+}
+
 // Cell bounding box of the end points of all rays walked from the Q16 origin
 // (eox, eoy) with the ranges in rho (Q16).  Every cell a walk visits lies
 // within one cell of its segment, so the box grown by 2 cells holds them all.
-template <int NT>
-__device__ void endpoint_bbox(const EnvParams& P, const int32_t* rho, int32_t eox, int32_t eoy, int32_t ib,
-                              RobotShared* sh) {
-  int32_t mnx = eox >> 16, mxx = mnx, mny = eoy >> 16, mxy = mny;
-  for (int32_t k = threadIdx.x; k < P.R; k += NT) {
-    const int32_t lim = rho[k] & 0x7fffffff;
-    const int32_t dv = ray_dir(P, ib, k);
+struct EndBox {
+  int32_t mnx, mxx, mny, mxy;
+  __device__ __forceinline__ EndBox(int32_t eox, int32_t eoy)
+      : mnx(eox >> 16), mxx(eox >> 16), mny(eoy >> 16), mxy(eoy >> 16) {}
+  // the end of a ray with table direction dv and range lim
+  __device__ __forceinline__ void add(int32_t eox, int32_t eoy, int32_t dv, int32_t lim) {
     const int32_t a = (int16_t)(dv & 0xffff), b = dv >> 16;
     const int32_t qx = (int32_t)(((int64_t)eox + (((int64_t)lim * a) >> 14)) >> 16);
     const int32_t qy = (int32_t)(((int64_t)eoy + (((int64_t)lim * b) >> 14)) >> 16);
     mnx = min(mnx, qx); mxx = max(mxx, qx);
     mny = min(mny, qy); mxy = max(mxy, qy);
   }
-  mnx = wave_min_i32(mnx); mxx = wave_max_i32(mxx);
-  mny = wave_min_i32(mny); mxy = wave_max_i32(mxy);
-  if ((threadIdx.x & 63) == 0) {
-    atomicMin(&sh->bx0, mnx); atomicMax(&sh->bx1, mxx);
-    atomicMin(&sh->by0, mny); atomicMax(&sh->by1, mxy);
+  __device__ __forceinline__ void store(RobotShared* sh) {
+    mnx = wave_min_i32(mnx); mxx = wave_max_i32(mxx);
+    mny = wave_min_i32(mny); mxy = wave_max_i32(mxy);
+    if ((threadIdx.x & 63) == 0) {
+      atomicMin(&sh->bx0, mnx); atomicMax(&sh->bx1, mxx);
+      atomicMin(&sh->by0, mny); atomicMax(&sh->by1, mxy);
+    }
   }
-}
+};
 
 // ---------------------------------------------------------------- stages
 template <int NT>
@@ -625,8 +657,9 @@ constexpr int kLook = kMarchLook;
 // LiDAR march of every ray of the robot from the true pose (lanes = rays),
 // then the reported range of each ray (sensor model of Sec. IV-A: true range
 // plus noise, rounded to the quantum, clamped to [r_min, r_max]).  The map
-// update walks the reported range; ray k takes draw 5 + k of gr.
-template <int NT>
+// update walks the reported range; ray k takes draw 5 + k of gr.  The lane slots (V.perm) are ordered by
+// the previous step's walk length of each ray.  BOX: also the box of the update's end points.
+template <int NT, bool BOX>
 __device__ void march_rays(const EnvParams& P, const RobotMeta& m, const LdsView& V, const uint32_t* sw,
                            int32_t wy0, float* ranges_out, const StepNoise& gr, bool record, int32_t r) {
   RobotShared* sh = V.sh;
@@ -636,8 +669,8 @@ __device__ void march_rays(const EnvParams& P, const RobotMeta& m, const LdsView
   const int32_t cx0 = tox >> 16, cy0 = toy >> 16;
   const bool inside = cx0 >= 0 && cx0 < s && cy0 >= 0 && cy0 < s;
   int16_t* raylen = P.raylen + (int64_t)r * P.R;
-  // lane slots ordered by the previous step's walk length of each ray
-  sort_rays<NT>(P.R, V.perm, V.hist, [&](int32_t k) { return (int32_t)raylen[k] >> 2; });
+  const int32_t eox = BOX ? sh->eox : 0, eoy = BOX ? sh->eoy : 0, ib_e = BOX ? sh->ib_e : 0;
+  EndBox box(eox, eoy);
   int32_t visits = 0;
   float dmin = __int_as_float(0x7f800000);
   for (int32_t k0 = 0; k0 < P.R; k0 += NT) {
@@ -649,6 +682,7 @@ __device__ void march_rays(const EnvParams& P, const RobotMeta& m, const LdsView
     RaySetup q{};
     int32_t li = 0, D = 0, i = 0, sx = 0, sy = 0;
     bool hit = false, done = true;
+    const int32_t dv_e = BOX && k < P.R ? ray_dir(P, ib_e, k) : 0;
     if (active) {
       const int32_t dv = ray_dir(P, ib, k);
       const int32_t a = (int16_t)(dv & 0xffff), b = dv >> 16;
@@ -715,6 +749,7 @@ __device__ void march_rays(const EnvParams& P, const RobotMeta& m, const LdsView
         rho_u = to_q16(rep, P.inv_c16);
       }
       dmin = fminf(dmin, rep);
+      if (BOX) box.add(eox, eoy, dv_e, rho_u);
       rho_lds[k] = rho_u | (cell >= 0 ? (int32_t)0x80000000 : 0);
       ranges_out[(int64_t)r * P.R + k] = rep;
       if (record) {
@@ -723,6 +758,7 @@ __device__ void march_rays(const EnvParams& P, const RobotMeta& m, const LdsView
       }
     }
   }
+  if (BOX) box.store(sh);
   visits = wave_sum_i32(visits);
   if ((threadIdx.x & 63) == 0 && visits) atomicAdd(&sh->cnt_march, visits);
   if (P.reward_mode == 1) {
@@ -1061,6 +1097,24 @@ __device__ void mark_segments(const EnvParams& P, const int32_t* rho_lds, int32_
   }
 }
 
+template <int NT>
+__device__ __forceinline__ void clear_bits(uint32_t* bits, int32_t vecs) {
+  uint4* u4 = reinterpret_cast<uint4*>(bits);
+  for (int32_t k = threadIdx.x; k < vecs; k += NT) u4[k] = make_uint4(0u, 0u, 0u, 0u);
+}
+
+// What the reward needs besides the map update's sums, by one thread while the others march: the
+// logarithm and cube root of the covariance's determinant are long FP64 chains.
+__device__ __forceinline__ void reward_inputs(const EnvParams& P, int32_t r, RobotShared* sh) {
+  const double det = cov_det(P.cov + 6 * (int64_t)r);
+  sh->ld = det > 0.0 ? log(det) : log(1.17549435e-38);
+  if (P.reward_mode == 1) {
+    sh->u = det > 0.0 ? cbrt(det) : 0.0;
+    sh->u_prev = P.u_prev[r];
+    sh->dcells = P.dcells[r];
+  }
+}
+
 // Map update from the estimated pose with the measured ranges, then the
 // reward.  rho_lds[k]: range (Q16) with bit 31 set when ray k hit.
 template <int NT, bool SEG>
@@ -1072,7 +1126,6 @@ __device__ __forceinline__ void update_and_reward(const StepKernelArgs& K0, cons
   const LdsPlan& L = K1.L;
   RobotShared* sh = V.sh;
   const int32_t* rho_lds = V.rho;
-  uint32_t* uni = V.uni;
   const int32_t s = m.side;
   const int32_t eox = sh->eox, eoy = sh->eoy, ib = sh->ib_e;
   const int32_t ecx = eox >> 16, ecy = eoy >> 16;
@@ -1087,8 +1140,8 @@ __device__ __forceinline__ void update_and_reward(const StepKernelArgs& K0, cons
     const int32_t nw = (x1 >> 5) - (x0 >> 5) + 1;
     const int32_t rowbits = nw << 5;
     const int32_t band = L.band_rows;
-    uint32_t* miss = uni;
-    uint16_t* list = reinterpret_cast<uint16_t*>(reinterpret_cast<unsigned char*>(uni) + L.list_off);
+    uint32_t* miss = V.bits;
+    uint16_t* list = V.list;
     const uint32_t nw_magic = 0xffffffffu / (uint32_t)nw + 1u;
     const int64_t base = m.cell_off;
     if (!SEG) sort_mark_rays<NT>(P, rho_lds, V.perm, V.hist, ib);
@@ -1096,12 +1149,10 @@ __device__ __forceinline__ void update_and_reward(const StepKernelArgs& K0, cons
       const int32_t rows = min(band, y1 - by0 + 1);
       const uint32_t band_bits = (uint32_t)(rows * rowbits);
       const bool one_band = y1 - y0 + 1 <= band;
-      {
-        uint4* u4 = reinterpret_cast<uint4*>(uni);
-        const int32_t nclr = (rows * nw + 3) >> 2;
-        for (int32_t k = threadIdx.x; k < nclr; k += NT) u4[k] = make_uint4(0u, 0u, 0u, 0u);
+      if (!(L.cleared && by0 == y0)) {
+        clear_bits<NT>(miss, (rows * nw + 3) >> 2);
+        __syncthreads();
       }
-      __syncthreads();
       int32_t we0;
       if (SEG)
         mark_segments<NT>(P, rho_lds, V.perm, V.seg, V.hist, s, eox, eoy, ib, by0, x0w, rowbits, band_bits, one_band,
@@ -1147,22 +1198,20 @@ __device__ __forceinline__ void update_and_reward(const StepKernelArgs& K0, cons
       tot += sh->part[w];
       dsum += sh->dpart[w];
     }
-    int64_t* cnt = P.counters + 3 * (int64_t)r;
-    cnt[0] += dsum;
-    cnt[1] += sh->cnt_march;
-    cnt[2] += sh->cnt_upd;
+    // one writer per entry: atomics only so that nothing waits for the old values
+    unsigned long long* cnt = reinterpret_cast<unsigned long long*>(P.counters + 3 * (int64_t)r);
+    atomicAdd(cnt, (unsigned long long)dsum);
+    atomicAdd(cnt + 1, (unsigned long long)sh->cnt_march);
+    atomicAdd(cnt + 2, (unsigned long long)sh->cnt_upd);
     P.cost[r] = sh->cnt_march + sh->cnt_upd;
-    P.hq_total[r] += tot;
+    atomicAdd(reinterpret_cast<unsigned long long*>(P.hq_total + r), (unsigned long long)tot);
     const double rH = (double)(-tot) * (1.0 / 4294967296.0);
-    const float* c = P.cov + 6 * (int64_t)r;
-    const double det = cov_det(c);
-    const double ld = det > 0.0 ? log(det) : log(1.17549435e-38);
+    const double ld = sh->ld;
     const int32_t col = sh->collided;
     double rew;
     if (P.reward_mode == 1) {
-      const double u = det > 0.0 ? cbrt(det) : 0.0;
-      rew = paper_reward(P, col, P.dcells[r], P.u_prev[r], u, (double)__int_as_float(sh->dmin_bits));
-      P.u_prev[r] = u;
+      rew = paper_reward(P, col, sh->dcells, sh->u_prev, sh->u, (double)__int_as_float(sh->dmin_bits));
+      P.u_prev[r] = sh->u;
     } else {
       rew = (double)P.w_entropy * rH - (double)P.w_dopt * ld - (double)P.lambda_col * (double)col;
     }
@@ -1171,7 +1220,7 @@ __device__ __forceinline__ void update_and_reward(const StepKernelArgs& K0, cons
     A.done[r] = (uint8_t)(col || (P.episode_len > 0 && t >= P.episode_len));
     P.terms[2 * (int64_t)r] = (float)rH;
     P.terms[2 * (int64_t)r + 1] = (float)ld;
-    P.draws[r] += 1;   // every step, with or without the caller's draws
+    atomicAdd(reinterpret_cast<unsigned long long*>(P.draws + r), 1ull);   // every step, with or without the caller's draws
   }
 }
 
@@ -1219,8 +1268,9 @@ __global__ __launch_bounds__(NT) void k_march(EnvParams P, StepArgs A, LdsPlan L
   int32_t wy0;
   uint32_t* sw = V.uni + march_guard_words(m.side);
   stage_world<NT>(P, m, sh->toy >> 16, L.world_halo, sw, wy0);
-  __syncthreads();
-  march_rays<NT>(P, m, V, sw, wy0, A.ranges, step_noise(P, A, r), true, r);
+  const int16_t* raylen = P.raylen + (int64_t)r * P.R;
+  sort_rays<NT>(P.R, V.perm, V.hist, [&](int32_t k) { return (int32_t)raylen[k] >> 2; });   // ends at a barrier
+  march_rays<NT, false>(P, m, V, sw, wy0, A.ranges, step_noise(P, A, r), true, r);
   if (threadIdx.x == 0) {
     P.counters[3 * (int64_t)r + 1] += sh->cnt_march;
     P.dmin_bits[r] = sh->dmin_bits;
@@ -1260,10 +1310,24 @@ __global__ __launch_bounds__(NT) void k_update(EnvParams, StepArgs, LdsPlan) {
     const int32_t hc = P.hitc[(int64_t)r * P.R + k];
     V.rho[k] = rq | (hc >= 0 ? (int32_t)0x80000000 : 0);
   }
+  if (L.cleared) clear_bits<NT>(V.bits, L.clear_vecs);
   __syncthreads();
-  endpoint_bbox<NT>(P, V.rho, sh->eox, sh->eoy, sh->ib_e, sh);
+  {
+    EndBox box(sh->eox, sh->eoy);
+    for (int32_t k = threadIdx.x; k < P.R; k += NT)
+      box.add(sh->eox, sh->eoy, ray_dir(P, sh->ib_e, k), V.rho[k] & 0x7fffffff);
+    box.store(sh);
+  }
+  if (threadIdx.x == NT - 64) reward_inputs(P, r, sh);
   __syncthreads();
   update_and_reward<NT, SEG>(K0, m, V, r);
+}
+
+// The apply pass's table into LDS, by the waves that do not move the robot.
+template <int NT>
+__device__ __forceinline__ void stage_table(const EnvParams& P, uint32_t* lut) {
+  if (threadIdx.x < 64) return;
+  for (int32_t i = (int32_t)threadIdx.x - 64; i < 2 * P.lclamp + 2; i += NT - 64) lut[i] = P.miss_tab[i];
 }
 
 // One robot of the fused step (motion, march, update, reward) by the whole workgroup.
@@ -1271,7 +1335,13 @@ template <int NT, bool SEG>
 __device__ __forceinline__ void fused_robot(const StepKernelArgs& K0, const LdsView& V, int32_t r) {
   RobotShared* sh = V.sh;
   const RobotMeta m = K0.P.meta[r];
-  if (threadIdx.x < 64) {   // wave 0: lanes 0..4 draw the normals, lane 0 moves the robot
+  const int32_t wave = (int32_t)threadIdx.x >> 6;
+  if (wave == 1) {   // the march's lane slots, the longest of the last step's walks first
+    const EnvParams& P = fresh(K0).P;
+    const int16_t* raylen = P.raylen + (int64_t)r * P.R;
+    sort_rays_wave(P.R, V.perm, V.hist, [&](int32_t k) { return (int32_t)raylen[k] >> 2; });
+  }
+  if (wave == 0) {   // lanes 0..4 draw the normals, lane 0 moves the robot
     const StepKernelArgs& K = fresh(K0);
     const EnvParams& P = K.P;
     const StepArgs& A = K.A;
@@ -1299,14 +1369,14 @@ __device__ __forceinline__ void fused_robot(const StepKernelArgs& K0, const LdsV
   int32_t wy0;
   uint32_t* sw = V.uni + march_guard_words(m.side);
   stage_world<NT>(P, m, sh->toy >> 16, L.world_halo, sw, wy0);
+  if (L.cleared) clear_bits<NT>(V.bits, L.clear_vecs);
   __syncthreads();
   if (prox && threadIdx.x == 0 && sh->near) {
     sh->collided = 1;
     P.flags[2 * (int64_t)r] = 1;
   }
-  march_rays<NT>(P, m, V, sw, wy0, A.ranges, step_noise(P, A, r), L.record != 0, r);
-  endpoint_bbox<NT>(fresh(K0).P, V.rho, sh->eox, sh->eoy, sh->ib_e, sh);
-  __syncthreads();
+  if (threadIdx.x == NT - 64) reward_inputs(P, r, sh);   // the last wave: its rays, if any, are the shortest
+  march_rays<NT, true>(P, m, V, sw, wy0, A.ranges, step_noise(P, A, r), L.record != 0, r);
   update_and_reward<NT, SEG>(K0, m, V, r);
 }
 
@@ -1363,7 +1433,7 @@ __global__ __launch_bounds__(NT, SEG ? 6 : 1) void k_fused(EnvParams, StepArgs, 
   extern __shared__ __align__(16) unsigned char smem[];
   const StepKernelArgs& K0 = step_kernel_args();
   const LdsView V = lds_view(smem, K0.L);
-  for (int32_t i = threadIdx.x; i < 2 * K0.P.lclamp + 2; i += NT) V.lut[i] = K0.P.miss_tab[i];
+  stage_table<NT>(K0.P, V.lut);
   fused_robot<NT, SEG>(K0, V, K0.P.order[blockIdx.x]);
 }
 
@@ -1375,7 +1445,7 @@ __global__ __launch_bounds__(NT, 4) void k_fused_persist(EnvParams, StepArgs, Ld
   extern __shared__ __align__(16) unsigned char smem[];
   const StepKernelArgs& K0 = step_kernel_args();
   const LdsView V = lds_view(smem, K0.L);
-  for (int32_t i = threadIdx.x; i < 2 * K0.P.lclamp + 2; i += NT) V.lut[i] = K0.P.miss_tab[i];
+  stage_table<NT>(K0.P, V.lut);
   for (int32_t w = blockIdx.x; w < K0.P.n; w += gridDim.x) {
     fused_robot<NT, SEG>(K0, V, fresh(K0).P.order[w]);
     __syncthreads();
