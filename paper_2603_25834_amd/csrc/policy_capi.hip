@@ -13,6 +13,7 @@
 #include "aslam.h"
 #include "policy_kernels.h"
 #include "conv_fused.h"
+#include "gemm_nt.h"
 #include "gru_kernels.h"
 
 using namespace aslam;
@@ -30,6 +31,9 @@ int pfail(int code, const std::string& m) {
 }
 }  // namespace
 
+// Row length of FC1's operands: whole cache lines of BF16.
+constexpr int32_t fc1_pitch(int32_t k1) { return (k1 + 63) / 64 * 64; }
+
 struct aslam_policy {
   aslam_policy_config cfg{};
   Offsets off{};
@@ -39,7 +43,7 @@ struct aslam_policy {
   float *z2 = nullptr, *part = nullptr, *hpart = nullptr;
   uint16_t *w1b = nullptr, *w1t = nullptr, *w2b = nullptr, *w2t = nullptr;   // BF16 weight copies
   uint4* cfrag = nullptr;   // the encoder's weight fragments (k_conv_frags, k_conv_bwd_frags)
-  int32_t k1p = 0;   // FC1 input width padded to a multiple of 8
+  int32_t k1p = 0;   // FC1 input width padded with zeros (fc1_pitch)
   // split-precision forward (config precision 1): the lo parts of the FC1 input rows, of h1 and of the
   // FC weights (the encoder's lo fragments sit in cfrag from kConvLoFrag on)
   bool prec = false;
@@ -63,6 +67,7 @@ constexpr int kConvFragsAll = kConvLoFrag + kConvFrags;   // forward, backward p
 constexpr int kConvBwdGrid = 256;  // encoder backward: one 8-wave workgroup per CU (LDS-bound)
 constexpr int64_t kFc1Splits = 12, kFc2Splits = 64;
 constexpr int kFc1MinBlocks = 512;   // FC1 forward: resident workgroups (two per CU) that its K splits fill
+constexpr int kFc1WideBlocks = 160;  // workgroups from which FC1 takes the 128 x 256 tiles
 
 int64_t splits_for(int64_t K, int64_t min_chunk, int64_t max_splits) {
   return std::max<int64_t>(1, std::min<int64_t>(max_splits, K / min_chunk));
@@ -198,10 +203,8 @@ int encode_fc1(aslam_policy* P, const float* prm, const int16_t* crop, const flo
     k_conv_fwd<false><<<std::min(B, kConvGrid), 256, 0, st>>>(prm, o, P->cfrag, crop, scan, state, P->cfg.n_scan,
                                                               rows, P->x, nullptr, P->k1p, B);
   PCHK(hipGetLastError());
-  // FC1: [B x k1p] x [k1p x 256] (both operands zero-padded from k1 to k1p)
-  const int K1 = P->k1p;
-  const LdBF16K xa{P->x, K1, B, K1};
-  const LdBF16K wa{P->w1b, K1, kHid, K1};
+  // FC1: [B x k1] x [k1 x 256] (both operands zero-padded from k1 to k1p)
+  const int K1 = (int)((P->off.k1 + 7) / 8 * 8);
   // as many K splits as keep the grid within one round of kFc1MinBlocks resident workgroups; with the
   // three split-precision products and few row tiles (a rollout step) a third of that: the products
   // fill the round themselves, and more slices would only add partial-sum traffic (at 750 rows, 32
@@ -209,22 +212,33 @@ int encode_fc1(aslam_policy* P, const float* prm, const int16_t* crop, const flo
   const int tiles = ((B + 127) / 128) * (kHid / 128);
   int S = std::max(1, std::min(32, kFc1MinBlocks / tiles));
   if (P->prec && tiles < 32) S = std::max(1, std::min(32, kFc1MinBlocks / (3 * tiles)));
+  const int nz = slices_used(K1, S, 64);
+  const int64_t slice = (int64_t)B * kHid;
+  // The wide kernel (128 x 256 tiles, one workgroup per CU) while its tiles and slices come near a round of
+  // the CUs; below that (a rollout step: 84 workgroups at 750 rows, 38 us) the 128 x 128 tiles with each
+  // product in slices of its own are faster (27 us).
+  if (S == 1 || (B + 127) / 128 * nz >= kFc1WideBlocks) {
+    const gemm_nt::Operands fc1{P->x, P->x_lo, P->w1b, P->w1b_lo, P->k1p, P->k1p, B, kHid, P->k1p};
+    const int k_split = ((K1 + S - 1) / S + 63) / 64 * 64;
+    const gemm_nt::EpiPartial part{P->part, kHid, slice};
+    if (P->prec) PCHK(gemm_nt::run<3>(fc1, part, k_split, st));
+    else if (S == 1) PCHK(gemm_nt::run<1>(fc1, gemm_nt::EpiBiasRelu{P->h1, prm + o.f1b, kHid}, k_split, st));
+    else PCHK(gemm_nt::run<1>(fc1, part, k_split, st));
+    *S_used = P->prec ? 3 * nz : S == 1 ? 0 : nz;
+    return ASL_OK;
+  }
+  const LdBF16K xa{P->x, P->k1p, B, K1};
+  const LdBF16K wa{P->w1b, P->k1p, kHid, K1};
   if (P->prec) {
     // x_hi W_hi, x_hi W_lo and x_lo W_hi, each split S ways, into consecutive groups of slices (one
     // launch, the products over z: product 1 reads W's lo part, product 2 x's)
-    const int nz = slices_used(K1, S, 64);
-    const int64_t slice = (int64_t)B * kHid;
-    PCHK((gemm::run<128, 128, 64, 2, 2>(gemm::HiLo<LdBF16K>{xa, LdBF16K{P->x_lo, K1, B, K1}, 4u},
-                                         gemm::HiLo<LdBF16K>{wa, LdBF16K{P->w1b_lo, K1, kHid, K1}, 2u},
+    PCHK((gemm::run<128, 128, 64, 2, 2>(gemm::HiLo<LdBF16K>{xa, LdBF16K{P->x_lo, P->k1p, B, K1}, 4u},
+                                         gemm::HiLo<LdBF16K>{wa, LdBF16K{P->w1b_lo, P->k1p, kHid, K1}, 2u},
                                          EpiPartial{P->part, kHid, slice}, B, kHid, K1, S, st, 3)));
     *S_used = 3 * nz;
-  } else if (S == 1) {
-    PCHK((gemm::run<128, 128, 64, 2, 2>(xa, wa, EpiBiasReluBF16{P->h1, prm + o.f1b, kHid}, B, kHid, K1, 1, st)));
-    *S_used = 0;
   } else {
-    *S_used = slices_used(K1, S, 64);
-    PCHK((gemm::run<128, 128, 64, 2, 2>(xa, wa, EpiPartial{P->part, kHid, (int64_t)B * kHid}, B, kHid, K1, S,
-                                         st)));
+    *S_used = nz;
+    PCHK((gemm::run<128, 128, 64, 2, 2>(xa, wa, EpiPartial{P->part, kHid, slice}, B, kHid, K1, S, st)));
   }
   return ASL_OK;
 }
@@ -316,14 +330,14 @@ int aslam_policy_create(const aslam_policy_config* cfg, aslam_policy** out) {
   p->max_b = cfg->max_batch;
   const int64_t Bm = p->max_b;
   p->part_floats = part_need(p);
-  p->k1p = (p->off.k1 + 7) / 8 * 8;
+  p->k1p = fc1_pitch(p->off.k1);
   struct A { void** ptr; size_t bytes; } al[] = {
-      {(void**)&p->x, 2 * (size_t)Bm * ((p->off.k1 + 7) / 8 * 8)},  {(void**)&p->h1, 2 * (size_t)Bm * kHid},
+      {(void**)&p->x, 2 * (size_t)Bm * p->k1p},  {(void**)&p->h1, 2 * (size_t)Bm * kHid},
       {(void**)&p->dz2, 2 * (size_t)Bm * kHid},  {(void**)&p->dz1, 2 * (size_t)Bm * kHid},
       {(void**)&p->dz2c, 2 * (size_t)Bm * kFeat}, {(void**)&p->z2, 4 * (size_t)Bm * kHid},
       {(void**)&p->part, 4 * (size_t)p->part_floats},
       {(void**)&p->hpart, 4 * (size_t)((Bm + kHeadRows - 1) / kHeadRows) * kHeadPart},
-      {(void**)&p->w1b, 2 * (size_t)kHid * ((p->off.k1 + 7) / 8 * 8)}, {(void**)&p->w1t, 2 * (size_t)kFeat * kHid},
+      {(void**)&p->w1b, 2 * (size_t)kHid * p->k1p}, {(void**)&p->w1t, 2 * (size_t)kFeat * kHid},
       {(void**)&p->w2b, 2 * (size_t)kHid * kHid},                        {(void**)&p->w2t, 2 * (size_t)kHid * kHid},
       {(void**)&p->cfrag, sizeof(uint4) * 64 * kConvFragsAll},
   };
@@ -416,7 +430,7 @@ int aslam_policy_forward(aslam_policy* P, const float* params, const int16_t* cr
 namespace {
 constexpr int64_t kNoAllocMaxScan = 720;
 constexpr int64_t kNoAllocMaxBatch = 256;
-constexpr int64_t kNoAllocK1p = (kFeat + kNoAllocMaxScan + 12 + 7) / 8 * 8;
+constexpr int64_t kNoAllocK1p = fc1_pitch(kFeat + kNoAllocMaxScan + 12);
 constexpr int64_t align256(int64_t v) { return (v + 255) / 256 * 256; }
 constexpr int64_t kNaW1b = 0;
 constexpr int64_t kNaW2b = kNaW1b + align256(2 * kHid * kNoAllocK1p);
@@ -476,7 +490,7 @@ int aslam_policy_forward_noalloc(const float* params, int32_t n_scan, const int1
   P.cfg.max_batch = batch;
   P.off = offsets(n_scan);
   P.max_b = batch;
-  P.k1p = (P.off.k1 + 7) / 8 * 8;
+  P.k1p = fc1_pitch(P.off.k1);
   P.w1b = reinterpret_cast<uint16_t*>(base + kNaW1b);
   P.w2b = reinterpret_cast<uint16_t*>(base + kNaW2b);
   P.cfrag = reinterpret_cast<uint4*>(base + kNaFrag);

@@ -117,22 +117,6 @@ struct LdBF16I {
 // store8(m, n0, v, nvalid): row m, columns n0 .. n0 + nvalid - 1 (n0 multiple of 8).
 // kSliced: the epilogue stores a split-K slice and takes its index (store8z(z, ...)).
 
-struct EpiBiasReluBF16 {
-  uint16_t* out; const float* bias; int64_t ld;
-  static constexpr bool kPrefetch = false, kSliced = false;
-  __device__ void store8(int m, int n0, const float* v, int nvalid) const {
-    uint16_t h[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) h[j] = j < nvalid ? f2bf(fmaxf(v[j] + bias[n0 + j], 0.0f)) : (uint16_t)0;
-    uint16_t* q = out + (int64_t)m * ld + n0;
-    if (nvalid == 8 && ((reinterpret_cast<uintptr_t>(q) & 15) == 0)) {
-      *reinterpret_cast<uint4*>(q) = pack8(h);
-    } else {
-      for (int j = 0; j < nvalid; ++j) q[j] = h[j];
-    }
-  }
-};
-
 struct EpiBiasF32 {
   float* out; const float* bias; int64_t ld;
   static constexpr bool kPrefetch = false, kSliced = false;
