@@ -40,16 +40,7 @@ using gemm::bf16x8;
 using gemm::f32x4;
 
 constexpr int kBlk = 33;                 // crop 2x2 blocks per row and column, plus the zero block -1
-constexpr int kA1Row = 33;               // a1 pixels per row and column, plus the zero pixel -1
 constexpr int kCropLds = kBlk * kBlk * 4;            // BF16 elements
-constexpr int kA1Lds = kA1Row * kA1Row * kC1;        // BF16 elements
-
-// a1 pixel (y, x), x, y in [-1, 31], of the forward kernel's LDS copy: rows of 33
-// pixel slots with even x + 1 in slots 0..16 and odd x + 1 in slots 17..32, so
-// that conv2's stride-2 reads along x hit consecutive slots (different banks).
-__device__ __forceinline__ int a1_slot(int y, int x) {
-  return (y + 1) * kA1Row + ((x + 1) & 1) * 17 + ((x + 1) >> 1);
-}
 
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   return (uint32_t)f2bf(lo) | ((uint32_t)f2bf(hi) << 16);
@@ -180,44 +171,10 @@ __device__ __forceinline__ uint2 pack_relu4(const f32x4& acc, const float b[4]) 
   return make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16));
 }
 
-// conv1 + ReLU of the staged crop into s_a1 (pixel (y, x) at a1_slot(y, x) * 16): 64 tiles of 16 pixels
-// over the NW waves, four at a time so that their operand reads are in flight together; PREC: the
-// crop's and the weights' lo parts enter the product too, and a1's lo part goes to s_a1l.  The wave's
-// tiles' LDS offsets are formed once for all samples: tile j of the wave is wave + NW j, win[j] the
-// element offset of its window operand in the crop (-1: the lanes with lg >= 2, which supply zeros)
-// and slot[j] that of its output in a1.
-template <bool PREC, int NW>
-__device__ __forceinline__ void conv1_lds_at(const uint16_t* s_crop, const uint16_t* s_cropl, uint16_t* s_a1,
-                                             uint16_t* s_a1l, const bf16x8& w1f, const bf16x8& w1fl, const float b1[4],
-                                             const int (&win)[kA1 * kA1 / 16 / NW],
-                                             const int (&slot)[kA1 * kA1 / 16 / NW]) {
-  constexpr int kT = kA1 * kA1 / 16 / NW;
-  auto window = [&](const uint16_t* c, int off) -> uint4 {
-    if (off < 0) return make_uint4(0u, 0u, 0u, 0u);
-    const uint2 a = *reinterpret_cast<const uint2*>(c + off);
-    const uint2 d = *reinterpret_cast<const uint2*>(c + off + 4);
-    return make_uint4(a.x, a.y, d.x, d.y);
-  };
-#pragma unroll
-  for (int j0 = 0; j0 < kT; j0 += 4) {
-    uint4 u[4], ul[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      u[i] = window(s_crop, win[j0 + i]);
-      if (PREC) ul[i] = window(s_cropl, win[j0 + i]);
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      f32x4 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1f, __builtin_bit_cast(bf16x8, u[i]),
-                                                         f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-      if (PREC) {
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1f, __builtin_bit_cast(bf16x8, ul[i]), acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1fl, __builtin_bit_cast(bf16x8, u[i]), acc, 0, 0, 0);
-      }
-      *reinterpret_cast<uint2*>(s_a1 + slot[j0 + i]) = pack_relu4<false>(acc, b1);
-      if (PREC) *reinterpret_cast<uint2*>(s_a1l + slot[j0 + i]) = pack_relu4<true>(acc, b1);
-    }
-  }
+// Bit e: the e-th of four packed ReLU outputs is > 0.
+__device__ __forceinline__ uint32_t positive4(const uint2& h) {
+  return ((h.x & 0x7fffu) ? 1u : 0u) | ((h.x & 0x7fff0000u) ? 2u : 0u) | ((h.y & 0x7fffu) ? 4u : 0u) |
+         ((h.y & 0x7fff0000u) ? 8u : 0u);
 }
 
 // Encoder forward: a2[b * lda2 + co*256 + oy*16 + ox] = bf16(relu(conv2(relu(conv1(crop_b))))), and
@@ -226,34 +183,62 @@ __device__ __forceinline__ void conv1_lds_at(const uint16_t* s_crop, const uint1
 // The workgroup loops over samples; the next sample's crop and the first 512 elements of its
 // scan / state tail are loaded into registers while the current one is processed, so no global read
 // is waited on inside a sample (a longer tail, R > 500, reads its remainder directly).
+// MASK: amask receives conv2's ReLU mask for the backward, bit ox of word [b][co][oy] (bit n % 8 of byte
+// n / 8 of the row's features n).
+// PREC: a2lo receives the lo parts of the same row (conv features and the scan / state tail), the
+// products are split as described at the top, and the workgroup holds the crop and a1 twice.
+//
+// What bounds it: a sample is a chain of two phases with a barrier behind each (conv1 reads the crop and
+// writes a1, conv2 reads a1 while the next crop is stored), so a CU needs workgroups at different places
+// of it.  Without border pixels the LDS of a sample is 40 KB (80 KB with PREC): four (two) workgroups of four
+// waves per CU; the borders' zeros are put into the operands instead.  The tiles' LDS offsets are one
+// base and immediate strides.  With borders (43.6 and 87 KB: three workgroups, one of eight waves) the
+// kernel took 170 us on 9000 split-precision samples and 126 us on 16384 BF16 ones; it takes 152 and 122
+// (109 without the mask).
 constexpr int kConvFwdTailPre = 2;   // tail elements per thread held in registers
 
 // The lo fragments of the split-precision path start at fragment kConvLoFrag (after the backward's).
 constexpr int kConvLoFrag = 20;
 
-// PREC: a2lo receives the lo parts of the same row (conv features and the scan / state tail), the
-// products are split as described at the top, and the workgroup holds the crop and a1 twice (87 KB of
-// LDS: one workgroup per CU, of NT = 512 threads so that eight waves share the CU).
-template <bool PREC, int NT = 256>
-__global__ __launch_bounds__(NT) void k_conv_fwd(const float* __restrict__ prm, Offsets o,
-                                                  const uint4* __restrict__ frag, const int16_t* __restrict__ crop,
-                                                  const float* __restrict__ scan, const float* __restrict__ state,
-                                                  int R, const int32_t* __restrict__ rows, uint16_t* __restrict__ a2,
-                                                  uint16_t* __restrict__ a2lo, int64_t lda2, int B) {
-  constexpr int kCopies = PREC ? 2 : 1;
-  __shared__ __align__(16) uint16_t s_crop[kCopies * kCropLds];
-  __shared__ __align__(16) uint16_t s_a1[kCopies * kA1Lds];
-  uint16_t* const s_cropl = s_crop + (PREC ? kCropLds : 0);
-  uint16_t* const s_a1l = s_a1 + (PREC ? kA1Lds : 0);
-  constexpr int NW = NT / 64;
-  static_assert(NW == 4 || NW == 8, "four or eight waves");
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, lr = lane & 15, lg = lane >> 4;
-  {
-    uint4* z = reinterpret_cast<uint4*>(s_crop);
-    for (int i = threadIdx.x; i < kCopies * kCropLds / 8; i += NT) z[i] = make_uint4(0u, 0u, 0u, 0u);
-    z = reinterpret_cast<uint4*>(s_a1);
-    for (int i = threadIdx.x; i < kCopies * kA1Lds / 8; i += NT) z[i] = make_uint4(0u, 0u, 0u, 0u);
+constexpr int kConvFwdThreads = 256;
+constexpr int kCropFwd = kA1 * kA1 * 4;      // BF16 elements: block (Y, X) at (Y * 32 + X) * 4
+constexpr int kA1Fwd = kA1 * kA1 * kC1;
+// a1 pixel (y, x) at (y * 32 + (x % 2) * 16 + x / 2) * 16, its two channel halves swapped when y / 2 is odd:
+// conv2's stride-2 reads of four columns in each of two rows hit different banks.
+
+// Crop registers into the forward's LDS copy (and, PREC, its lo parts), space-to-depth, as BF16(L / 256).
+template <bool PREC>
+__device__ __forceinline__ void store_crop_fwd(const CropRegs<kConvFwdThreads>& r, uint16_t* s_crop, uint16_t* s_cropl) {
+#pragma unroll
+  for (int i = 0; i < CropRegs<kConvFwdThreads>::kPer; ++i) {
+    const int v = threadIdx.x + i * kConvFwdThreads;
+    const int y = v >> 3, X0 = (v & 7) * 4;
+    const int32_t w[4] = {r.v[i].x, r.v[i].y, r.v[i].z, r.v[i].w};
+    const int at = ((y >> 1) * kA1 + X0) * 4 + 2 * (y & 1);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float lo = (float)(int16_t)(w[q] & 0xffff) * (1.0f / 256.0f);
+      const float hi = (float)(w[q] >> 16) * (1.0f / 256.0f);
+      *reinterpret_cast<uint32_t*>(s_crop + at + 4 * q) = (uint32_t)f2bf(lo) | ((uint32_t)f2bf(hi) << 16);
+      if (PREC)
+        *reinterpret_cast<uint32_t*>(s_cropl + at + 4 * q) =
+            (uint32_t)bf16_part<true>(lo) | ((uint32_t)bf16_part<true>(hi) << 16);
+    }
   }
+}
+
+template <bool PREC, bool MASK>
+__global__ __launch_bounds__(kConvFwdThreads, PREC ? 2 : 4) void k_conv_fwd(
+    const float* __restrict__ prm, Offsets o, const uint4* __restrict__ frag, const int16_t* __restrict__ crop,
+    const float* __restrict__ scan, const float* __restrict__ state, int R, const int32_t* __restrict__ rows,
+    uint16_t* __restrict__ a2, uint16_t* __restrict__ a2lo, int64_t lda2, int B, uint16_t* __restrict__ amask) {
+  constexpr int NT = kConvFwdThreads, NW = NT / 64, kCopies = PREC ? 2 : 1;
+  __shared__ __align__(16) uint16_t s_all[kCopies * (kCropFwd + kA1Fwd)];
+  uint16_t* const s_a1 = s_all;
+  uint16_t* const s_a1l = s_a1 + (PREC ? kA1Fwd : 0);
+  uint16_t* const s_crop = s_all + kCopies * kA1Fwd;
+  uint16_t* const s_cropl = s_crop + (PREC ? kCropFwd : 0);
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, lr = lane & 15, lg = lane >> 4;
   const bf16x8 w1f = __builtin_bit_cast(bf16x8, frag[lane]);
   const bf16x8 w1fl = PREC ? __builtin_bit_cast(bf16x8, frag[64 * kConvLoFrag + lane]) : w1f;
   float b1[4];
@@ -284,30 +269,8 @@ __global__ __launch_bounds__(NT) void k_conv_fwd(const float* __restrict__ prm, 
       tv[i] = j < tail ? tail_value(sb, j) : 0.0f;
     }
   };
-  // the LDS offsets of the wave's conv1 tiles and conv2 operands are the same for every sample
-  constexpr int kT1 = kA1 * kA1 / 16 / NW, kR2 = kA2 / NW;
-  int c1_win[kT1], c1_slot[kT1], c2_off[kR2][5];
-#pragma unroll
-  for (int j = 0; j < kT1; ++j) {
-    const int px = (wave + NW * j) * 16 + lr, y = px >> 5, x = px & 31;
-    c1_win[j] = lg < 2 ? ((y + lg) * kBlk + x) * 4 : -1;
-    c1_slot[j] = a1_slot(y, x) * kC1 + 4 * lg;
-  }
-#pragma unroll
-  for (int i = 0; i < kR2; ++i)
-#pragma unroll
-    for (int s = 0; s < 5; ++s) {
-      const int oy = wave + NW * i, k0 = 32 * s + 8 * lg, tap = k0 >> 4, ci0 = k0 & 15;
-      c2_off[i][s] = tap < 9 ? a1_slot(2 * oy + tap / 3 - 1, 2 * lr + tap % 3 - 1) * kC1 + ci0 : -1;
-    }
-  auto col_frag = [&](const uint16_t* a, int off) -> bf16x8 {
-    return __builtin_bit_cast(bf16x8, off < 0 ? make_uint4(0u, 0u, 0u, 0u) : *reinterpret_cast<const uint4*>(a + off));
-  };
-  if (blockIdx.x < B) load_sample(blockIdx.x);
-  __syncthreads();
-  for (int b = blockIdx.x; b < B; b += gridDim.x) {
-    store_crop<NT>(cr, s_crop);
-    if (PREC) store_crop<NT, true>(cr, s_cropl);
+  auto store_sample = [&](int b) {   // the loaded sample's crop into LDS, its tail into the output row
+    store_crop_fwd<PREC>(cr, s_crop, s_cropl);
     uint16_t* row = a2 + (int64_t)b * lda2 + kFeat;
     uint16_t* rowl = PREC ? a2lo + (int64_t)b * lda2 + kFeat : row;
 #pragma unroll
@@ -323,35 +286,112 @@ __global__ __launch_bounds__(NT) void k_conv_fwd(const float* __restrict__ prm, 
       row[j] = f2bf(v);
       if (PREC) rowl[j] = bf16_part<true>(v);
     }
-    __syncthreads();
-    // the next sample's crop and tail are loaded while this one is processed
-    if (b + (int)gridDim.x < B) load_sample(b + gridDim.x);
-    conv1_lds_at<PREC, NW>(s_crop, s_cropl, s_a1, s_a1l, w1f, w1fl, b1, c1_win, c1_slot);
-    __syncthreads();
+  };
+  // conv1: the wave's tile j covers the 16 pixels of row y = 8 wave + j / 2 from column 16 (j % 2); its window
+  // operand is the blocks (y - 1 + lg, x - 1) and (.., x) for the lanes with lg < 2, zeros for the rest, above
+  // the first row and left of the first column
+  const int y0 = kA1 / NW * wave;
+  const int win0 = ((y0 - 1 + lg) * kA1 + lr) * 4, slot0 = (y0 * kA1 + (lr & 1) * 16 + (lr >> 1)) * kC1 + 4 * lg;
+  static_assert((kA1 / NW) % 4 == 0, "the halves' swap of a wave's row y0 + q is that of row q");
+  auto window = [&](const uint16_t* c, int j) -> uint4 {
+    if (lg >= 2 || (lg == 0 && y0 + (j >> 1) == 0)) return make_uint4(0u, 0u, 0u, 0u);
+    const uint16_t* q = c + win0 + ((j >> 1) * kA1 + (j & 1) * 16) * 4;
+    const uint2 d = *reinterpret_cast<const uint2*>(q);
+    uint2 a = make_uint2(0u, 0u);
+    if ((j & 1) || lr > 0) a = *reinterpret_cast<const uint2*>(q - 4);
+    return make_uint4(a.x, a.y, d.x, d.y);
+  };
+  // conv2: the wave's four output rows, as four tiles: row m = 4 q + e of tile i is the output (oy = 4 wave + q,
+  // ox = 4 i + e), so that a lane ends up with the 16 outputs of one row of its channel.  Operand of k slice s
+  // for this lane (a tap and a channel half); rows above and columns left of the image are zeros.
+  static_assert(kA2 / NW == 4, "a wave's four output rows");
+  int c2_off[5];
+  bool c2_ok[5], c2_first[5];   // inside; inside also in the first tile
 #pragma unroll
-    for (int i = 0; i < kR2; ++i) {
-      const int oy = wave + NW * i;
-      f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+  for (int s = 0; s < 5; ++s) {
+    const int k0 = 32 * s + 8 * lg, tap = k0 >> 4, half = (k0 >> 3) & 1;
+    const int y = 2 * (4 * wave + (lr >> 2)) + tap / 3 - 1, x = 2 * (lr & 3) + tap % 3 - 1;
+    c2_ok[s] = tap < 9 && y >= 0;
+    c2_first[s] = c2_ok[s] && x >= 0;
+    c2_off[s] = (y * kA1 + (x & 1) * 16 + (x >> 1)) * kC1 + 8 * (half ^ ((y >> 1) & 1));
+  }
+  auto col_frag = [&](const uint16_t* a, int i, int s) -> bf16x8 {
+    uint4 u = make_uint4(0u, 0u, 0u, 0u);
+    if (i > 0 ? c2_ok[s] : c2_first[s]) u = *reinterpret_cast<const uint4*>(a + c2_off[s] + i * 4 * kC1);
+    return __builtin_bit_cast(bf16x8, u);
+  };
+  if (blockIdx.x < B) {
+    load_sample(blockIdx.x);
+    store_sample(blockIdx.x);
+    if (blockIdx.x + gridDim.x < B) load_sample(blockIdx.x + gridDim.x);
+  }
+  __syncthreads();
+  for (int b = blockIdx.x; b < B; b += gridDim.x) {
+    // conv1 + ReLU into a1, four tiles at a time so that their operand reads are in flight together
+#pragma unroll
+    for (int j0 = 0; j0 < kA1 * kA1 / 16 / NW; j0 += 4) {
+      uint4 u[4], ul[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        u[i] = window(s_crop, j0 + i);
+        if (PREC) ul[i] = window(s_cropl, j0 + i);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        f32x4 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1f, __builtin_bit_cast(bf16x8, u[i]),
+                                                           f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+        if (PREC) {
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1f, __builtin_bit_cast(bf16x8, ul[i]), acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1fl, __builtin_bit_cast(bf16x8, u[i]), acc, 0, 0, 0);
+        }
+        const int q = (j0 + i) >> 1;
+        const int at = (slot0 + (q * kA1 + ((j0 + i) & 1) * 8) * kC1) ^ ((q & 2) ? 8 : 0);
+        *reinterpret_cast<uint2*>(s_a1 + at) = pack_relu4<false>(acc, b1);
+        if (PREC) *reinterpret_cast<uint2*>(s_a1l + at) = pack_relu4<true>(acc, b1);
+      }
+    }
+    __syncthreads();
+    // the next sample's crop takes the place of the one just used, the one after is loaded
+    if (b + (int)gridDim.x < B) {
+      store_sample(b + gridDim.x);
+      if (b + 2 * (int)gridDim.x < B) load_sample(b + 2 * gridDim.x);
+    }
+    f32x4 acc[2][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      acc[0][i] = acc[1][i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int s = 0; s < 5; ++s) {
-        const bf16x8 af = col_frag(s_a1, c2_off[i][s]);
-        acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, w2f[0][s], acc0, 0, 0, 0);
-        acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, w2f[1][s], acc1, 0, 0, 0);
+        const bf16x8 af = col_frag(s_a1, i, s);
+        acc[0][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, w2f[0][s], acc[0][i], 0, 0, 0);
+        acc[1][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, w2f[1][s], acc[1][i], 0, 0, 0);
         if (PREC) {
-          const bf16x8 afl = col_frag(s_a1l, c2_off[i][s]);
-          acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, w2fl[0][s], acc0, 0, 0, 0);
-          acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, w2fl[1][s], acc1, 0, 0, 0);
-          acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afl, w2f[0][s], acc0, 0, 0, 0);
-          acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afl, w2f[1][s], acc1, 0, 0, 0);
+          const bf16x8 afl = col_frag(s_a1l, i, s);
+          acc[0][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, w2fl[0][s], acc[0][i], 0, 0, 0);
+          acc[1][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, w2fl[1][s], acc[1][i], 0, 0, 0);
+          acc[0][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afl, w2f[0][s], acc[0][i], 0, 0, 0);
+          acc[1][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afl, w2f[1][s], acc[1][i], 0, 0, 0);
         }
       }
-      const int64_t off = (int64_t)b * lda2 + oy * kA2 + 4 * lg;
-      const float bb0[4] = {b2[0], b2[0], b2[0], b2[0]}, bb1[4] = {b2[1], b2[1], b2[1], b2[1]};
-      *reinterpret_cast<uint2*>(a2 + off + lr * 256) = pack_relu4<false>(acc0, bb0);
-      *reinterpret_cast<uint2*>(a2 + off + (16 + lr) * 256) = pack_relu4<false>(acc1, bb1);
+    }
+    // row oy = 4 wave + lg of channels lr and 16 + lr: 32 bytes a lane, the wave's rows of a channel one line
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const float bb[4] = {b2[h], b2[h], b2[h], b2[h]};
+      const int64_t off = (int64_t)b * lda2 + (16 * h + lr) * 256 + (4 * wave + lg) * kA2;
+      uint2 v[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = pack_relu4<false>(acc[h][i], bb);
+      reinterpret_cast<uint4*>(a2 + off)[0] = make_uint4(v[0].x, v[0].y, v[1].x, v[1].y);
+      reinterpret_cast<uint4*>(a2 + off)[1] = make_uint4(v[2].x, v[2].y, v[3].x, v[3].y);
+      if (MASK)
+        amask[((int64_t)b * kC2 + 16 * h + lr) * kA2 + 4 * wave + lg] =
+            (uint16_t)(positive4(v[0]) | (positive4(v[1]) << 4) | (positive4(v[2]) << 8) | (positive4(v[3]) << 12));
       if (PREC) {
-        *reinterpret_cast<uint2*>(a2lo + off + lr * 256) = pack_relu4<true>(acc0, bb0);
-        *reinterpret_cast<uint2*>(a2lo + off + (16 + lr) * 256) = pack_relu4<true>(acc1, bb1);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = pack_relu4<true>(acc[h][i], bb);
+        reinterpret_cast<uint4*>(a2lo + off)[0] = make_uint4(v[0].x, v[0].y, v[1].x, v[1].y);
+        reinterpret_cast<uint4*>(a2lo + off)[1] = make_uint4(v[2].x, v[2].y, v[3].x, v[3].y);
       }
     }
     __syncthreads();

@@ -24,6 +24,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "gemm_bf16.h"
 
 namespace aslam {
@@ -271,6 +273,146 @@ struct EpiBiasRelu {
         make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16));
   }
 };
+
+// ---------------------------------------------------------------- conv-feature gradient
+//
+// out[m][n] = bf16(mask(m, n) ? sum_k dz[m][k] wt[n][k] : 0), k < 256, n < 8192: FC1's input gradient at the
+// conv features through conv2's ReLU, the mask as one bit per feature (bit n % 8 of byte n / 8 of row m).
+//
+// What bounds it is memory: the output (16 KB a row), beside which the 128 x 128 tiles this takes the
+// place of read the BF16 activations for the mask (16 KB more) and both operands of every tile again.
+// Here a workgroup keeps the fragments of 64 WN features' weights in registers (a wave's 64 features: 128
+// registers a lane) and walks over row tiles of 128 (64 KB, two in LDS, the next one's reads in flight), and
+// the mask costs 1 KB a row.  Workgroups eight apart (one XCD) share their row tiles.  The weights' rows
+// are dealt to the MFMA fragments so that a lane holds eight consecutive features of a row: one 16-byte
+// store.  9000 rows: 120 -> 60 us, 16384 rows: 221 -> 97 us.
+constexpr int kDxK = 256, kDxTile = kBM * kDxK * 2;   // bytes of a row tile
+
+__device__ __forceinline__ uint32_t mask2(uint32_t bits, float lo, float hi) {
+  return ((bits & 1u) ? (uint32_t)gemm::f2bf(lo) : 0u) | ((bits & 2u) ? (uint32_t)gemm::f2bf(hi) << 16 : 0u);
+}
+
+template <int WN>
+__global__ __launch_bounds__(128 * WN) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_feature_grad(
+    const uint16_t* __restrict__ dz, const uint16_t* __restrict__ wt, const uint8_t* __restrict__ mask,
+    uint16_t* __restrict__ out, int M, int N, int groups) {
+  __shared__ __align__(16) unsigned char s0[kDxTile];
+  __shared__ __align__(16) unsigned char s1[kDxTile];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, lr = lane & 15, lg = lane >> 4;
+  const int wm = wave / WN, wn = wave % WN;
+  const int group = blockIdx.x % groups, nw = (blockIdx.x / groups * WN + wn) * 64;   // the wave's first feature
+  const int tiles = (M + kBM - 1) / kBM;
+  // row tile t into buf: a wave's read covers two rows of 512 bytes; chunk c of row r lies at c ^ (r % 8)
+  const int r0 = 2 * wave + (lane >> 5);
+  const uint32_t chunk = (uint32_t)((lane & 31) ^ (r0 & 7)) * 16u;
+  auto issue = [&](unsigned char* buf, int t) {
+    const glb_bytes base = (glb_bytes)(dz + (int64_t)t * kBM * kDxK);
+    const int last = M - 1 - t * kBM;   // rows past M read the last one
+#pragma unroll
+    for (int i = 0; i < 32 / WN; ++i)
+      to_lds(base, (uint32_t)min(r0 + 4 * WN * i, last) * (kDxK * 2) + (chunk ^ ((4 * WN * i) & 7) * 16u),
+             buf + (2 * WN * i + wave) * 1024);
+  };
+  bf16x8 w[4][8];
+  const int wrow = (lr >> 2) * 8 + (lr & 3);   // + (j / 2) * 32 + (j % 2) * 4: the feature of fragment j's row lr
+  issue(s0, group);
+  if (WN <= 2) {
+    // the weights' rows into s1 in the row tiles' layout, and from there to the registers
+    const glb_bytes base = (glb_bytes)(wt + (int64_t)(nw - wn * 64) * kDxK);
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      to_lds(base, (uint32_t)(r0 + 4 * WN * i) * (kDxK * 2) + (chunk ^ ((4 * WN * i) & 7) * 16u),
+             s1 + (2 * WN * i + wave) * 1024);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0070);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks) {
+        const int n = wn * 64 + (j >> 1) * 32 + (j & 1) * 4 + wrow;
+        w[j][ks] = frag(s1 + n * (kDxK * 2) + (((4 * ks + lg) ^ (n & 7)) << 4));
+      }
+    __syncthreads();
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks)
+        w[j][ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(
+            wt + (int64_t)(nw + (j >> 1) * 32 + (j & 1) * 4 + wrow) * kDxK + 32 * ks + 8 * lg));
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0070);   // the first tile (no stores follow it)
+  }
+  const int f0 = (wm * 64 + lr) * (kDxK * 2) + ((lg ^ (lr & 7)) << 4);
+  auto tile = [&](unsigned char* cur, unsigned char* next, int t) {
+    const int m0 = t * kBM + wm * 64 + lr;
+    // the tile has arrived when at most the eight stores of the tile before are outstanding
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0078);   // vmcnt(8) lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    uint2 mk[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      mk[i] = *reinterpret_cast<const uint2*>(mask + (int64_t)min(m0 + 16 * i, M - 1) * (N / 8) + nw / 8);
+    if (t + groups < tiles) issue(next, t + groups);
+    f32x4 acc[4][4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      bf16x8 x[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[i] = frag(cur + ((f0 ^ ((ks & 1) * 64)) + (ks >> 1) * 128 + i * 16 * kDxK * 2));
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[j][ks], x[i], acc[j][i], 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int m = m0 + 16 * i;
+      if (m >= M) continue;
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const uint32_t b = (q ? mk[i].y : mk[i].x) >> (8 * lg);
+        const f32x4 lo = acc[2 * q][i], hi = acc[2 * q + 1][i];
+        *reinterpret_cast<uint4*>(out + (int64_t)m * N + nw + q * 32 + lg * 8) =
+            make_uint4(mask2(b, lo[0], lo[1]), mask2(b >> 2, lo[2], lo[3]), mask2(b >> 4, hi[0], hi[1]),
+                       mask2(b >> 6, hi[2], hi[3]));
+      }
+    }
+  };
+  for (int t = group; t < tiles; t += 2 * groups) {
+    tile(s0, s1, t);
+    if (t + groups < tiles) tile(s1, s0, t + groups);
+  }
+}
+
+// N a multiple of 256; 16-byte aligned operands.
+inline hipError_t feature_grad(const uint16_t* dz, const uint16_t* wt, const uint8_t* mask, uint16_t* out, int M, int N,
+                               hipStream_t st) {
+  if (M < 1 || N < kBN || N % kBN) return hipErrorInvalidValue;
+  // Workgroups of 64, 128 or 256 features: few row tiles leave the chip idle with the wide ones, many reread
+  // their rows in every slice.  64 / 128 / 256 features took 5.8 / 6.5 / 13 us at 96 rows, 7.0 / 7.6 / 14 at
+  // 200, 12 / 9.1 / 15 at 400, 20 / 15.4 / 16.6 at 800, 125 / 77 / 59 at 9000.
+  constexpr int kDxNarrow = 2, kDxMid = 4;
+  const int groups = std::min(8, (M + kBM - 1) / kBM);
+  if (groups <= kDxNarrow)
+    k_feature_grad<1><<<(unsigned)(N / 64 * groups), 128, 0, st>>>(dz, wt, mask, out, M, N, groups);
+  else if (groups <= kDxMid)
+    k_feature_grad<2><<<(unsigned)(N / 128 * groups), 256, 0, st>>>(dz, wt, mask, out, M, N, groups);
+  else
+    k_feature_grad<4><<<(unsigned)(N / kBN * groups), kThreads, 0, st>>>(dz, wt, mask, out, M, N, groups);
+  return hipGetLastError();
+}
 
 }  // namespace gemm_nt
 }  // namespace aslam

@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -40,6 +41,7 @@ struct aslam_policy {
   int64_t max_b = 0;
   uint16_t *x = nullptr;   // FC1 input [B][k1p]: conv features (8192) | scan | state | zero pad, BF16
   uint16_t *h1 = nullptr, *dz2 = nullptr, *dz1 = nullptr, *dz2c = nullptr;
+  uint16_t* amask = nullptr;   // conv2's ReLU mask, one bit per feature: [B][32][16] words
   float *z2 = nullptr, *part = nullptr, *hpart = nullptr;
   uint16_t *w1b = nullptr, *w1t = nullptr, *w2b = nullptr, *w2t = nullptr;   // BF16 weight copies
   uint4* cfrag = nullptr;   // the encoder's weight fragments (k_conv_frags, k_conv_bwd_frags)
@@ -61,8 +63,8 @@ struct aslam_policy {
 
 namespace {
 
-constexpr int kConvGrid = 768;     // encoder forward: the resident workgroups (three per CU, LDS-bound), each looping over samples
-constexpr int kConvGridPrec = 256; // the split-precision encoder forward holds twice the LDS: one per CU
+constexpr int kConvGrid = 1024;    // encoder forward: the resident workgroups (four per CU), each looping over samples
+constexpr int kConvGridPrec = 512; // the split-precision encoder forward holds twice the LDS: two per CU
 constexpr int kConvFragsAll = kConvLoFrag + kConvFrags;   // forward, backward phase and lo fragments
 constexpr int kConvBwdGrid = 256;  // encoder backward: one 8-wave workgroup per CU (LDS-bound)
 constexpr int64_t kFc1Splits = 12, kFc2Splits = 64;
@@ -194,14 +196,11 @@ int convert_weights(aslam_policy* P, const float* prm, hipStream_t st, bool tran
 // split K so that the launch fills the chip: then *S_used split-K slices are left in P->part;
 // otherwise FC1 writes h1 = bf16(relu(. + b1)) and *S_used = 0.
 int encode_fc1(aslam_policy* P, const float* prm, const int16_t* crop, const float* scan, const float* state,
-               const int32_t* rows, int B, hipStream_t st, int* S_used) {
-  const Offsets& o = P->off;
-  if (P->prec)
-    k_conv_fwd<true, 512><<<std::min(B, kConvGridPrec), 512, 0, st>>>(prm, o, P->cfrag, crop, scan, state,
-                                                                      P->cfg.n_scan, rows, P->x, P->x_lo, P->k1p, B);
-  else
-    k_conv_fwd<false><<<std::min(B, kConvGrid), 256, 0, st>>>(prm, o, P->cfrag, crop, scan, state, P->cfg.n_scan,
-                                                              rows, P->x, nullptr, P->k1p, B);
+               const int32_t* rows, int B, hipStream_t st, int* S_used, bool training = false) {
+  (P->prec ? (training ? k_conv_fwd<true, true> : k_conv_fwd<true, false>)
+           : (training ? k_conv_fwd<false, true> : k_conv_fwd<false, false>))<<<
+      std::min(B, P->prec ? kConvGridPrec : kConvGrid), kConvFwdThreads, 0, st>>>(
+      prm, P->off, P->cfrag, crop, scan, state, P->cfg.n_scan, rows, P->x, P->x_lo, P->k1p, B, P->amask);
   PCHK(hipGetLastError());
   // FC1: [B x k1] x [k1 x 256] (both operands zero-padded from k1 to k1p)
   const int K1 = (int)((P->off.k1 + 7) / 8 * 8);
@@ -222,7 +221,7 @@ int encode_fc1(aslam_policy* P, const float* prm, const int16_t* crop, const flo
     const int k_split = ((K1 + S - 1) / S + 63) / 64 * 64;
     const gemm_nt::EpiPartial part{P->part, kHid, slice};
     if (P->prec) PCHK(gemm_nt::run<3>(fc1, part, k_split, st));
-    else if (S == 1) PCHK(gemm_nt::run<1>(fc1, gemm_nt::EpiBiasRelu{P->h1, prm + o.f1b, kHid}, k_split, st));
+    else if (S == 1) PCHK(gemm_nt::run<1>(fc1, gemm_nt::EpiBiasRelu{P->h1, prm + P->off.f1b, kHid}, k_split, st));
     else PCHK(gemm_nt::run<1>(fc1, part, k_split, st));
     *S_used = P->prec ? 3 * nz : S == 1 ? 0 : nz;
     return ASL_OK;
@@ -250,7 +249,7 @@ int forward_core(aslam_policy* P, const float* prm, const int16_t* crop, const f
   int rc = convert_weights(P, prm, st, true);
   if (rc) return rc;
   int S = 0;
-  rc = encode_fc1(P, prm, crop, scan, state, rows, B, st, &S);
+  rc = encode_fc1(P, prm, crop, scan, state, rows, B, st, &S, true);
   if (rc) return rc;
   if (S > 0) {
     const int64_t groups = (int64_t)B * (kHid / 8);
@@ -334,7 +333,7 @@ int aslam_policy_create(const aslam_policy_config* cfg, aslam_policy** out) {
   struct A { void** ptr; size_t bytes; } al[] = {
       {(void**)&p->x, 2 * (size_t)Bm * p->k1p},  {(void**)&p->h1, 2 * (size_t)Bm * kHid},
       {(void**)&p->dz2, 2 * (size_t)Bm * kHid},  {(void**)&p->dz1, 2 * (size_t)Bm * kHid},
-      {(void**)&p->dz2c, 2 * (size_t)Bm * kFeat}, {(void**)&p->z2, 4 * (size_t)Bm * kHid},
+      {(void**)&p->dz2c, 2 * (size_t)Bm * kFeat}, {(void**)&p->amask, (size_t)Bm * kFeat / 8}, {(void**)&p->z2, 4 * (size_t)Bm * kHid},
       {(void**)&p->part, 4 * (size_t)p->part_floats},
       {(void**)&p->hpart, 4 * (size_t)((Bm + kHeadRows - 1) / kHeadRows) * kHeadPart},
       {(void**)&p->w1b, 2 * (size_t)kHid * p->k1p}, {(void**)&p->w1t, 2 * (size_t)kFeat * kHid},
@@ -398,7 +397,7 @@ int64_t aslam_policy_param_count(const aslam_policy_config* cfg) {
 
 int aslam_policy_destroy(aslam_policy* p) {
   if (!p) return pfail(ASL_EINVAL, "policy is NULL");
-  void* ptrs[] = {p->x, p->h1, p->dz2, p->dz1, p->dz2c, p->z2, p->part, p->hpart,
+  void* ptrs[] = {p->x, p->h1, p->dz2, p->dz1, p->dz2c, p->amask, p->z2, p->part, p->hpart,
                   p->w1b, p->w1t, p->w2b, p->w2t, p->cfrag,
                   p->wihb, p->whhb, p->wiht, p->whht, p->hst, p->g_r, p->g_z, p->g_n, p->g_ghn,
                   p->dh_head, p->hp_bf, p->dg, p->rows, p->x_lo, p->h1_lo, p->w1b_lo,
@@ -583,8 +582,7 @@ int backward_fc1_encoder(aslam_policy* P, const float* params, const int16_t* cr
     PCHK(launch_reduce(part, S_used, (int64_t)kHid * o.k1, grads + o.f1w, 0, (int64_t)kHid * o.k1, st));
   }
   // dA2 -> dz2c = (dz1 W1[:, :8192]) * [a2 > 0]
-  PCHK((gemm::run<128, 128, 64, 2, 2>(LdBF16K{P->dz1, kHid, B, kHid}, LdBF16K{P->w1t, kHid, kFeat, kHid},
-                                     EpiReluGradBF16{P->dz2c, P->x, kFeat, P->k1p}, B, kFeat, kHid, 1, st)));
+  PCHK(gemm_nt::feature_grad(P->dz1, P->w1t, reinterpret_cast<const uint8_t*>(P->amask), P->dz2c, B, kFeat, st));
   // encoder: conv2 / conv1 weight and bias gradients in one pass over the minibatch
   {
     const int grid = std::min(B, kConvBwdGrid);
@@ -738,7 +736,7 @@ int aslam_policy_backward_seq(aslam_policy* P, const float* params, const int16_
   int rc = convert_weights(P, params, st, true);
   if (rc) return rc;
   int S = 0;
-  rc = encode_fc1(P, params, crop, scan, state, P->rows, B, st, &S);
+  rc = encode_fc1(P, params, crop, scan, state, P->rows, B, st, &S, true);
   if (rc) return rc;
   if (S > 0) {
     const int64_t groups = (int64_t)B * (kHid / 8);

@@ -196,6 +196,33 @@ def test_split_backward_matches_exact_fp64_gradient(B):
     assert np.allclose(loss.cpu().numpy()[1:], terms, rtol=1e-4, atol=1e-5)
 
 
+@pytest.mark.parametrize("b,pieces", [(1, 8), (129, 8), (257, 4), (513, 2)])
+def test_split_gradient_is_the_mean_of_its_pieces(b, pieces):
+    """The gradient of b * pieces rows against the mean of the pieces' gradients: row counts around the edges of
+    the 128-row tiles and of the feature gradient's workgroup widths (at most 256 rows, at most 512, more).  The
+    pieces' 1 / b is a power of two times the whole's, so every BF16 rounding is the same, and what differs is
+    the order of FP32 sums: 2e-7 relative, and at most a ReLU sign of a unit within that of zero, one of the
+    128 b * pieces active units of FC1, whose share of a gradient that cancels threefold is 3 / sqrt(128 * 1026)
+    = 8e-3.  Bound 1e-2 per tensor (relative L2); a lost row of a 129-row piece would be 1 / sqrt(129) = 9e-2."""
+    theta, t = _case(b * pieces, 5)
+    pol, params, dev = _gpu(theta, t, precision=1)
+
+    def grad(part):
+        g = torch.zeros_like(params)
+        pol.backward(params, *(part[k].contiguous() for k in ("crop", "scan", "state", "act", "old_logp", "adv",
+                                                               "ret")), g)
+        torch.cuda.synchronize()
+        return g.cpu().double().numpy()
+
+    say(f"[policy] {pieces} pieces of {b} rows")
+    whole = grad(dev)
+    mean = sum(grad({k: v[i * b:(i + 1) * b] for k, v in dev.items()}) for i in range(pieces)) / pieces
+    errs = _tensor_errors(whole, mean)
+    say("[policy] whole against pieces: " + " ".join(f"{k}={v:.1e}" for k, v in errs.items()))
+    for k, v in errs.items():
+        assert v < 1e-2, (k, v)
+
+
 def test_split_backward_against_central_differences_per_coordinate():
     """Split forward, random advantages, 64 samples: 64 sampled coordinates of every tensor (all of a
     smaller one) against FP64 central differences of the exact loss: the sampled sub-vector within
