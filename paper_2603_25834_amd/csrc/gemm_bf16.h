@@ -1,21 +1,16 @@
 // gemm_bf16.h -- generic BF16 x BF16 -> FP32 MFMA GEMM for gfx950 (library-internal).
 //
-// C[M,N] = sum_k A[m,k] B[k,n] with operands fetched through loader functors
-// (so a GEMM can read a transposed matrix or a concatenation without
-// materialising it) and results handed to an epilogue functor (bias, ReLU,
-// masks, BF16 stores, split-K partial sums).
+// C[M,N] = sum_k A[m,k] B[k,n] with operands contiguous along k, fetched through
+// loader functors, and results handed to an epilogue functor (bias, ReLU,
+// masks, BF16 stores, split-K partial sums).  Weight gradients, whose operands
+// are contiguous along their rows, are gemm_tn.h's.
 //
 // Tiling: a workgroup of 256 threads (4 waves) owns a BM x BN tile of C; the
 // waves are arranged WM x WN and each accumulates a (BM/WM) x (BN/WN) sub-tile
 // in 16x16 MFMA fragments.  K advances BK per stage, double buffered in LDS,
 // with the global loads of the next two stages in registers while the current
 // stage feeds the MFMAs (one stage ahead on edge tiles).  Both operands are staged as [row][k]
-// (rows padded by 8 elements) and read as one 16-byte fragment per lane.  An
-// operand whose source is contiguous along the row index is transposed on the
-// way in: a thread loads the same eight rows at k and k + 1 and stores eight
-// 32-bit (k, k + 1) pairs; the 16-byte chunks of a row are XOR-swizzled with
-// (row / 8) so that those stores, eight rows apart across lanes, spread over
-// the LDS banks.
+// (rows padded by 8 elements) and read as one 16-byte fragment per lane.
 // The finished tile is staged through LDS as FP32 so that the epilogue sees
 // eight consecutive columns of a row per call (16-byte loads and stores).
 //
@@ -44,9 +39,7 @@ __device__ __forceinline__ uint16_t lane16(const uint4& v, int j) {
 }
 
 // Loader contract (eight BF16 packed in a uint4, element j in bits 16j..16j+15):
-//   static constexpr bool kMajor;
-//   kMajor  : fetch(i, k) = X(i, k + j), j < 8 (k multiple of 8)
-//   !kMajor : fetch(i, k) = X(i + j, k), j < 8 (i multiple of 8)
+//   fetch(i, k) = X(i, k + j), j < 8 (k multiple of 8)
 // where X(i, k) is A(m = i, k) for the A operand and B(k, n = i) for B.
 // Out-of-range elements must read as 0.
 //
@@ -88,14 +81,11 @@ template <class L>
 using Bound = typename BoundT<L>::type;
 
 // LDS elements of one stage of an operand with ROWS rows ([row][k], rows padded by 8).
-template <bool KMAJOR, int ROWS, int BK>
+template <int ROWS, int BK>
 struct Stage {
   static constexpr int kLd = BK + 8;
   static constexpr int kElems = ROWS * kLd;
-  // element (r, k) of a transposed (!KMAJOR) stage: 16-byte chunk k / 8 swizzled with (r / 8)
-  __device__ static __forceinline__ int at(int r, int k) {
-    return KMAJOR ? r * kLd + k : r * kLd + ((((k >> 3) ^ (r >> 3)) & (BK / 8 - 1)) << 3) + (k & 7);
-  }
+  __device__ static __forceinline__ int at(int r, int k) { return r * kLd + k; }
 };
 
 template <int BM, int BN, int BK, int WM, int WN>
@@ -106,33 +96,25 @@ struct Cfg {
   static_assert(FM * 16 == TM && FN * 16 == TN, "fragment tiling");
   static_assert(BK % 32 == 0, "BK is a multiple of the MFMA depth");
   static constexpr int VA = BM * BK / 8, VB = BN * BK / 8;            // 8-element vectors per stage
-  // vectors per thread, rounded up to even (a transposed operand is fetched in pairs)
-  static constexpr int PA = ((VA + 255) / 256 + 1) & ~1, PB = ((VB + 255) / 256 + 1) & ~1;
+  static constexpr int PA = (VA + 255) / 256, PB = (VB + 255) / 256;   // vectors per thread
   static constexpr int kEpiBytes = BM * (BN + 4) * 4;                 // FP32 tile (rows padded)
 };
 
-// kMajor: register p holds vector v = tid + 256 p = (row v / (BK/8), k-chunk v % (BK/8)).
-// !kMajor: registers 2q, 2q + 1 hold pair w = tid + 256 q = (k = 2 (w / (ROWS/8)), row-chunk w % (ROWS/8))
-// at k and k + 1 (consecutive lanes read consecutive row-chunks of the same source rows).
+// Register p holds vector v = tid + 256 p = (row v / (BK/8), k-chunk v % (BK/8)).
 // Element offsets, from the tile origin, of the vectors fetch_tile loads into this thread's registers
 // (the same assignment as fetch_tile), used by the unchecked path for tiles that lie wholly inside a
-// plain strided matrix (loader fields p, ld, rows, cols): 256 threads cover whole rows (k-major) or
-// whole k pairs, so the offset of register p (pair q) is base + p * step (base + q * step, + ld for k + 1).
+// plain strided matrix (loader fields p, ld, rows, cols): 256 threads cover whole rows, so the offset of
+// register p is base + p * step.
 struct TileOff {
   int64_t base, step;
 };
 
 template <class L, int ROWS, int BK>
 __device__ __forceinline__ TileOff tile_offsets(const L& ld) {
-  static_assert(256 % (BK / 8) == 0 && 256 % (ROWS / 8) == 0, "256 threads cover whole rows / k pairs");
+  static_assert(256 % (BK / 8) == 0, "256 threads cover whole rows");
   TileOff o;
-  if (L::kMajor) {
-    o.base = (int64_t)(threadIdx.x / (BK / 8)) * ld.ld + (threadIdx.x % (BK / 8)) * 8;
-    o.step = (int64_t)(256 / (BK / 8)) * ld.ld;
-  } else {
-    o.base = (int64_t)(2 * (threadIdx.x / (ROWS / 8))) * ld.ld + (threadIdx.x % (ROWS / 8)) * 8;
-    o.step = (int64_t)(2 * (256 / (ROWS / 8))) * ld.ld;
-  }
+  o.base = (int64_t)(threadIdx.x / (BK / 8)) * ld.ld + (threadIdx.x % (BK / 8)) * 8;
+  o.step = (int64_t)(256 / (BK / 8)) * ld.ld;
   return o;
 }
 
@@ -148,22 +130,11 @@ __device__ __forceinline__ bool tile_interior(const L& ld, int row0, int k0) {
 template <class L, int ROWS, int BK, int P>
 __device__ __forceinline__ void fetch_fast(const L& ld, int row0, int k0, u32x4 (&regs)[P], const TileOff& off) {
   constexpr int V = ROWS * BK / 8;
-  const uint16_t* base = (L::kMajor ? ld.p + (int64_t)row0 * ld.ld + k0 : ld.p + (int64_t)k0 * ld.ld + row0) + off.base;
-  if (L::kMajor) {
+  const uint16_t* base = ld.p + (int64_t)row0 * ld.ld + k0 + off.base;
 #pragma unroll
-    for (int p = 0; p < P; ++p) {
-      const int v = threadIdx.x + p * 256;
-      if (V % 256 == 0 || v < V) regs[p] = *reinterpret_cast<const u32x4*>(base + p * off.step);
-    }
-  } else {
-#pragma unroll
-    for (int q = 0; q < P / 2; ++q) {
-      const int w = threadIdx.x + q * 256;
-      if (V / 2 % 256 == 0 || w < V / 2) {
-        regs[2 * q] = *reinterpret_cast<const u32x4*>(base + q * off.step);
-        regs[2 * q + 1] = *reinterpret_cast<const u32x4*>(base + q * off.step + ld.ld);
-      }
-    }
+  for (int p = 0; p < P; ++p) {
+    const int v = threadIdx.x + p * 256;
+    if (V % 256 == 0 || v < V) regs[p] = *reinterpret_cast<const u32x4*>(base + p * off.step);
   }
 }
 
@@ -174,27 +145,13 @@ __device__ __forceinline__ void fetch_tile(const L& ld, int row0, int k0, u32x4 
     fetch_fast<L, ROWS, BK>(ld, row0, k0, regs, off);
     return;
   }
-  if (L::kMajor) {
 #pragma unroll
-    for (int p = 0; p < P; ++p) {
-      const int v = threadIdx.x + p * 256;
-      if (V % 256 == 0 || v < V) {
-        const int i = v / (BK / 8), kq = v % (BK / 8);
-        const uint4 u = ld.fetch(row0 + i, k0 + kq * 8);
-        regs[p] = u32x4{u.x, u.y, u.z, u.w};
-      }
-    }
-  } else {
-    constexpr int VP = V / 2;
-#pragma unroll
-    for (int q = 0; q < P / 2; ++q) {
-      const int w = threadIdx.x + q * 256;
-      if (VP % 256 == 0 || w < VP) {
-        const int k = 2 * (w / (ROWS / 8)), iq = w % (ROWS / 8);
-        const uint4 u0 = ld.fetch(row0 + iq * 8, k0 + k), u1 = ld.fetch(row0 + iq * 8, k0 + k + 1);
-        regs[2 * q] = u32x4{u0.x, u0.y, u0.z, u0.w};
-        regs[2 * q + 1] = u32x4{u1.x, u1.y, u1.z, u1.w};
-      }
+  for (int p = 0; p < P; ++p) {
+    const int v = threadIdx.x + p * 256;
+    if (V % 256 == 0 || v < V) {
+      const int i = v / (BK / 8), kq = v % (BK / 8);
+      const uint4 u = ld.fetch(row0 + i, k0 + kq * 8);
+      regs[p] = u32x4{u.x, u.y, u.z, u.w};
     }
   }
 }
@@ -206,47 +163,27 @@ __device__ __forceinline__ bool rows_interior(const L& ld, int row0) {
   return row0 + ROWS <= ld.rows && (ld.ld & 7) == 0 && (reinterpret_cast<uintptr_t>(ld.p) & 15) == 0;
 }
 
-template <class L, int ROWS, int BK, int P>
+template <int ROWS, int BK, int P>
 __device__ __forceinline__ void store_tile(uint16_t* s, const u32x4 (&regs)[P]) {
-  using S = Stage<L::kMajor, ROWS, BK>;
   constexpr int V = ROWS * BK / 8;
-  if (L::kMajor) {
 #pragma unroll
-    for (int p = 0; p < P; ++p) {
-      const int v = threadIdx.x + p * 256;
-      if (V % 256 == 0 || v < V) {
-        const int i = v / (BK / 8), kq = v % (BK / 8);
-        *reinterpret_cast<u32x4*>(s + S::at(i, kq * 8)) = regs[p];
-      }
-    }
-  } else {
-    constexpr int VP = V / 2;
-#pragma unroll
-    for (int q = 0; q < P / 2; ++q) {
-      const int w = threadIdx.x + q * 256;
-      if (VP % 256 == 0 || w < VP) {
-        const int k = 2 * (w / (ROWS / 8)), iq = w % (ROWS / 8);
-        const u32x4 a = regs[2 * q], b = regs[2 * q + 1];
-        const uint32_t wa[4] = {a[0], a[1], a[2], a[3]}, wb[4] = {b[0], b[1], b[2], b[3]};
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const uint32_t lo = (wa[j >> 1] >> ((j & 1) * 16)) & 0xffffu;
-          const uint32_t hi = (wb[j >> 1] >> ((j & 1) * 16)) & 0xffffu;
-          *reinterpret_cast<uint32_t*>(s + S::at(iq * 8 + j, k)) = lo | (hi << 16);
-        }
-      }
+  for (int p = 0; p < P; ++p) {
+    const int v = threadIdx.x + p * 256;
+    if (V % 256 == 0 || v < V) {
+      const int i = v / (BK / 8), kq = v % (BK / 8);
+      *reinterpret_cast<u32x4*>(s + Stage<ROWS, BK>::at(i, kq * 8)) = regs[p];
     }
   }
 }
 
 // MFMA fragment of row r (tile-local) and k values kk .. kk + 7 (kk multiple of 8).
-template <bool KMAJOR, int ROWS, int BK>
+template <int ROWS, int BK>
 __device__ __forceinline__ bf16x8 load_frag(const uint16_t* s, int r, int kk) {
-  return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(s + Stage<KMAJOR, ROWS, BK>::at(r, kk)));
+  return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(s + Stage<ROWS, BK>::at(r, kk)));
 }
 
 // The MFMAs of one staged K step: the wave's FM x FN fragments of C, BK / 32 products each.
-template <int BM, int BN, int BK, int WM, int WN, bool AMAJ, bool BMAJ>
+template <int BM, int BN, int BK, int WM, int WN>
 __device__ __forceinline__ void mma_stage(const uint16_t* a_st, const uint16_t* b_st, int ra0, int rb0, int kl,
                                           f32x4 (&acc)[Cfg<BM, BN, BK, WM, WN>::FM][Cfg<BM, BN, BK, WM, WN>::FN]) {
   using C = Cfg<BM, BN, BK, WM, WN>;
@@ -254,10 +191,10 @@ __device__ __forceinline__ void mma_stage(const uint16_t* a_st, const uint16_t* 
   for (int kk = 0; kk < BK; kk += 32) {
     bf16x8 bf[C::FN];
 #pragma unroll
-    for (int j = 0; j < C::FN; ++j) bf[j] = load_frag<BMAJ, BN, BK>(b_st, rb0 + j * 16, kk + kl);
+    for (int j = 0; j < C::FN; ++j) bf[j] = load_frag<BN, BK>(b_st, rb0 + j * 16, kk + kl);
 #pragma unroll
     for (int i = 0; i < C::FM; ++i) {
-      const bf16x8 af = load_frag<AMAJ, BM, BK>(a_st, ra0 + i * 16, kk + kl);
+      const bf16x8 af = load_frag<BM, BK>(a_st, ra0 + i * 16, kk + kl);
 #pragma unroll
       for (int j = 0; j < C::FN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bf[j], acc[i][j], 0, 0, 0);
     }
@@ -299,8 +236,8 @@ __global__ __launch_bounds__(256) void k_gemm(LA0 la0, LB0 lb0, EPI epi, int M, 
   using LA = Bound<LA0>;
   using LB = Bound<LB0>;
   using C = Cfg<BM, BN, BK, WM, WN>;
-  using SA = Stage<LA::kMajor, BM, BK>;
-  using SB = Stage<LB::kMajor, BN, BK>;
+  using SA = Stage<BM, BK>;
+  using SB = Stage<BN, BK>;
   constexpr int kStageBytes = 2 * (SA::kElems + SB::kElems) * 2;   // double-buffered A and B
   constexpr int kLds = kStageBytes > C::kEpiBytes ? kStageBytes : C::kEpiBytes;
   __shared__ __align__(16) unsigned char smem[kLds];
@@ -356,29 +293,29 @@ __global__ __launch_bounds__(256) void k_gemm(LA0 la0, LB0 lb0, EPI epi, int M, 
     const int k1 = kb + BK * min(1, nfast - 1);
     fetch_fast<LA, BM, BK>(la, m_blk, k1, ra_o, oa);
     fetch_fast<LB, BN, BK>(lb, n_blk, k1, rb_o, ob);
-    store_tile<LA, BM, BK>(sA, ra_e);
-    store_tile<LB, BN, BK>(sB, rb_e);
+    store_tile<BM, BK>(sA, ra_e);
+    store_tile<BN, BK>(sB, rb_e);
     __syncthreads();
     for (; t + 2 <= nfast; t += 2) {
       const int k2 = kb + BK * min(t + 2, nfast - 1);
       fetch_fast<LA, BM, BK>(la, m_blk, k2, ra_e, oa);
       fetch_fast<LB, BN, BK>(lb, n_blk, k2, rb_e, ob);
-      mma_stage<BM, BN, BK, WM, WN, LA::kMajor, LB::kMajor>(sA, sB, ra0, rb0, kl, acc);
-      store_tile<LA, BM, BK>(sA1, ra_o);
-      store_tile<LB, BN, BK>(sB1, rb_o);
+      mma_stage<BM, BN, BK, WM, WN>(sA, sB, ra0, rb0, kl, acc);
+      store_tile<BM, BK>(sA1, ra_o);
+      store_tile<BN, BK>(sB1, rb_o);
       __syncthreads();
       const int k3 = kb + BK * min(t + 3, nfast - 1);
       fetch_fast<LA, BM, BK>(la, m_blk, k3, ra_o, oa);
       fetch_fast<LB, BN, BK>(lb, n_blk, k3, rb_o, ob);
-      mma_stage<BM, BN, BK, WM, WN, LA::kMajor, LB::kMajor>(sA1, sB1, ra0, rb0, kl, acc);
+      mma_stage<BM, BN, BK, WM, WN>(sA1, sB1, ra0, rb0, kl, acc);
       if (t + 2 < nfast) {
-        store_tile<LA, BM, BK>(sA, ra_e);
-        store_tile<LB, BN, BK>(sB, rb_e);
+        store_tile<BM, BK>(sA, ra_e);
+        store_tile<BN, BK>(sB, rb_e);
       }
       __syncthreads();
     }
     if (t < nfast) {   // an odd count: the last step is in buffer 0
-      mma_stage<BM, BN, BK, WM, WN, LA::kMajor, LB::kMajor>(sA, sB, ra0, rb0, kl, acc);
+      mma_stage<BM, BN, BK, WM, WN>(sA, sB, ra0, rb0, kl, acc);
       __syncthreads();
       ++t;
     }
@@ -387,8 +324,8 @@ __global__ __launch_bounds__(256) void k_gemm(LA0 la0, LB0 lb0, EPI epi, int M, 
   if (t < nsteps) {
     fetch_tile<LA, BM, BK>(la, m_blk, kb + t * BK, ra_e, oa);
     fetch_tile<LB, BN, BK>(lb, n_blk, kb + t * BK, rb_e, ob);
-    store_tile<LA, BM, BK>(sA, ra_e);
-    store_tile<LB, BN, BK>(sB, rb_e);
+    store_tile<BM, BK>(sA, ra_e);
+    store_tile<BN, BK>(sB, rb_e);
     __syncthreads();
     for (int u = 0; t < nsteps; ++t, ++u) {
       const int buf = u & 1;
@@ -397,11 +334,11 @@ __global__ __launch_bounds__(256) void k_gemm(LA0 la0, LB0 lb0, EPI epi, int M, 
         fetch_tile<LA, BM, BK>(la, m_blk, kb + (t + 1) * BK, ra_e, oa);
         fetch_tile<LB, BN, BK>(lb, n_blk, kb + (t + 1) * BK, rb_e, ob);
       }
-      mma_stage<BM, BN, BK, WM, WN, LA::kMajor, LB::kMajor>(sA + buf * SA::kElems, sB + buf * SB::kElems, ra0, rb0, kl,
+      mma_stage<BM, BN, BK, WM, WN>(sA + buf * SA::kElems, sB + buf * SB::kElems, ra0, rb0, kl,
                                                              acc);
       if (more) {
-        store_tile<LA, BM, BK>(sA + (buf ^ 1) * SA::kElems, ra_e);
-        store_tile<LB, BN, BK>(sB + (buf ^ 1) * SB::kElems, rb_e);
+        store_tile<BM, BK>(sA + (buf ^ 1) * SA::kElems, ra_e);
+        store_tile<BN, BK>(sB + (buf ^ 1) * SB::kElems, rb_e);
       }
       __syncthreads();
     }

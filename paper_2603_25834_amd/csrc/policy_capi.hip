@@ -15,6 +15,7 @@
 #include "policy_kernels.h"
 #include "conv_fused.h"
 #include "gemm_nt.h"
+#include "gemm_tn.h"
 #include "gru_kernels.h"
 
 using namespace aslam;
@@ -93,6 +94,35 @@ int slices_used(int64_t K, int64_t splits, int BK) {
   int64_t chunk = (K + splits - 1) / splits;
   chunk = (chunk + BK - 1) / BK * BK;
   return (int)((K + chunk - 1) / chunk);
+}
+
+// Slices of the rows for a weight gradient in tiles of T x T: the workgroups that are resident (two per CU of
+// the small tile, one of the large) take their stages' time, and the slices' partial sums cost as much as a stage
+// per 30 small tiles or 17 large ones (FC1's weight, GEMM and reduction, us: 9000 rows 74 (7 large slices) / 76 (6) /
+// 92 (4); 3000 rows 45 (1 small slice + 10) / 42 (2) / 37 (3) / 45 (4); 96 rows 19 (1) / 23 (3)).
+int weight_slices(int64_t rows, int T, int tiles, int64_t max_slices) {
+  const int slots = T == 256 ? 256 : 512, tiles_per_stage = T == 256 ? 17 : 30;
+  int best = 1;
+  int64_t best_cost = -1;
+  for (int s = 1; s <= max_slices; ++s) {
+    const int64_t rounds = ((int64_t)tiles * s + slots - 1) / slots;
+    const int64_t cost = tiles_per_stage * rounds * (gemm_tn::slice_rows(rows, s) / gemm_tn::kRows) + (int64_t)tiles * s;
+    if (best_cost < 0 || cost < best_cost) { best = s; best_cost = cost; }
+  }
+  return best;
+}
+
+// dst[n][k] += sum_m d[m][n] x[m][k].  256 x 256 tiles read FC1's large operand once, but leave the chip idle
+// where there are few of them or few rows (GEMM and reduction, us, small / large tiles: FC1's weight 19 / 28 at 96 rows,
+// 27 / 29 at 750, 37 / 43 at 3000, 81 / 74 at 9000; FC2's at 9000 rows 16 / 22, one of the GRU's 21 / 24).
+hipError_t weight_grad(aslam_policy* P, const gemm_tn::Operands& g, int64_t max_slices, float* dst, hipStream_t st) {
+  constexpr int kLargeTiles = 32, kLargeRows = 6144;
+  const int T = gemm_tn::tiles(g.N, g.K, 256) >= kLargeTiles && g.M >= kLargeRows ? 256 : 128;
+  const int S = weight_slices(g.M, T, gemm_tn::tiles(g.N, g.K, T), max_slices);
+  const hipError_t e = gemm_tn::run(g, P->part, T, S, st);
+  if (e != hipSuccess) return e;
+  const int64_t n = (int64_t)g.N * g.K;
+  return launch_reduce(P->part, gemm_tn::slices(g.M, S), n, dst, 0, n, st);
 }
 
 int64_t part_need(const aslam_policy* p) {
@@ -546,13 +576,7 @@ int aslam_policy_backward_rows(aslam_policy* P, const float* params, const int16
   PCHK(launch_reduce_heads(P->hpart, nb, params, o, grads, loss, P->cfg.c_value, P->cfg.c_entropy, st));
   float* part = P->part;
   // FC2 weight: dW2[out][in] = sum_b dz2[b][out] h1[b][in]
-  {
-    const int64_t S = splits_for(B, 256, kFc2Splits);
-    const int S_used = slices_used(B, S, 64);
-    PCHK((gemm::run<128, 128, 64, 2, 2>(LdBF16I{P->dz2, kHid, kHid, B}, LdBF16I{P->h1, kHid, kHid, B},
-                                       EpiPartial{part, kHid, (int64_t)kHid * kHid}, kHid, kHid, B, (int)S, st)));
-    PCHK(launch_reduce(part, S_used, (int64_t)kHid * kHid, grads + o.f2w, 0, (int64_t)kHid * kHid, st));
-  }
+  PCHK(weight_grad(P, gemm_tn::Operands{P->dz2, kHid, kHid, P->h1, kHid, kHid, B}, kFc2Splits, grads + o.f2w, st));
   // dh1 -> dz1 = (dz2 W2) * [h1 > 0]
   PCHK((gemm::run<128, 128, 64, 2, 2>(LdBF16K{P->dz2, kHid, B, kHid}, LdBF16K{P->w2t, kHid, kHid, kHid},
                                      EpiReluGradBF16{P->dz1, P->h1, kHid, kHid}, B, kHid, kHid, 1, st)));
@@ -574,13 +598,7 @@ int backward_fc1_encoder(aslam_policy* P, const float* params, const int16_t* cr
   PCHK(hipGetLastError());
   PCHK(launch_reduce(part, kBiasBlocks, kHid, grads + o.f1b, 0, kHid, st));
   // FC1 weight: dW1[out][k] = sum_b dz1[b][out] X[b][k]
-  {
-    const int64_t S = splits_balanced(B, 64, 2 * (int64_t)((o.k1 + 127) / 128), 512, kFc1Splits);
-    const int S_used = slices_used(B, S, 64);
-    PCHK((gemm::run<128, 128, 64, 2, 2>(LdBF16I{P->dz1, kHid, kHid, B}, LdBF16I{P->x, P->k1p, o.k1, B},
-                                       EpiPartial{part, o.k1, (int64_t)kHid * o.k1}, kHid, o.k1, B, (int)S, st)));
-    PCHK(launch_reduce(part, S_used, (int64_t)kHid * o.k1, grads + o.f1w, 0, (int64_t)kHid * o.k1, st));
-  }
+  PCHK(weight_grad(P, gemm_tn::Operands{P->dz1, kHid, kHid, P->x, P->k1p, o.k1, B}, kFc1Splits, grads + o.f1w, st));
   // dA2 -> dz2c = (dz1 W1[:, :8192]) * [a2 > 0]
   PCHK(gemm_nt::feature_grad(P->dz1, P->w1t, reinterpret_cast<const uint8_t*>(P->amask), P->dz2c, B, kFeat, st));
   // encoder: conv2 / conv1 weight and bias gradients in one pass over the minibatch
@@ -775,17 +793,8 @@ int aslam_policy_backward_seq(aslam_policy* P, const float* params, const int16_
   PCHK(launch_reduce_segs(part, (int)tiles, grads, ReduceSegs{{kGates, kGates, 0, 0}, {0, 0, 0, 0}, {o.gbi, o.gbh, 0, 0}},
                           2 * kGates, st));
   // GRU weights: dW_ih = sum_s dgi[s] h1[s]^T, dW_hh = sum_s dgh[s] hp[s]^T
-  {
-    const int64_t S2 = splits_for(B, 256, kFc2Splits);
-    const int S2u = slices_used(B, S2, 64);
-    const int64_t n = (int64_t)kGates * kHid;
-    PCHK((gemm::run<128, 128, 64, 2, 2>(LdBF16I{dgi, kGates, kGates, B}, LdBF16I{P->h1, kHid, kHid, B},
-                                       EpiPartial{part, kHid, n}, kGates, kHid, B, (int)S2, st)));
-    PCHK(launch_reduce(part, S2u, n, grads + o.gih, 0, n, st));
-    PCHK((gemm::run<128, 128, 64, 2, 2>(LdBF16I{dgh, kGates, kGates, B}, LdBF16I{P->hp_bf, kHid, kHid, B},
-                                       EpiPartial{part, kHid, n}, kGates, kHid, B, (int)S2, st)));
-    PCHK(launch_reduce(part, S2u, n, grads + o.ghh, 0, n, st));
-  }
+  PCHK(weight_grad(P, gemm_tn::Operands{dgi, kGates, kGates, P->h1, kHid, kHid, B}, kFc2Splits, grads + o.gih, st));
+  PCHK(weight_grad(P, gemm_tn::Operands{dgh, kGates, kGates, P->hp_bf, kHid, kHid, B}, kFc2Splits, grads + o.ghh, st));
   // FC1 output gradient: dz1 = (dgi W_ih) * [h1 > 0]
   PCHK((gemm::run<128, 128, 64, 2, 2>(LdBF16K{dgi, kGates, B, kGates}, LdBF16K{P->wiht, kGates, kHid, kGates},
                                      EpiReluGradBF16{P->dz1, P->h1, kHid, kHid}, B, kHid, kGates, 1, st)));

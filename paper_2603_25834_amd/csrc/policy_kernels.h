@@ -85,7 +85,6 @@ __device__ __forceinline__ uint4 pack8(const uint16_t v[8]) {
 
 // BF16 matrix, element (i, k) at p[i*ld + k]; contiguous along k.
 struct LdBF16K {
-  static constexpr bool kMajor = true;
   const uint16_t* p; int64_t ld; int rows, cols;
   __device__ uint4 fetch(int i, int k) const {
     if (i >= rows || k >= cols) return make_uint4(0u, 0u, 0u, 0u);
@@ -94,21 +93,6 @@ struct LdBF16K {
     uint16_t v[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) v[j] = (k + j < cols) ? q[j] : (uint16_t)0;
-    return pack8(v);
-  }
-};
-
-// BF16 matrix, element (i, k) at p[k*ld + i]; contiguous along i.
-struct LdBF16I {
-  static constexpr bool kMajor = false;
-  const uint16_t* p; int64_t ld; int rows, cols;
-  __device__ uint4 fetch(int i, int k) const {
-    if (i >= rows || k >= cols) return make_uint4(0u, 0u, 0u, 0u);
-    const uint16_t* q = p + (int64_t)k * ld + i;
-    if (i + 8 <= rows && ((reinterpret_cast<uintptr_t>(q) & 15) == 0)) return *reinterpret_cast<const uint4*>(q);
-    uint16_t v[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = (i + j < rows) ? q[j] : (uint16_t)0;
     return pack8(v);
   }
 };

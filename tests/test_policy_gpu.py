@@ -196,16 +196,20 @@ def test_split_backward_matches_exact_fp64_gradient(B):
     assert np.allclose(loss.cpu().numpy()[1:], terms, rtol=1e-4, atol=1e-5)
 
 
-@pytest.mark.parametrize("b,pieces", [(1, 8), (129, 8), (257, 4), (513, 2)])
-def test_split_gradient_is_the_mean_of_its_pieces(b, pieces):
+@pytest.mark.parametrize("b,pieces,rays", [(1, 8, R), (129, 8, R), (257, 4, R), (513, 2, R), (4097, 2, R), (65, 2, 257)])
+def test_split_gradient_is_the_mean_of_its_pieces(b, pieces, rays):
     """The gradient of b * pieces rows against the mean of the pieces' gradients: row counts around the edges of
-    the 128-row tiles and of the feature gradient's workgroup widths (at most 256 rows, at most 512, more).  The
+    the 128-row tiles, of the feature gradient's workgroup widths (at most 256 rows, at most 512, more) and of the
+    weight gradients' tiles (32-row stages, large tiles from 6144 rows), and FC1 rows that are no multiple of four.  The
     pieces' 1 / b is a power of two times the whole's, so every BF16 rounding is the same, and what differs is
     the order of FP32 sums: 2e-7 relative, and at most a ReLU sign of a unit within that of zero, one of the
     128 b * pieces active units of FC1, whose share of a gradient that cancels threefold is 3 / sqrt(128 * 1026)
     = 8e-3.  Bound 1e-2 per tensor (relative L2); a lost row of a 129-row piece would be 1 / sqrt(129) = 9e-2."""
-    theta, t = _case(b * pieces, 5)
-    pol, params, dev = _gpu(theta, t, precision=1)
+    from paper_2603_25834_amd.policy import Policy
+    theta = synth.init_policy_params(rays, 5)
+    pol = Policy(rays, max_batch=b * pieces, precision=1)
+    dev = {k: torch.from_numpy(v).cuda() for k, v in synth.policy_batch(b * pieces, rays, 5).items()}
+    params = torch.from_numpy(theta).cuda()
 
     def grad(part):
         g = torch.zeros_like(params)
@@ -217,7 +221,11 @@ def test_split_gradient_is_the_mean_of_its_pieces(b, pieces):
     say(f"[policy] {pieces} pieces of {b} rows")
     whole = grad(dev)
     mean = sum(grad({k: v[i * b:(i + 1) * b] for k, v in dev.items()}) for i in range(pieces)) / pieces
-    errs = _tensor_errors(whole, mean)
+    errs, at = {}, 0
+    for name, shp in PR.PolicyShape(n_scan=rays).param_layout():
+        n = int(np.prod(shp))
+        errs[name] = np.linalg.norm((whole - mean)[at:at + n]) / max(np.linalg.norm(mean[at:at + n]), 1e-30)
+        at += n
     say("[policy] whole against pieces: " + " ".join(f"{k}={v:.1e}" for k, v in errs.items()))
     for k, v in errs.items():
         assert v < 1e-2, (k, v)
