@@ -42,8 +42,9 @@ using gemm::f32x4;
 constexpr int kBlk = 33;                 // crop 2x2 blocks per row and column, plus the zero block -1
 constexpr int kCropLds = kBlk * kBlk * 4;            // BF16 elements
 
-__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
-  return (uint32_t)f2bf(lo) | ((uint32_t)f2bf(hi) << 16);
+__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {   // one conversion of two
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)lo, (__bf16)hi});
 }
 
 // hi = bf16(v), or with LO the remainder bf16(v - hi).
@@ -150,16 +151,6 @@ __device__ __forceinline__ void store_crop(const CropRegs<NT>& r, uint16_t* s_cr
           (uint32_t)bf16_part<LO>(lo) | ((uint32_t)bf16_part<LO>(hi) << 16);
     }
   }
-}
-
-// conv1 window operand of pixel px (lanes with lg >= 2 supply zeros) from a space-to-depth crop.
-__device__ __forceinline__ uint4 conv1_window(const uint16_t* s_crop, int px, int lg) {
-  const int y = px >> 5, x = px & 31;
-  if (lg >= 2) return make_uint4(0u, 0u, 0u, 0u);
-  const uint16_t* q = s_crop + ((y + lg) * kBlk + x) * 4;
-  const uint2 a = *reinterpret_cast<const uint2*>(q);
-  const uint2 c = *reinterpret_cast<const uint2*>(q + 4);
-  return make_uint4(a.x, a.y, c.x, c.y);
 }
 
 // Four ReLU outputs packed as BF16 (hi parts, or with LO the lo parts).
@@ -414,51 +405,47 @@ namespace pol {
 //   dz1 = bf16(da1) * [a1 > 0]
 //   dW1[co][tap]     += sum_px dz1[co][px] in[pixel(px, tap)]
 //   db1 += sum dz1,  db2 += sum dz2.
-// The workgroup (8 waves) keeps its gradient sums over all its samples and
+// The workgroup (four waves) keeps its gradient sums over all its samples and
 // writes them once, as partials [gridDim.x][kConvPart], reduced afterwards in
 // a fixed order.
 //
+// What bounds it: a sample is a chain of three phases (stage the crop and dz2; conv1; the products) with a
+// barrier behind each, so a CU holds two workgroups that are at different places of it (77 KB of LDS; 68 in
+// BF16), and the vector instructions: the operands come from LDS in the layout that they arrive in, transposed by the
+// read where the product contracts over the other index (ds_read_b64_tr_b16: of a group's 16 lanes, lane
+// 4 r + c reads four elements of row r, lane i receives element i of the four rows), and the bias sums are
+// products with ones.  One workgroup of eight waves with transposed copies in LDS (three shifted planes of a1,
+// five of the crop, two of dz2: 127 KB, 560 vector instructions a wave and sample) took 187 us on 9000
+// split-precision samples, 267 on 16384 BF16 ones and 36 on 96; this takes 111, 171 and 11.
+//
 // LDS layouts (BF16):
-//   crop   space-to-depth, as in the forward kernel (conv1's operand);
-//   inq    the crop again as five column-residue planes, inq[p][y+1][X] =
-//          in[y][4X + p] for p < 4 and inq[4][y+1][X] = in[y][4X - 1] (row 0 and
-//          inq[4][.][0] zero): the operand of the dW1 product, where a lane
-//          needs the input under one tap at four pixels 2 apart, i.e. four
-//          input columns 4 apart -- four consecutive elements of one plane;
-//   a1x    [kx][ci][y+1][ox] = a1[ci][y][2 ox + kx - 1] (channels padded by 8
-//          elements against bank conflicts): for a fixed tap, eight
-//          consecutive output columns are eight consecutive elements, so the
-//          im2col operand of the dW2 product is one 16-byte read; y = -1 and
-//          x = -1 are zero;
-//   dzT    [co][pos], rows padded to 264 elements: the dW2 operand is one
-//          16-byte read (eight positions of one channel);
-//   dz     [oy][ox][co] over 17 x 17 positions (row and column 16 zero),
-//          positions padded to 40 elements so that eight lanes' 16-byte
-//          accesses cover all banks: the operand of the input-gradient
-//          product (eight channels of one position per read), transposed
-//          from dzT once per sample.
+//   crop   cell (y, x) at row y + 2 (rows of 128 bytes, rows 0 and 1 zero), column x of copy A and column x + 2
+//          of copy B (its columns 0 and 1 zero): four consecutive cells from any even column are eight aligned
+//          bytes of one copy.  The 64-byte halves of row r are swapped when r / 2 is odd, and B starts 128 bytes
+//          past A's last row, so that conv1's and dW1's reads of two row pairs and both copies cover all banks.
+//   a1     pixel (y, x), 16 channels of 32 bytes, at row y + 1 (row 0 zero): the even columns, 48 bytes of zeros,
+//          the odd columns: a product's reads of 8 positions along x are 256 contiguous bytes, and conv1's stores
+//          of 16 pixels' channel halves cover all banks.
+//   dz     [co][pos], rows of 512 bytes; the 32-byte blocks oy of a channel's row at oy ^ f(co), f = co % 4 +
+//          4 (co / 8 % 2): the transposing read of channels 8 g .. 8 g + 3 covers all banks.
+// dW2: K = 32 positions, k = 8 lg + 4 h + r <-> (oy = 4 wave + 2 s + h, ox = 4 lg + r), s the wave's k-step.
 // da1 is computed one sub-pixel phase (y % 2, x % 2) at a time: the input
 // pixels of a phase form a 16 x 16 grid that receives taps ky = 1 (y even) or
 // ky in {0, 2} (y odd), likewise kx, each from the output position
-// (qy + (py + 1 - ky) / 2, qx + (px + 1 - kx) / 2).  K = 32 channels per tap.
+// (qy + (py + 1 - ky) / 2, qx + (px + 1 - kx) / 2).  K = 32 channels per tap.  The operands of the positions
+// one to the right are those of the positions moved by a lane.
 // dz1 = bf16(da1) * [a1 > 0] never leaves registers: a lane holds channel
-// lr at the pixels 4 lg + i of the phase rows qy = wave and wave + 8, and
-// those eight values are exactly its A operand of one dW1 MFMA (K = the
-// wave's 32 pixels of the phase), so dW1 is accumulated right after each
-// phase's two da1 products.
+// lr at the pixels 4 lg + i of the phase rows qy = wave + 4 rr, and
+// those of two rows are exactly its A operand of one dW1 MFMA, so dW1 is accumulated right after each
+// phase's da1 products.  dW1's columns are 4 ky + kx + 1.
 constexpr int kConvPartW2 = kC2 * 144;          // [co][tap*16 + ci]
 constexpr int kConvPartW1 = kC1 * 16;           // [co][tap], taps padded to 16
 constexpr int kConvPart = kConvPartW2 + kConvPartW1 + kC1 + kC2;
-constexpr int kA1xRow = 16, kA1xRows = 33;
-constexpr int kA1xCi = kA1xRows * kA1xRow + 8;         // one channel's rows, padded against bank conflicts
-constexpr int kA1xLds = 3 * kC1 * kA1xCi;               // BF16 elements
-constexpr int kDzRow = 256 + 8;
-constexpr int kDzLds = kC2 * kDzRow;
-constexpr int kDzSide = 17, kDzPos = 40;
-constexpr int kDzPLds = kDzSide * kDzSide * kDzPos;
-constexpr int kInqRow = kCrop / 4, kInqPlane = (kCrop + 1) * kInqRow;   // 16 columns, 65 rows (row 0 zero)
-constexpr int kInqLds = 5 * kInqPlane;
-constexpr int kBwdThreads = 512;
+constexpr int kBwdThreads = 256;
+constexpr int kCropRow = 2 * kCrop, kCropB = (kCrop + 3) * kCropRow;   // bytes: a row, copy B
+constexpr int kCropBytes = kCropB + (kCrop + 3) * kCropRow;            // (a row past the end for dW1's unused columns)
+constexpr int kA1Pix = 2 * kC1, kA1Odd = 17 * kA1Pix + 16, kA1RowB = kA1Odd + 16 * kA1Pix, kA1Bytes = 33 * kA1RowB;
+constexpr int kDzRowB = 512, kDzBytes = kC2 * kDzRowB;
 
 struct PhaseTaps {
   int n;                 // taps of the phase (1, 2 or 4)
@@ -521,225 +508,241 @@ __global__ __launch_bounds__(64 * kConvPhaseFrags) void k_conv_bwd_frags(const f
   conv_bwd_frag_elem(prm, o, frag, threadIdx.x);
 }
 
+typedef short short4_t __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) short4_t lds_short4;
+
+__device__ __forceinline__ uint2 read_tr(const unsigned char* p) {
+  return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4*)p));
+}
+
+// Each lane of 16 gets the next one's value, the last one zero.
+__device__ __forceinline__ uint32_t next_lane(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x101, 0xf, 0xf, true);
+}
+
+// Two gradients as BF16 where the two activations a (BF16, not negative) are not zero.
+__device__ __forceinline__ uint32_t masked2(uint32_t a, float lo, float hi) {
+  // two 16-bit operations each (in C++ they become a compare and a select per value); the matrix cores must
+  // not read an asm's result directly, the wait that takes is the compiler's to insert
+  uint32_t on, mask;
+  asm("v_pk_min_u16 %0, %1, %2" : "=v"(on) : "v"(a & 0x7fff7fffu), "v"(0x00010001u));
+  asm("v_pk_mul_lo_u16 %0, %1, %2" : "=v"(mask) : "v"(on), "v"(0xffffffffu));
+  return mask & pack_bf16x2(lo, hi);
+}
+
 // PREC: conv1 is recomputed with split operands (the crop's lo part staged beside it), so its ReLU
 // mask is the one the split forward applied; the products of the backward stay BF16.
 template <bool PREC>
-__global__ __launch_bounds__(kBwdThreads) void k_conv_bwd(const float* __restrict__ prm, Offsets o,
-                                                          const uint4* __restrict__ frag,
-                                                          const int16_t* __restrict__ crop,
-                                                          const int32_t* __restrict__ rows,
-                                                          const uint16_t* __restrict__ dz2c, int B,
-                                                          float* __restrict__ part) {
-  __shared__ __align__(16) uint16_t s_crop[(PREC ? 2 : 1) * kCropLds];
-  uint16_t* const s_cropl = s_crop + (PREC ? kCropLds : 0);
-  __shared__ __align__(16) uint16_t s_a1x[kA1xLds];
-  __shared__ __align__(16) uint16_t s_dz[kDzLds];
-  __shared__ __align__(16) uint16_t s_dzp[kDzPLds];
-  __shared__ __align__(16) uint16_t s_inq[kInqLds];
-  __shared__ float s_red[8][kC1 * 16];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, lr = lane & 15, lg = lane >> 4;
+__global__ __launch_bounds__(kBwdThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_conv_bwd(
+    const float* __restrict__ prm, Offsets o, const uint4* __restrict__ frag, const int16_t* __restrict__ crop,
+    const int32_t* __restrict__ rows, const uint16_t* __restrict__ dz2c, int B, float* __restrict__ part) {
+  __shared__ __align__(256) unsigned char s_crop[kCropBytes];
+  __shared__ __align__(256) unsigned char s_a1[kA1Bytes];
+  __shared__ __align__(256) unsigned char s_dz[kDzBytes];
+  __shared__ __align__(16) uint16_t s_cropl[PREC ? (kCropLds + 7) / 8 * 8 : 8];   // space-to-depth, with its border
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, lr = lane & 15, lg = lane >> 4;
   {
     uint4* z = reinterpret_cast<uint4*>(s_crop);
-    for (int i = threadIdx.x; i < (PREC ? 2 : 1) * kCropLds / 8; i += kBwdThreads) z[i] = make_uint4(0u, 0u, 0u, 0u);
-    z = reinterpret_cast<uint4*>(s_a1x);
-    for (int i = threadIdx.x; i < kA1xLds / 8; i += kBwdThreads) z[i] = make_uint4(0u, 0u, 0u, 0u);
-    z = reinterpret_cast<uint4*>(s_dzp);
-    for (int i = threadIdx.x; i < kDzPLds / 8; i += kBwdThreads) z[i] = make_uint4(0u, 0u, 0u, 0u);
-    z = reinterpret_cast<uint4*>(s_inq);
-    for (int i = threadIdx.x; i < kInqLds / 8; i += kBwdThreads) z[i] = make_uint4(0u, 0u, 0u, 0u);
+    for (int i = threadIdx.x; i < kCropBytes / 16; i += kBwdThreads) z[i] = make_uint4(0u, 0u, 0u, 0u);
+    z = reinterpret_cast<uint4*>(s_a1);
+    for (int i = threadIdx.x; i < kA1Bytes / 16; i += kBwdThreads) z[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (PREC) {
+      z = reinterpret_cast<uint4*>(s_cropl);
+      for (int i = threadIdx.x; i < (kCropLds + 7) / 8; i += kBwdThreads) z[i] = make_uint4(0u, 0u, 0u, 0u);
+    }
   }
   // registers that live for the whole workgroup
-  // conv1's weights as the B operand: the same values as the forward's A fragment (W'[k][co] at co = lane % 16)
-  const bf16x8 w1f = __builtin_bit_cast(bf16x8, frag[lane]);
-  const bf16x8 w1fl = PREC ? __builtin_bit_cast(bf16x8, frag[64 * kConvLoFrag + lane]) : w1f;
-  const float b1c = prm[o.c1b + lr];
-  // phase weights: this wave's qy rows are {wave, wave + 8}; all four phases, 9 k-steps
+  // conv1's weights with k in the order of the window's reads, 4 dy + 2 c + dx (the sum is the same, bit for bit)
+  auto w1_frag = [&](int f) {
+    const uint4 w = frag[64 * f + lane];
+    return __builtin_bit_cast(bf16x8, make_uint4(w.x, w.z, w.y, w.w));
+  };
+  const bf16x8 w1f = w1_frag(0), w1fl = PREC ? w1_frag(kConvLoFrag) : w1f;
+  float b1[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) b1[i] = prm[o.c1b + 4 * lg + i];
   bf16x8 wph[kConvPhaseFrags];
 #pragma unroll
   for (int q = 0; q < kConvPhaseFrags; ++q) wph[q] = __builtin_bit_cast(bf16x8, frag[64 * (kConvFrags + q) + lane]);
-  // accumulators: every dW2 tile (nt = tap, mt = output-channel half) over this wave's k-step
-  // (positions 32 wave .. 32 wave + 31) of every sample
-  f32x4 gw2[9][2];
+  const bf16x8 ones = __builtin_bit_cast(bf16x8, make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u));
+  const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
+  // sums over the workgroup's samples: dW2 [tap][output-channel half], dW1, the biases (the same in every column)
+  f32x4 gw2[9][2], gw1 = zero4, gb1 = zero4, gb2[2] = {zero4, zero4};
 #pragma unroll
   for (int a = 0; a < 9; ++a)
 #pragma unroll
-    for (int c = 0; c < 2; ++c) gw2[a][c] = f32x4{0.f, 0.f, 0.f, 0.f};
-  f32x4 gw1 = {0.f, 0.f, 0.f, 0.f};
-  float gb1 = 0.0f, gb2[2] = {0.f, 0.f};
+    for (int c = 0; c < 2; ++c) gw2[a][c] = zero4;
+  f32x4 c0 = zero4;   // in registers of its own: as a constant it is written before each product that starts from it
+  asm("" : "+v"(c0));
   // the sample's crop and dz2 in registers; the next sample's are loaded while this one is processed
   CropRegs<kBwdThreads> cr;
-  uint4 dzr[2];
+  gemm::u32x4 dzr[4];
   auto load_sample = [&](int bb) {
     load_crop<kBwdThreads>(crop + (rows ? (int64_t)rows[bb] : (int64_t)bb) * kCrop * kCrop, cr);
-    const uint4* src = reinterpret_cast<const uint4*>(dz2c + (int64_t)bb * kFeat);
-    dzr[0] = src[threadIdx.x];
-    dzr[1] = src[threadIdx.x + kBwdThreads];
+    const gemm::u32x4* src = reinterpret_cast<const gemm::u32x4*>(dz2c + (int64_t)bb * kFeat);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) dzr[i] = src[threadIdx.x + i * kBwdThreads];
   };
+  // staging: the thread's crop vectors are eight cells of rows y and y + 32, its dz2 vectors eight positions
+  // (half a block) of channels co, co + 8, ..
+  const int q8 = threadIdx.x & 7, row = (int)(threadIdx.x >> 3) + 2, swap = ((row >> 1) & 1) * 64;
+  unsigned char* const st_a = s_crop + row * kCropRow + ((16 * q8) ^ swap);
+  unsigned char* const st_b = s_crop + kCropB + row * kCropRow;
+  const int co = threadIdx.x >> 5;   // 0 .. 7
+  const int st_dz = co * kDzRowB + (((((int)threadIdx.x & 31) >> 1) ^ (co & 3)) << 5) + 16 * (threadIdx.x & 1);
+  // conv1's windows: odd columns from copy A, even ones from copy B; lanes with lg >= 2 read what lg - 2 reads
+  // (finite values; their weights are zero)
+  const int l1 = lg & 1;
+  const unsigned char* const win = s_crop + ((lr & 1) ? 4 * lr - 4 : kCropB + 4 * lr) + (16 * wave + 2 * l1) * kCropRow;
+  const unsigned char* const win2[2] = {win + 64 * l1, win + 64 * (l1 ^ 1)};
+  const uint16_t* const winl = s_cropl + ((8 * wave + l1) * kBlk + lr) * 4;
+  unsigned char* const st_a1 = s_a1 + (8 * wave + 1) * kA1RowB + (lr & 1) * kA1Odd + (lr >> 1) * kA1Pix + 8 * lg;
+  // transposing reads: this lane's row (lr / 4) and four elements (lr % 4)
+  const int tr = lr >> 2, tc = lr & 3;
+  const unsigned char* const px0 = s_a1 + (4 * lg + tr) * kA1Pix + 8 * tc;           // positions 4 lg + r along x
+  const uint32_t dzt = (8 * lg + tr) * kDzRowB + ((tr | (l1 << 2)) << 5) + 8 * tc;   // channels 8 lg + r, block ^ oy
+  const uint32_t dza = lr * kDzRowB + (((lr & 3) | ((lr >> 3) << 2)) << 5) + 8 * lg;   // channel lr, positions 4 lg ..
+  const unsigned char* in2[2];   // dW1's cells at phase row py: rows 4 wave + ky - 1 (+ 2 py), columns 16 lg + 4 r ..
+#pragma unroll
+  for (int py = 0; py < 2; ++py)
+    in2[py] = s_crop + (4 * wave + tc + 1 + 2 * py) * kCropRow + ((32 * lg + 8 * tr) ^ (64 * (py ^ ((tc + 1) >> 1 & 1))));
   if (blockIdx.x < B) load_sample(blockIdx.x);
   __syncthreads();
 
   for (int b = blockIdx.x; b < B; b += gridDim.x) {
-    // ---- stage the crop and dz2 ([co][pos]); db2 from the same values
-    store_crop<kBwdThreads>(cr, s_crop);
+    // ---- stage the crop and dz2
     if (PREC) store_crop<kBwdThreads, true>(cr, s_cropl);
-    {
-      // the thread's eight cells: row y = v / 8, columns 8 (v % 8) + j, i.e. X = 2 (v % 8) + (j >= 4)
-      // and residue j % 4
-      static_assert(CropRegs<kBwdThreads>::kPer == 1, "one crop vector per thread");
-      const int v = threadIdx.x, y = v >> 3, X0 = 2 * (v & 7);
-      const int32_t w[4] = {cr.v[0].x, cr.v[0].y, cr.v[0].z, cr.v[0].w};
-      uint16_t c[8];
 #pragma unroll
-      for (int j = 0; j < 8; ++j)
-        c[j] = f2bf((float)(int16_t)(w[j >> 1] >> ((j & 1) * 16)) * (1.0f / 256.0f));
-      uint16_t* rowp = s_inq + (y + 1) * kInqRow + X0;
+    for (int i = 0; i < 2; ++i) {
+      const int32_t w[4] = {cr.v[i].x, cr.v[i].y, cr.v[i].z, cr.v[i].w};
+      uint32_t c[4];
 #pragma unroll
-      for (int p = 0; p < 4; ++p)
-        *reinterpret_cast<uint32_t*>(rowp + p * kInqPlane) = (uint32_t)c[p] | ((uint32_t)c[4 + p] << 16);
-      rowp[4 * kInqPlane + 1] = c[3];
-      if (X0 + 2 < kInqRow) rowp[4 * kInqPlane + 2] = c[7];
+      for (int j = 0; j < 4; ++j)
+        c[j] = pack_bf16x2((float)(int16_t)(w[j] & 0xffff) * (1.0f / 256.0f), (float)(w[j] >> 16) * (1.0f / 256.0f));
+      const int at = i * 32 * kCropRow;
+      *reinterpret_cast<uint4*>(st_a + at) = make_uint4(c[0], c[1], c[2], c[3]);
+      *reinterpret_cast<uint32_t*>(st_b + at + ((16 * q8 + 4) ^ swap)) = c[0];
+      *reinterpret_cast<uint2*>(st_b + at + ((16 * q8 + 8) ^ swap)) = make_uint2(c[1], c[2]);
+      if (q8 < 7) *reinterpret_cast<uint32_t*>(st_b + at + ((16 * q8 + 16) ^ swap)) = c[3];
     }
-    {
 #pragma unroll
-      for (int r = 0; r < 2; ++r) {
-        const int v = threadIdx.x + r * kBwdThreads;   // vector of 8 positions of channel co
-        const int co = v >> 5, p0 = (v & 31) * 8;
-        const uint4 u = dzr[r];
-        *reinterpret_cast<uint4*>(s_dz + co * kDzRow + p0) = u;
-        float e[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        add_bf16x8(e, u);
-        gb2[r] += ((e[0] + e[1]) + (e[2] + e[3])) + ((e[4] + e[5]) + (e[6] + e[7]));
-      }
-    }
+    for (int i = 0; i < 4; ++i)   // channel co + 8 i: block bit 2 flips with i
+      *reinterpret_cast<gemm::u32x4*>(s_dz + ((st_dz ^ ((i & 1) * 128)) + i * 8 * kDzRowB)) = dzr[i];
     __syncthreads();
     if (b + (int)gridDim.x < B) load_sample(b + gridDim.x);
-    // ---- conv1 recompute: C[px][co], lane gets pixels 16 t + 4 lg + i of channel lr; the wave's
-    // eight tiles t = wave + 8 m are taken four at a time so that their operand reads overlap
+    // ---- conv1 recompute: C'[co][px], the wave's tile j the 16 pixels of row y = 8 wave + j / 2 from column
+    // 16 (j % 2), four tiles at a time so that their operand reads overlap
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      uint4 u[4], ul[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int t = wave + 8 * (4 * h + i);
-        u[i] = conv1_window(s_crop, t * 16 + lr, lg);
-        if (PREC) ul[i] = conv1_window(s_cropl, t * 16 + lr, lg);
-      }
+    for (int j0 = 0; j0 < 16; j0 += 4) {
+      bf16x8 u[4], ul[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int t = wave + 8 * (4 * h + i);
-        f32x4 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, u[i]), w1f,
-                                                           f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+        const int j = j0 + i;
+        // bit 6 of the column is (j ^ l1 ^ j / 2) % 2
+        const unsigned char* q = win2[(j ^ (j >> 1)) & 1] + (j >> 1) * 2 * kCropRow;
+        const uint2 a = *reinterpret_cast<const uint2*>(q), c = *reinterpret_cast<const uint2*>(q + kCropRow);
+        u[i] = __builtin_bit_cast(bf16x8, make_uint4(a.x, a.y, c.x, c.y));
         if (PREC) {
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ul[i]), w1f, acc, 0, 0, 0);
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, u[i]), w1fl, acc, 0, 0, 0);
+          const uint16_t* ql = winl + ((j >> 1) * kBlk + 16 * (j & 1)) * 4;
+          const uint2 e = *reinterpret_cast<const uint2*>(ql), f = *reinterpret_cast<const uint2*>(ql + 4);
+          ul[i] = __builtin_bit_cast(bf16x8, make_uint4(e.x, f.x, e.y, f.y));
         }
-        const int px0 = t * 16 + 4 * lg, y = px0 >> 5, x0 = px0 & 31;   // x0 = 0 mod 4
-        uint16_t hv[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) hv[e] = f2bf(fmaxf(acc[e] + b1c, 0.0f));
-        uint16_t* row = s_a1x + lr * kA1xCi + (y + 1) * kA1xRow;    // kx plane 0
-        const int plane = kC1 * kA1xCi;
-        // even x -> kx = 1 at ox = x / 2; odd x -> kx = 0 at (x + 1) / 2 and kx = 2 at (x - 1) / 2
-        *reinterpret_cast<uint32_t*>(row + plane + (x0 >> 1)) = (uint32_t)hv[0] | ((uint32_t)hv[2] << 16);
-        *reinterpret_cast<uint32_t*>(row + 2 * plane + (x0 >> 1)) = (uint32_t)hv[1] | ((uint32_t)hv[3] << 16);
-        row[(x0 >> 1) + 1] = hv[1];
-        if ((x0 >> 1) + 2 < kA1xRow) row[(x0 >> 1) + 2] = hv[3];
       }
-    }
-    // dz2 [co][pos] -> [pos][co]: thread takes position v % 256 and channels 8 (v / 256) .. + 7
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const int v = threadIdx.x + r * kBwdThreads;
-      const int pos = v & 255, cg = v >> 8;
-      uint16_t g[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) g[e] = s_dz[(8 * cg + e) * kDzRow + pos];
-      *reinterpret_cast<uint4*>(s_dzp + ((pos >> 4) * kDzSide + (pos & 15)) * kDzPos + 8 * cg) = pack8(g);
+      for (int i = 0; i < 4; ++i) {
+        const int j = j0 + i;
+        f32x4 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1f, u[i], c0, 0, 0, 0);
+        if (PREC) {
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1f, ul[i], acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1fl, u[i], acc, 0, 0, 0);
+        }
+        *reinterpret_cast<uint2*>(st_a1 + (j >> 1) * kA1RowB + (j & 1) * 8 * kA1Pix) = pack_relu4<false>(acc, b1);
+      }
     }
     __syncthreads();
-    // ---- dW2: the wave's k-step (positions p0 = 32 wave + 8 lg .. + 7 of the lane) for all nine taps;
-    // the dz operand is read once and serves every tap
-    {
-      const int p0 = 32 * wave + 8 * lg, oy = p0 >> 4, ox0 = p0 & 15;
+    // ---- dW2: the wave's two k-steps of 32 positions for all nine taps; db2
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
       bf16x8 af[2];
 #pragma unroll
-      for (int mt = 0; mt < 2; ++mt)
-        af[mt] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(s_dz + (16 * mt + lr) * kDzRow + p0));
+      for (int mt = 0; mt < 2; ++mt) {
+        uint2 v[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          v[h] = *reinterpret_cast<const uint2*>(s_dz + (dza ^ (uint32_t)((4 * wave + 2 * s + h) << 5)) + mt * 16 * kDzRowB);
+        af[mt] = __builtin_bit_cast(bf16x8, make_uint4(v[0].x, v[0].y, v[1].x, v[1].y));
+        gb2[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[mt], ones, gb2[mt], 0, 0, 0);
+      }
 #pragma unroll
       for (int nt = 0; nt < 9; ++nt) {
         const int ky = nt / 3, kx = nt % 3;
-        const int yy = 2 * oy + ky - 1;
-        const bf16x8 bf = __builtin_bit_cast(
-            bf16x8, *reinterpret_cast<const uint4*>(s_a1x + (kx * kC1 + lr) * kA1xCi + (yy + 1) * kA1xRow + ox0));
+        uint2 v[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)   // row 2 oy + ky - 1, columns 2 ox + kx - 1
+          v[h] = read_tr(px0 + (8 * wave + 4 * s + 2 * h + ky) * kA1RowB + (kx == 1 ? 0 : kx == 2 ? kA1Odd : kA1Odd - kA1Pix));
+        const bf16x8 bf = __builtin_bit_cast(bf16x8, make_uint4(v[0].x, v[0].y, v[1].x, v[1].y));
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt)
           gw2[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[mt], bf, gw2[nt][mt], 0, 0, 0);
       }
     }
-    // ---- da1 by phases -> dz1 (masked, BF16, in registers); db1; dW1 per phase
-    {
+    // ---- da1 by phases -> dz1 (masked, BF16, in registers); db1; dW1.  Two of the wave's rows qy = wave + 4 rr
+    // at a time
+#pragma unroll
+    for (int r2 = 0; r2 < 2; ++r2) {
+      bf16x8 pos[2][2][2];   // [row of the pair][dy][dx]
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int dy = 0; dy < 2; ++dy) {
+          const int oy = wave + 4 * (2 * r2 + k) + dy;
+          uint4 v = make_uint4(0u, 0u, 0u, 0u);
+          if (oy < kA2) {
+            const unsigned char* q = s_dz + (dzt ^ (uint32_t)(oy << 5));
+            const uint2 a = read_tr(q), c = read_tr(q + 4 * kDzRowB);
+            v = make_uint4(a.x, a.y, c.x, c.y);
+          }
+          pos[k][dy][0] = __builtin_bit_cast(bf16x8, v);
+          pos[k][dy][1] = __builtin_bit_cast(bf16x8, make_uint4(next_lane(v.x), next_lane(v.y), next_lane(v.z), next_lane(v.w)));
+        }
       int q = 0;
 #pragma unroll
       for (int ph = 0; ph < 4; ++ph) {
         const int py = ph >> 1, px = ph & 1;
         const PhaseTaps t = phase_taps(py, px);
-        uint32_t dpk[4];
+        uint2 d[2], in[2];
 #pragma unroll
-        for (int rr = 0; rr < 2; ++rr) {
-          const int qy = wave + 8 * rr;
-          f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int k = 0; k < 2; ++k) {
+          const int rr = 2 * r2 + k;
+          f32x4 acc = c0;
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
             if (j >= t.n) break;
-            const int oy = qy + t.dy[j], ox = lr + t.dx[j];
-            const bf16x8 af = __builtin_bit_cast(
-                bf16x8, *reinterpret_cast<const uint4*>(s_dzp + (oy * kDzSide + ox) * kDzPos + 8 * lg));
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, wph[q + j], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pos[k][t.dy[j]][t.dx[j]], wph[q + j], acc, 0, 0, 0);
           }
           // lane: input pixels (2 qy + py, 2 (4 lg + i) + px), channel lr
-          const int y = 2 * qy + py;
-          const uint2 m = *reinterpret_cast<const uint2*>(
-              s_a1x + ((1 + px) * kC1 + lr) * kA1xCi + (y + 1) * kA1xRow + 4 * lg);
-          const uint32_t mw[2] = {m.x, m.y};
-          uint16_t d[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const uint16_t a = (uint16_t)(mw[i >> 1] >> ((i & 1) * 16));
-            d[i] = bf2f(a) > 0.0f ? f2bf(acc[i]) : (uint16_t)0;
-            gb1 += bf2f(d[i]);
-          }
-          dpk[2 * rr] = (uint32_t)d[0] | ((uint32_t)d[1] << 16);
-          dpk[2 * rr + 1] = (uint32_t)d[2] | ((uint32_t)d[3] << 16);
+          const uint2 m = read_tr(px0 + (2 * wave + 8 * rr + py + 1) * kA1RowB + px * kA1Odd);
+          d[k] = make_uint2(masked2(m.x, acc[0], acc[1]), masked2(m.y, acc[2], acc[3]));
+          in[k] = read_tr(in2[py] + 16 * rr * kCropRow + (px ? 0 : kCropB));
         }
         q += t.n;
-        // dW1: C[co][tap] += sum_k dz1[co][k] in(k, tap) over the wave's 32 pixels of the phase, k = 8 lg
-        // + 4 rr + i <-> pixel (2 (wave + 8 rr) + py, 2 (4 lg + i) + px).  B: lane (tap = lr, lg) reads
-        // in[4 qy + 2 py + ky - 1][16 lg + 4 i + r], r = 2 px + kx - 1, i < 4: plane r (plane 4 for
-        // r = -1), four consecutive elements from column 4 lg.
-        uint2 bw[2] = {make_uint2(0u, 0u), make_uint2(0u, 0u)};
-        if (lr < 9) {
-          const int ky = lr / 3, kx = lr % 3, r = 2 * px + kx - 1;
-          const uint16_t* pl = s_inq + (r < 0 ? 4 : r) * kInqPlane + 4 * lg;
-#pragma unroll
-          for (int rr = 0; rr < 2; ++rr) {
-            const int row = 4 * (wave + 8 * rr) + 2 * py + ky - 1;
-            bw[rr] = *reinterpret_cast<const uint2*>(pl + (row + 1) * kInqRow);
-          }
-        }
-        const uint4 au = make_uint4(dpk[0], dpk[1], dpk[2], dpk[3]);
-        const uint4 bu = make_uint4(bw[0].x, bw[0].y, bw[1].x, bw[1].y);
-        gw1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, au), __builtin_bit_cast(bf16x8, bu),
-                                                      gw1, 0, 0, 0);
+        const bf16x8 df = __builtin_bit_cast(bf16x8, make_uint4(d[0].x, d[0].y, d[1].x, d[1].y));
+        gw1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            df, __builtin_bit_cast(bf16x8, make_uint4(in[0].x, in[0].y, in[1].x, in[1].y)), gw1, 0, 0, 0);
+        gb1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(df, ones, gb1, 0, 0, 0);
       }
     }
     __syncthreads();
   }
 
-  // ---- write the workgroup's partial sums (fixed order everywhere)
+  // ---- write the workgroup's partial sums (fixed order everywhere), the waves' summed in wave order through LDS
+  constexpr int NW = kBwdThreads / 64;
   float* out = part + (int64_t)blockIdx.x * kConvPart;
-  float* st = reinterpret_cast<float*>(s_a1x);   // free after the sample loop
-  // dW2 [co][nt*16 + ci]: lane value C[4 lg + i][lr] of tile (nt, mt) = (co = 16 mt + 4 lg + i, ci = lr), the
-  // eight waves' k-step partials summed in wave order, three taps at a time through LDS
+  float* st = reinterpret_cast<float*>(s_a1);   // free after the sample loop
+  static_assert(NW * 3 * 512 * 4 <= kA1Bytes && NW * (256 + kC1 + kC2) * 4 <= kDzBytes, "the sums' staging");
+  // dW2 [co][nt*16 + ci]: lane value C[4 lg + i][lr] of tile (nt, mt) = (co = 16 mt + 4 lg + i, ci = lr), three taps
+  // at a time
 #pragma unroll
   for (int g = 0; g < 3; ++g) {
 #pragma unroll
@@ -752,38 +755,33 @@ __global__ __launch_bounds__(kBwdThreads) void k_conv_bwd(const float* __restric
     for (int e = threadIdx.x; e < 3 * 512; e += kBwdThreads) {
       const int j = e >> 9, r = e & 511;
       float sum = 0.0f;
-      for (int w = 0; w < 8; ++w) sum += st[(w * 3 + j) * 512 + r];
+#pragma unroll
+      for (int w = 0; w < NW; ++w) sum += st[(w * 3 + j) * 512 + r];
       out[(r >> 4) * 144 + (3 * g + j) * 16 + (r & 15)] = sum;
     }
     __syncthreads();
   }
-  // dW1 tile: C[4 lg + i][lr] = (co = 4 lg + i, tap = lr), summed over the waves in wave order
+  // dW1 [co][tap] and the biases
+  float* sb = reinterpret_cast<float*>(s_dz) + wave * (256 + kC1 + kC2);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) s_red[wave][(4 * lg + i) * 16 + lr] = gw1[i];
-  __syncthreads();
-  for (int e = threadIdx.x; e < kC1 * 16; e += kBwdThreads) {
-    float sum = 0.0f;
-    for (int w = 0; w < 8; ++w) sum += s_red[w][e];
-    out[kConvPartW2 + e] = sum;
+  for (int i = 0; i < 4; ++i) {
+    const int c = 4 * lg + i;
+    if ((lr & 3) > 0 && lr < 12) sb[c * 16 + (lr >> 2) * 3 + (lr & 3) - 1] = gw1[i];
+    else sb[c * 16 + (lr < 12 ? 9 + (lr >> 2) : lr)] = 0.0f;   // taps 9 .. 15
+    if (lr == 0) {
+      sb[256 + c] = gb1[i];
+      sb[256 + kC1 + c] = gb2[0][i];
+      sb[256 + kC1 + 16 + c] = gb2[1][i];
+    }
   }
   __syncthreads();
-  {
-    // db1: lane lr of each wave holds a channel-lr sum; db2: thread t holds channels t / 32 and t / 32 + 16
-    st[threadIdx.x] = gb1;
-    st[kBwdThreads + threadIdx.x] = gb2[0];
-    st[2 * kBwdThreads + threadIdx.x] = gb2[1];
-    __syncthreads();
-    if (threadIdx.x < kC1) {
-      float s = 0.0f;
-      for (int t = 0; t < kBwdThreads; ++t)
-        if ((t & 15) == threadIdx.x) s += st[t];
-      out[kConvPartW2 + kConvPartW1 + threadIdx.x] = s;
-    } else if (threadIdx.x >= 64 && threadIdx.x < 64 + kC2) {
-      const int co = threadIdx.x - 64, r = co >> 4, t0 = (co & 15) * 32;
-      float s = 0.0f;
-      for (int t = t0; t < t0 + 32; ++t) s += st[(1 + r) * kBwdThreads + t];
-      out[kConvPartW2 + kConvPartW1 + kC1 + co] = s;
-    }
+  static_assert(kConvPartW1 == 256, "dW1, db1 and db2 are consecutive in the partials");
+  for (int e = threadIdx.x; e < 256 + kC1 + kC2; e += kBwdThreads) {
+    const float* q = reinterpret_cast<const float*>(s_dz) + e;
+    float sum = 0.0f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) sum += q[w * (256 + kC1 + kC2)];
+    out[kConvPartW2 + e] = sum;
   }
 }
 

@@ -67,7 +67,7 @@ namespace {
 constexpr int kConvGrid = 1024;    // encoder forward: the resident workgroups (four per CU), each looping over samples
 constexpr int kConvGridPrec = 512; // the split-precision encoder forward holds twice the LDS: two per CU
 constexpr int kConvFragsAll = kConvLoFrag + kConvFrags;   // forward, backward phase and lo fragments
-constexpr int kConvBwdGrid = 256;  // encoder backward: one 8-wave workgroup per CU (LDS-bound)
+constexpr int kConvBwdGrid = 512;  // encoder backward: two workgroups per CU (LDS)
 constexpr int64_t kFc1Splits = 12, kFc2Splits = 64;
 constexpr int kFc1MinBlocks = 512;   // FC1 forward: resident workgroups (two per CU) that its K splits fill
 constexpr int kFc1WideBlocks = 160;  // workgroups from which FC1 takes the 128 x 256 tiles
