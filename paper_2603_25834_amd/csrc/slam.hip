@@ -50,6 +50,7 @@ constexpr int kCsmMaxHalf = 8;                      // W, V <= 8
 constexpr int kCsmMaxRayHeadings = 8192;            // (2V + 1) * R ray offsets staged in LDS
 constexpr int kCsmMaxCand = (2 * kCsmMaxHalf + 1) * (2 * kCsmMaxHalf + 1) * (2 * kCsmMaxHalf + 1);
 constexpr int64_t kCsmLdsBudget = 163840 - 64;      // dynamic LDS of the staged kernel (160 KB less its reductions)
+constexpr int64_t kCsmCellsBudget = 163840 - 2048;  // of the one for whole-cell steps (its counts too)
 
 // ------------------------------------------------------------------ correlative scan matching
 
@@ -183,6 +184,64 @@ constexpr int kCsmLdsMaxCand = 1024;
 constexpr int kCsmLdsMaxLine = 9;                  // 2W + 1 <= 9
 constexpr int kCsmLdsPad = 2;                      // cells between a staged row's end and the next row
 constexpr int32_t kNoReturnY = -(1 << 30);        // y offset of a ray without a return: a negative row in every band
+
+// The candidates' scores (the chunks' partial sums in chunk order), their best, the best outside its 3 x 3 x 3
+// neighbourhood and the rays used (this thread's count in `used`), into o[0 .. 5].
+__device__ __forceinline__ void finish_match(const int32_t* s_part, int32_t (*s_red)[2], int chunks, int ncand, int nw,
+                                             int W, int V, int used, int32_t* o) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int32_t sc[2];
+#pragma unroll
+  for (int m = 0; m < 2; ++m) {
+    const int c = threadIdx.x + m * kCsmLdsThreads;
+    sc[m] = INT32_MIN;
+    if (c < ncand) {
+      int32_t t = 0;
+#pragma unroll 5
+      for (int z = 0; z < chunks; ++z) t += s_part[z * ncand + c];
+      sc[m] = t;
+    }
+  }
+  int32_t bs = INT32_MIN, bi = INT32_MAX;
+#pragma unroll
+  for (int m = 0; m < 2; ++m) {
+    const int c = threadIdx.x + m * kCsmLdsThreads;
+    if (c < ncand && (sc[m] > bs || (sc[m] == bs && c < bi))) { bs = sc[m]; bi = c; }
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    const int32_t os = __shfl_xor(bs, off, 64), oi = __shfl_xor(bi, off, 64);
+    if (os > bs || (os == bs && oi < bi)) { bs = os; bi = oi; }
+  }
+  if (lane == 0) { s_red[wave][0] = bs; s_red[wave][1] = bi; }
+  __syncthreads();
+  bs = s_red[0][0]; bi = s_red[0][1];
+  for (int w = 1; w < kCsmLdsThreads / 64; ++w) {
+    const int32_t os = s_red[w][0], oi = s_red[w][1];
+    if (os > bs || (os == bs && oi < bi)) { bs = os; bi = oi; }
+  }
+  const int bk = bi / (nw * nw), brem = bi - bk * nw * nw, bj = brem / nw, bii = brem - bj * nw;
+  int32_t ss = INT32_MIN;
+#pragma unroll
+  for (int m = 0; m < 2; ++m) {
+    const int c = threadIdx.x + m * kCsmLdsThreads;
+    if (c >= ncand) continue;
+    const int k = c / (nw * nw), rem = c - k * nw * nw, j = rem / nw, i = rem - j * nw;
+    if (max(max(abs(i - bii), abs(j - bj)), abs(k - bk)) >= 2) ss = max(ss, sc[m]);
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) ss = max(ss, __shfl_xor(ss, off, 64));
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) used += __shfl_xor(used, off, 64);
+  __syncthreads();
+  if (lane == 0) { s_red[wave][0] = ss; s_red[wave][1] = used; }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int32_t s2 = s_red[0][0], u = s_red[0][1];
+    for (int w = 1; w < kCsmLdsThreads / 64; ++w) { s2 = max(s2, s_red[w][0]); u += s_red[w][1]; }
+    o[0] = bii - W; o[1] = bj - W; o[2] = bk - V; o[3] = bs; o[4] = s2; o[5] = u;
+  }
+}
 
 __global__ __launch_bounds__(kCsmLdsThreads) void k_csm_lds(const int16_t* __restrict__ belief,
                                                             const int64_t* __restrict__ cell_off,
@@ -400,57 +459,256 @@ __global__ __launch_bounds__(kCsmLdsThreads) void k_csm_lds(const int16_t* __res
       if (i < nw) s_part[ch * ncand + line * nw + i] = acc[i];
   }
   __syncthreads();
-  int32_t sc[2];
+  finish_match(s_part, s_red, chunks, ncand, nw, W, V, used, out + 6 * (int64_t)r);
+}
+
+// The same for lattices whose translation step is one cell (the default), with at most 9 translations per axis
+// and 1024 candidates: every candidate of a heading then reads, per ray, a window of (2W + 1)^2 cells around
+// the ray's end cell, so the end cell is found once per heading and ray and a line of candidates along x is
+// 2W + 1 consecutive cells, read as whole 4-byte words.
+//
+// What bounds the general kernel above is vector instructions: the bounds and addresses of every single cell,
+// about seven per read.  Here the box of cells is staged between zeros (2W rows above, 2W + 1 below, 8 columns
+// or more after each row, which are also those before the next), an end cell whose window misses the box is moved to
+// the zeros below, and a line is five words (W = 4), moved by a cell where its first cell lies in a word's upper half:
+// per ray and line five word reads, five alignments and nine sums, no test.  Lanes on one ray at neighbouring rows
+// and headings read the same or neighbouring words (lists of the rays by that half, which need no alignment, put
+// neighbouring headings on different rays: 22 thousand cycles a robot for the scores, 16 this way).
+// What bounds it now is one workgroup per CU (the grid's 131 KB), whose phases follow one another: 12 thousand cycles
+// for the end cells (a table read of its own line each), 11 for the staging, 16 for the scores, 5 for the best.
+// 750 robots, 256 x 256 cells, W = 4, V = 5: 117 -> 68 us at 360 rays, 60 -> 40 at 128.  1024 threads: 68 and 45.
+constexpr int kCellPad = 8;            // zero columns after each row, >= 2 W
+constexpr int16_t kNoReturnCell = -32768;   // row of a ray without a return: outside every band
+
+// End cell of ray q at heading ph + dh, relative to the search centre's cell, in Q16.
+__device__ __forceinline__ int2 ray_offset(const int32_t* dirtab, int32_t heading, int32_t rq) {
+  int32_t h = heading % kNang;
+  if (h < 0) h += kNang;
+  const int32_t d = dirtab[h];
+  const int32_t c = (int32_t)(int16_t)(d & 0xffff), s = d >> 16;
+  return make_int2((int32_t)(((int64_t)rq * c) >> 14), (int32_t)(((int64_t)rq * s) >> 14));
+}
+
+// acc[i] += the i-th cell of each ray's window row, i < NW, over the rays q0 .. q1 - 1: at(q) is the byte offset of
+// the window's first cell.
+template <int NW, class AT>
+__device__ __forceinline__ void score_cells(const unsigned char* grid, uint32_t row, const AT& at, int q0, int q1,
+                                            int32_t (&acc)[NW]) {
+  typedef short Pair __attribute__((ext_vector_type(2)));
+  constexpr int ND = (NW + 1) / 2, kRays = 4;
+  auto load = [&](int32_t (&w)[ND], uint32_t a) {
+    const int32_t* g = reinterpret_cast<const int32_t*>(grid + (a & ~3u));
 #pragma unroll
-  for (int m = 0; m < 2; ++m) {
-    const int c = threadIdx.x + m * kCsmLdsThreads;
-    sc[m] = INT32_MIN;
-    if (c < ncand) {
-      int32_t t = 0;
-      for (int z = 0; z < chunks; ++z) t += s_part[z * ncand + c];
-      sc[m] = t;
+    for (int d = 0; d < ND; ++d) w[d] = g[d];
+  };
+  auto add = [&](const int32_t (&w)[ND], uint32_t a) {
+#pragma unroll
+    for (int d = 0; d < ND; ++d) {
+      const Pair v = __builtin_bit_cast(Pair, __builtin_amdgcn_alignbyte(w[d + 1 < ND ? d + 1 : d], w[d], a));
+      acc[2 * d] = __builtin_amdgcn_sdot2(v, Pair{1, 0}, acc[2 * d], false);
+      if (2 * d + 1 < NW) acc[2 * d + 1] = __builtin_amdgcn_sdot2(v, Pair{0, 1}, acc[2 * d + 1], false);
     }
-  }
-  int32_t bs = INT32_MIN, bi = INT32_MAX;
+  };
+  int q = q0;
+  for (; q + kRays <= q1; q += kRays) {
+    int32_t w[kRays][ND];
+    uint32_t a[kRays];
 #pragma unroll
-  for (int m = 0; m < 2; ++m) {
-    const int c = threadIdx.x + m * kCsmLdsThreads;
-    if (c < ncand && (sc[m] > bs || (sc[m] == bs && c < bi))) { bs = sc[m]; bi = c; }
+    for (int u = 0; u < kRays; ++u) {
+      a[u] = at(q + u) + row;
+      load(w[u], a[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < kRays; ++u) add(w[u], a[u]);
+  }
+  for (; q < q1; ++q) {
+    int32_t w[ND];
+    const uint32_t a = at(q) + row;
+    load(w, a);
+    add(w, a);
+  }
+}
+
+// Dynamic LDS: cap_cells int16 cells (a multiple of 8; the partial sums take this space after the last band), then
+// (2V + 1) R words: the rays' end cells (x low, y high), with one band turned into their windows' offsets in place,
+// else each band's pass forms those as it reads them.
+typedef uint32_t Words4 __attribute__((ext_vector_type(4)));   // (an array of a plain vector type stays in registers)
+
+template <int W>
+__global__ __launch_bounds__(kCsmLdsThreads) void k_csm_cells(
+    const int16_t* __restrict__ belief, const int64_t* __restrict__ cell_off, const int32_t* __restrict__ side,
+    const int32_t* __restrict__ pose_q, const int32_t* __restrict__ rho_q, int R, const int32_t* __restrict__ a_off,
+    const int32_t* __restrict__ dirtab, int V, int step_h, int cap_cells, int32_t* __restrict__ out) {
+  constexpr int NW = 2 * W + 1, kWaves = kCsmLdsThreads / 64;
+  extern __shared__ __align__(16) unsigned char s_dyn[];
+  int16_t* s_grid = reinterpret_cast<int16_t*>(s_dyn);
+  int32_t* s_part = reinterpret_cast<int32_t*>(s_dyn);
+  uint32_t* s_list = reinterpret_cast<uint32_t*>(s_dyn + 2 * (int64_t)cap_cells);
+  __shared__ int32_t s_red[kWaves][2];
+  __shared__ int32_t s_box[4];                        // min x, max x, min y, max y of the ray offsets
+  const int r = blockIdx.x;
+  const int nk = 2 * V + 1, ncand = nk * NW * NW, nline = nk * NW;
+  const int32_t px = pose_q[3 * r], py = pose_q[3 * r + 1], ph = pose_q[3 * r + 2];
+  const int32_t* rho = rho_q + (int64_t)r * R;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int32_t sd = side[r];
+  const int64_t base = cell_off[r];
+  if (threadIdx.x < 2) { s_box[2 * threadIdx.x] = INT32_MAX; s_box[2 * threadIdx.x + 1] = INT32_MIN; }
+  __syncthreads();
+  // ---- end cells, kInFlight of a thread's reads at a time
+  int32_t mnx = INT32_MAX, mxx = INT32_MIN, mny = INT32_MAX, mxy = INT32_MIN;
+  int used = 0;
+  {
+    constexpr int kInFlight = 4;
+    const int32_t ph0 = ph % kNang;   // headings in 32 bits: |k - V| step_h <= 8 x 46080
+    const int dk = kCsmLdsThreads / R, dq = kCsmLdsThreads - dk * R;
+    int k = threadIdx.x / R, q = threadIdx.x - k * R;
+    for (int e0 = threadIdx.x; e0 < nk * R; e0 += kInFlight * kCsmLdsThreads) {
+      int32_t rq[kInFlight], h[kInFlight];
+      bool first[kInFlight];
+#pragma unroll
+      for (int u = 0; u < kInFlight; ++u) {
+        const bool in = k < nk;
+        rq[u] = in ? rho[q] : -1;
+        h[u] = in ? a_off[q] % kNang + ph0 + (k - V) * step_h : 0;
+        first[u] = k == 0;
+        q += dq;
+        k += dk;
+        if (q >= R) { q -= R; ++k; }
+      }
+      int2 o[kInFlight];
+#pragma unroll
+      for (int u = 0; u < kInFlight; ++u) o[u] = ray_offset(dirtab, h[u], max(rq[u], 0));
+#pragma unroll
+      for (int u = 0; u < kInFlight; ++u) {
+        const int e = e0 + u * kCsmLdsThreads;
+        // (cells that do not fit 16 bits belong to a robot that is scored from global memory)
+        uint32_t cell = (uint32_t)kNoReturnCell << 16;
+        if (rq[u] >= 0) {
+          mnx = min(mnx, o[u].x); mxx = max(mxx, o[u].x); mny = min(mny, o[u].y); mxy = max(mxy, o[u].y);
+          used += first[u];
+          cell = ((uint32_t)(((int64_t)px + o[u].x) >> 16) & 0xffffu) | ((uint32_t)(((int64_t)py + o[u].y) >> 16) << 16);
+        }
+        if (e < nk * R) s_list[e] = cell;
+      }
+    }
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
-    const int32_t os = __shfl_xor(bs, off, 64), oi = __shfl_xor(bi, off, 64);
-    if (os > bs || (os == bs && oi < bi)) { bs = os; bi = oi; }
+    mnx = min(mnx, __shfl_xor(mnx, off, 64)); mxx = max(mxx, __shfl_xor(mxx, off, 64));
+    mny = min(mny, __shfl_xor(mny, off, 64)); mxy = max(mxy, __shfl_xor(mxy, off, 64));
   }
-  if (lane == 0) { s_red[wave][0] = bs; s_red[wave][1] = bi; }
+  if (lane == 0) {
+    atomicMin(&s_box[0], mnx); atomicMax(&s_box[1], mxx);
+    atomicMin(&s_box[2], mny); atomicMax(&s_box[3], mxy);
+  }
   __syncthreads();
-  bs = s_red[0][0]; bi = s_red[0][1];
-  for (int w = 1; w < kCsmLdsThreads / 64; ++w) {
-    const int32_t os = s_red[w][0], oi = s_red[w][1];
-    if (os > bs || (os == bs && oi < bi)) { bs = os; bi = oi; }
+  mnx = s_box[0]; mxx = s_box[1]; mny = s_box[2]; mxy = s_box[3];
+  // the cells any candidate's endpoint can reach, clipped to the grid (empty: every score is 0)
+  int64_t bx0 = 0, bx1 = -1, by0 = 0, by1 = -1;
+  if (mnx <= mxx && sd > 0) {
+    bx0 = max<int64_t>(0, (((int64_t)px + mnx) >> 16) - W);
+    bx1 = min<int64_t>(sd - 1, (((int64_t)px + mxx) >> 16) + W);
+    by0 = max<int64_t>(0, (((int64_t)py + mny) >> 16) - W);
+    by1 = min<int64_t>(sd - 1, (((int64_t)py + mxy) >> 16) + W);
   }
-  const int bk = bi / (nw * nw), brem = bi - bk * nw * nw, bj = brem / nw, bii = brem - bj * nw;
-  int32_t ss = INT32_MIN;
+  const bool empty = bx0 > bx1 || by0 > by1;
+  const bool vec = (reinterpret_cast<uintptr_t>(belief + base) & 15) == 0 && (sd & 7) == 0;
+  const int64_t x0a = vec ? (bx0 & ~(int64_t)7) : bx0;
+  const int64_t ncols = (vec ? min<int64_t>(sd, (bx1 + 8) & ~(int64_t)7) : bx1 + 1) - x0a;
+  // rows of 16 bytes; a pitch of a multiple of 16 words would put the nine rows of a window on few banks
+  int64_t pitch64 = ((ncols + 7) & ~(int64_t)7) + kCellPad;
+  if ((pitch64 & 31) == 0 && (by1 - by0 + 2 + 4 * W) * (pitch64 + 8) + kCellPad <= cap_cells) pitch64 += 8;
+  // as above: centre within 2^28, offsets within 2^29 (cells then fit 16 bits), and at least a row of the box
+  const bool near = mnx >= -(1 << 29) && mxx <= (1 << 29) && mny >= -(1 << 29) && mxy <= (1 << 29) &&
+                    px > -(1 << 28) && px < (1 << 28) && py > -(1 << 28) && py < (1 << 28);
+  const bool staged = near && pitch64 * (4 * W + 2) + kCellPad <= cap_cells;
+  const int chunks = max(1, min(R, kCsmLdsThreads / nline));
+  const int ch = threadIdx.x / nline, line = threadIdx.x - ch * nline, lk = line / NW, lj = line - lk * NW;
+  const bool active = ch < chunks;
+  int32_t acc[NW];
 #pragma unroll
-  for (int m = 0; m < 2; ++m) {
-    const int c = threadIdx.x + m * kCsmLdsThreads;
-    if (c >= ncand) continue;
-    const int k = c / (nw * nw), rem = c - k * nw * nw, j = rem / nw, i = rem - j * nw;
-    if (max(max(abs(i - bii), abs(j - bj)), abs(k - bk)) >= 2) ss = max(ss, sc[m]);
+  for (int i = 0; i < NW; ++i) acc[i] = 0;
+  if (!empty && staged) {
+    const int pitch = (int)pitch64, cols = (int)ncols, xa = (int)x0a;
+    const int band = (cap_cells - kCellPad) / pitch - (4 * W + 1);
+    const bool one = by1 - by0 + 1 <= band;
+    // byte offset of the first cell of the window's first row, of a ray whose end cell is v
+    auto window = [&](uint32_t v, int row0, int nrows) -> uint32_t {
+      const int x = (int)(int16_t)(v & 0xffff) - xa, y = ((int32_t)v >> 16) - row0;
+      const bool in = (uint32_t)(x + W) < (uint32_t)(cols + 2 * W) && (uint32_t)(y + W) < (uint32_t)(nrows + 2 * W);
+      return 2u * (uint32_t)(kCellPad + (in ? (y + W) * pitch + x : (nrows + 2 * W) * pitch) - W);
+    };
+    for (int row0 = (int)by0; row0 <= (int)by1; row0 += band) {
+      const int nrows = min(band, (int)by1 + 1 - row0);
+      // zeros around the rows; row y of the band at kCellPad + (2W + y) pitch
+      const int head = (kCellPad + 2 * W * pitch) / 8, tail = (2 * W + 1) * pitch / 8;
+      Words4* g16 = reinterpret_cast<Words4*>(s_grid);
+      for (int e = threadIdx.x; e < head + tail; e += kCsmLdsThreads)
+        g16[e < head ? e : nrows * (pitch / 8) + e] = Words4{0u, 0u, 0u, 0u};
+      if (vec) {
+        // 8 cells per access; thread t takes piece t mod p of rows t / p, t / p + rs, .. (p pieces a row, rs = 512 / p
+        // rows a pass; a row of more than 512 pieces: pieces t, t + 512, .. of every row), kStage reads in flight
+        constexpr int kStage = 8;
+        const Words4* src = reinterpret_cast<const Words4*>(belief + base + (int64_t)row0 * sd + x0a);
+        const int per_row = cols >> 3, src_pitch = sd >> 3, p8 = pitch >> 3;
+        const int rs = max(1, kCsmLdsThreads / per_row);
+        const int first = per_row >= kCsmLdsThreads ? 0 : (int)threadIdx.x / per_row;
+        const int piece0 = per_row >= kCsmLdsThreads ? (int)threadIdx.x : (int)threadIdx.x - first * per_row;
+        if (first < rs) {
+          for (int xp = piece0; xp < per_row; xp += kCsmLdsThreads) {
+            for (int y0 = first; y0 < nrows; y0 += kStage * rs) {
+              const Words4* s0 = src + (int64_t)y0 * src_pitch + xp;
+              Words4* d0 = g16 + head + y0 * p8 + xp;
+              Words4 t[kStage];
+#pragma unroll
+              for (int u = 0; u < kStage; ++u)
+                if (y0 + u * rs < nrows) t[u] = s0[(int64_t)u * rs * src_pitch];
+#pragma unroll
+              for (int u = 0; u < kStage; ++u)
+                if (y0 + u * rs < nrows) d0[u * rs * p8] = t[u];
+            }
+          }
+        }
+        const int pads = p8 - per_row;
+        for (int e = threadIdx.x; e < nrows * pads; e += kCsmLdsThreads)
+          g16[head + e / pads * p8 + per_row + e % pads] = Words4{0u, 0u, 0u, 0u};
+      } else {
+        for (int e = threadIdx.x; e < nrows * pitch; e += kCsmLdsThreads) {
+          const int yy = e / pitch, xx = e - yy * pitch;
+          s_grid[kCellPad + 2 * W * pitch + e] = xx < cols ? belief[base + (int64_t)(row0 + yy) * sd + x0a + xx] : (int16_t)0;
+        }
+      }
+      if (one) {   // the end cells become the lists
+        for (int e = threadIdx.x; e < nk * R; e += kCsmLdsThreads) s_list[e] = window(s_list[e], row0, nrows);
+      }
+      __syncthreads();
+      if (active) {
+        const int q0 = lk * R + ch * R / chunks, q1 = lk * R + (ch + 1) * R / chunks;
+        const uint32_t row = 2u * lj * pitch;
+        if (one) score_cells<NW>(s_dyn, row, [&](int q) { return s_list[q]; }, q0, q1, acc);
+        else score_cells<NW>(s_dyn, row, [&](int q) { return window(s_list[q], row0, nrows); }, q0, q1, acc);
+      }
+      __syncthreads();   // the band is read before the next one (or the partial sums) takes its space
+    }
+  } else if (!empty && active) {   // from global memory in 64 bits
+    const int q0 = (int)((int64_t)ch * R / chunks), q1 = (int)((int64_t)(ch + 1) * R / chunks);
+    for (int q = q0; q < q1; ++q) {
+      if (rho[q] < 0) continue;
+      const int2 o = ray_offset(dirtab, ph % kNang + (lk - V) * step_h + a_off[q] % kNang, rho[q]);
+      const int64_t cy = (((int64_t)py + o.y) >> 16) + lj - W, cx = (((int64_t)px + o.x) >> 16) - W;
+      if (cy < 0 || cy >= sd) continue;
+#pragma unroll
+      for (int i = 0; i < NW; ++i)
+        if (cx + i >= 0 && cx + i < sd) acc[i] += belief[base + cy * sd + cx + i];
+    }
   }
+  if (active) {
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) ss = max(ss, __shfl_xor(ss, off, 64));
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) used += __shfl_xor(used, off, 64);
+    for (int i = 0; i < NW; ++i) s_part[ch * ncand + line * NW + i] = acc[i];
+  }
   __syncthreads();
-  if (lane == 0) { s_red[wave][0] = ss; s_red[wave][1] = used; }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int32_t s2 = s_red[0][0], u = s_red[0][1];
-    for (int w = 1; w < kCsmLdsThreads / 64; ++w) { s2 = max(s2, s_red[w][0]); u += s_red[w][1]; }
-    int32_t* o = out + 6 * (int64_t)r;
-    o[0] = bii - W; o[1] = bj - W; o[2] = bk - V; o[3] = bs; o[4] = s2; o[5] = u;
-  }
+  finish_match(s_part, s_red, chunks, ncand, NW, W, V, used, out + 6 * (int64_t)r);
 }
 
 // ------------------------------------------------------------------ scan factor
@@ -811,6 +1069,21 @@ hipError_t launch_csm_match(const int32_t* tab, const int16_t* belief_dev, const
     const int chunks = std::max(1, std::min((int)R, kCsmLdsThreads / ((2 * V + 1) * (2 * W + 1))));
     const int64_t off_bytes = (int64_t)(2 * V + 1) * R * (int64_t)sizeof(int2);
     const int64_t part_cells = (2 * (int64_t)ncand * chunks + 7) & ~(int64_t)7;
+    if (step_xy_q == 65536 && W > 0) {
+      // the whole grid between its zeros, the end cells beside it
+      const int64_t list_bytes = (int64_t)(2 * V + 1) * R * 4, pitch = ((max_side + 7) & ~7) + kCellPad;
+      const int64_t room = ((kCsmCellsBudget - list_bytes) / 2) & ~(int64_t)7;
+      const int64_t whole = (int64_t)(max_side + 4 * W + 1) * (pitch + ((pitch & 31) == 0 ? 8 : 0)) + kCellPad;
+      const int64_t cap_cells = std::max(part_cells, std::min(whole, room));
+      const int bytes = (int)(2 * cap_cells + list_bytes);
+      auto kernel = W == 1 ? k_csm_cells<1> : W == 2 ? k_csm_cells<2> : W == 3 ? k_csm_cells<3> : k_csm_cells<4>;
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+      if (e != hipSuccess) return e;
+      kernel<<<n, kCsmLdsThreads, bytes, stream>>>(belief_dev, cell_off_dev, side_dev, pose_q_dev, rho_q_dev, R,
+                                                   a_off_dev, tab, V, step_h, (int)cap_cells, out_dev);
+      return hipGetLastError();
+    }
     const int64_t whole = (((int64_t)max_side + kCsmLdsPad) * max_side + 7) & ~(int64_t)7;
     const int64_t room = ((kCsmLdsBudget - off_bytes) / 2) & ~(int64_t)7;
     const int64_t cap_cells = std::max(part_cells, std::min(whole, room));

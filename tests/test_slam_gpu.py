@@ -96,6 +96,25 @@ def test_match_staged_and_global_grids(sides, max_side, W, V, R):
         assert tuple(int(v) for v in got[r]) == want, (r, got[r], want)
 
 
+@pytest.mark.parametrize("W,V,R,max_side", [(1, 8, 481, None), (2, 0, 1, None), (3, 8, 63, 48), (4, 5, 5, 48), (1, 1, 700, 20)])
+def test_match_whole_cell_steps(W, V, R, max_side):
+    """Lattices of one-cell steps at every width of the kernel for them, few and many rays, one band and several
+    (grids beside an LDS sized for max_side), rows of any residue: the oracle's answers (exact)."""
+    sides = [64, 37, 256, 300, 40]
+    grids, belief, cell_off, side, pose, rho, a_off = _batch(7 * W + V + R, sides, R, W, V, 65536, 64)
+    cfg = slam.csm_config(W, V, 65536, 64)
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    say(f"[slam] csm one-cell steps W={W} V={V} R={R} max_side={max_side}")
+    got = slam.csm_match(d(belief), d(cell_off), d(side), d(pose), d(rho), d(a_off), cfg, max_side=max_side)
+    torch.cuda.synchronize()
+    got = got.cpu().numpy()
+    trig = S._trig()
+    for r in range(len(sides)):
+        want = S.csm_match(grids[r], int(pose[r, 0]), int(pose[r, 1]), int(pose[r, 2]), rho[r], a_off, W, V, 65536, 64,
+                           trig)
+        assert tuple(int(v) for v in got[r]) == want, (r, got[r], want)
+
+
 def test_match_far_centres_and_offsets():
     """Staged grids are scored in 32-bit cell arithmetic only when the search centre lies within 2^28
     and every ray offset within 2^29 (Q16); a robot beyond either bound is scored in 64 bits in the same
