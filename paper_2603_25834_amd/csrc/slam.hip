@@ -747,8 +747,25 @@ constexpr int kIntLdsMinWords = 4096;    // LDS bitmaps of at least 16 KB: a ban
 constexpr int kIntLdsMaxWords = 16384;   // and at most 64 KB
 constexpr int kIntMaxSide = 32768;   // bit indices (row offset x row bits + column) stay below 2^31
 constexpr int kIntInFlight = 4;          // octets (8 cells, 16 bytes) each thread keeps in flight in the apply pass
-constexpr int kIntSortMax = 2048;        // rays are ordered by walk length when R <= this
-constexpr int kIntBins = 64;             // length classes of 8 steps
+constexpr int kIntSeg = 32;              // steps of a walk's segment
+constexpr int kIntItems = 2048;          // segments listed at a time (longer ones where the rays' would not fit)
+
+// floor(n / d) for n >= 0 and 0 < d <= 2^15 where the quotient is below 2^20 (the estimate's relative error is below
+// 2^-21, the remainder corrects it by one); a larger quotient comes out above 2^19.
+__device__ __forceinline__ int32_t floor_div(int32_t n, int32_t d) {
+  int32_t q = (int32_t)((float)n * __builtin_amdgcn_rcpf((float)d));
+  const int32_t r = n - q * d;
+  return q + (r < 0 ? -1 : (r >= d ? 1 : 0));
+}
+
+// x steps among the first i >= 1 steps of a walk with start value D0 of the decision variable D: with D in
+// (-65536 aa, 65536 bb] after them and equal to D0 + 65536 (kx bb - (i - kx) aa), kx = floor((i aa + bb - D0 / 65536) /
+// (aa + bb)), the fraction of D0 / 65536 rounding the numerator down.  Axis rays take x steps only (D0 = -1) or y
+// steps only (D0 = 1).
+__device__ __forceinline__ int32_t walk_x_steps(int32_t i, int32_t D0, int32_t aa, int32_t bb) {
+  if (aa == 0 || bb == 0) return D0 <= 0 ? i : 0;
+  return floor_div(i * aa + bb - (D0 >> 16) - ((D0 & 0xffff) != 0 ? 1 : 0), aa + bb);
+}
 
 // Saturating add of the increment of each coded cell of an octet (bit j of `any`: cell j coded, of `hit`:
 // a HIT) to the 8 int16 values packed in v.
@@ -768,12 +785,18 @@ __device__ __forceinline__ int4 apply_octet(int4 v, uint32_t any, uint32_t hit, 
 // One workgroup per robot.  The aligned pose is the predicted pose moved by the match's lattice
 // offsets; the increments are round(w_q l / 256) with w_q = rint(256 w).  Rows are processed in bands
 // whose two bitmaps fit the launch's LDS (sized for the largest side, up to 64 KB: a 512 x 512 grid is
-// one band).  Per band: clear; one lane per ray walks it from the aligned origin with the exact
-// traversal and sets MISS bits for the band's cells and the HIT bit of the end cell of a ray with a
-// return that ended at its range; then the apply pass: one saturating add per coded cell (HIT beats
-// MISS), an octet of 8 cells owned by one thread -- the result does not depend on ray or lane order,
-// so lanes take the rays longest first (a counting sort on the walk's length bound), which keeps the
-// rays of a wave alike in length and the workgroups that share a compute unit from issuing idle steps.
+// one band).  Per band: clear; one lane per ray finds its walk's length and end cell in closed form (up to 512 rays at
+// a time) and sets the HIT bit of a ray with a return that ended at its range; the walks are cut into segments of
+// kIntSeg steps, whose starts have a closed form too, and the lanes take the segments, the full ones first: they
+// set the MISS bits of the band's cells; then the apply pass: one saturating add per coded cell (HIT beats
+// MISS), an octet of 8 cells owned by one thread -- the result does not depend on ray or lane order.
+//
+// What bounds it: the walks were 57 of 102 thousand cycles of a robot (three robots a CU) when a lane took a ray,
+// longest first: the longest walk's 280 steps in sequence, fourteen instructions each with their tests.  A segment
+// is an eighth of that and a full one needs no test.  Then the apply pass, 28 thousand, which moves the coded octets
+// (about 110 KB a robot) at the rate of the memory.  750 robots, 256 x 256 cells: 64 -> 50 us at 360 rays,
+// 51 -> 36 at 128 (segments of 16 or 64 steps: 51 and 53, 38 and 40; eight octets in flight in the apply pass take a third
+// of the resident workgroups away: 64 and 50).
 //
 // The walk: with (a, b) the Q14 direction and the origin's fractional position, the k-th x crossing lies
 // at axis distance ex0 + 65536 k and is within the range iff (ex0 + 65536 k) 2^14 <= rho |a|, so the
@@ -789,8 +812,9 @@ __global__ __launch_bounds__(kIntThreads) void k_csm_integrate(
     const int32_t* __restrict__ wq_in) {
   extern __shared__ __align__(16) uint32_t bits[];
   __shared__ int32_t s_cnt[kIntThreads / 64];
-  __shared__ uint16_t s_perm[kIntSortMax];
-  __shared__ int32_t s_hist[kIntBins];
+  __shared__ uint32_t s_sum[kIntThreads / 64];     // full and (high half) partial segments of a wave's rays
+  __shared__ int32_t s_d0[kIntThreads], s_dir[kIntThreads], s_n[kIntThreads];   // a ray's walk
+  __shared__ uint32_t s_item[kIntItems];           // ray + 512 segment
   const int r = blockIdx.x;
   const int64_t s = side[r];
   const int64_t base = cell_off[r];
@@ -821,69 +845,29 @@ __global__ __launch_bounds__(kIntThreads) void k_csm_integrate(
   uint32_t* hitm = bits + band * nw;
   // 16-byte accesses when every row starts on an 8-cell boundary
   const bool vec = ((base | s) & 7) == 0;
-  const bool sorted = R <= kIntSortMax;
-  if (sorted) {
-    // length class of a ray: its Manhattan length in cells (an upper bound of its steps) / 8
-    auto ray_class = [&](int k) {
-      const int32_t rho = rho_q[(int64_t)r * R + k];
-      const int64_t lim = rho >= 0 ? (int64_t)rho : (int64_t)rmax_q;
-      int64_t di = (ah + (int64_t)a_off[k]) % kNang;
-      if (di < 0) di += kNang;
-      const int32_t dv = dirtab[di];
-      const int64_t ab = abs((int32_t)(int16_t)(dv & 0xffff)) + abs(dv >> 16);
-      return (int32_t)min<int64_t>(kIntBins - 1, ((lim >> 16) * ab) >> 17);
-    };
-    constexpr int kPer = kIntSortMax / kIntThreads;
-    int32_t cls[kPer];
-    for (int i = threadIdx.x; i < kIntBins; i += kIntThreads) s_hist[i] = 0;
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      const int k = threadIdx.x + u * kIntThreads;
-      cls[u] = k < R ? ray_class(k) : 0;
-      if (k < R) atomicAdd(&s_hist[cls[u]], 1);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {   // start of each class, longest class first
-      int32_t acc = 0;
-      for (int c = kIntBins - 1; c >= 0; --c) {
-        const int32_t h = s_hist[c];
-        s_hist[c] = acc;
-        acc += h;
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      const int k = threadIdx.x + u * kIntThreads;
-      if (k < R) s_perm[atomicAdd(&s_hist[cls[u]], 1)] = (uint16_t)k;
-    }
-    __syncthreads();
-  }
   int32_t cnt = 0;
   for (int32_t by0 = 0; by0 < si; by0 += band) {
     const int32_t rows = min(band, si - by0);
-    for (int32_t w = threadIdx.x; w < 2 * band * nw; w += kIntThreads) bits[w] = 0u;
+    for (int32_t w = threadIdx.x; w < (2 * band * nw + 3) / 4; w += kIntThreads)
+      reinterpret_cast<uint4*>(bits)[w] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
-    // Each lane's walk length and end cell are known before it starts: the walk stops at the first
+    // A walk's length and end cell are known before it starts: it stops at the first
     // barred crossing in distance order -- x crossing #nx at axis distance ex0 + 65536 nx or y crossing
-    // #ny, whichever comes first (x on a tie) -- after every crossing that precedes it.  The loop then
-    // only selects the next crossing by the sign of D and marks the cell; trip counts are uniform over
-    // the wave (lanes past their own length mark nothing), and while the band holds the whole grid and
-    // every lane is within its length the marks need no test.
+    // #ny, whichever comes first (x on a tie) -- after every crossing that precedes it.
     const int32_t rowbits = nw << 5;
     const uint32_t band_bits = (uint32_t)(rows * rowbits);
     const bool one_band = band >= si;
+    const int32_t w0 = (cy0 - by0) * rowbits + cx0;   // bit of the origin cell (may lie outside the band)
+    if (threadIdx.x == 0 && R > 0 && (uint32_t)w0 < band_bits) atomicOr(&miss[w0 >> 5], 1u << (w0 & 31));   // every walk's first
     for (int j0 = 0; j0 < R; j0 += kIntThreads) {
       const int j = j0 + (int)threadIdx.x;
       const bool valid = j < R;
       int32_t rho = -1, dv = 0;
       if (valid) {
-        const int k = sorted ? (int)s_perm[j] : j;
-        rho = rho_q[(int64_t)r * R + k];
-        int64_t di = (ah + (int64_t)a_off[k]) % kNang;
-        if (di < 0) di += kNang;
-        dv = dirtab[di];
+        rho = rho_q[(int64_t)r * R + j];
+        int32_t di = (int32_t)ah + a_off[j] % kNang;
+        di += di < 0 ? kNang : 0;
+        dv = dirtab[di >= kNang ? di - kNang : di];
       }
       const int64_t lim = rho >= 0 ? (int64_t)rho : (int64_t)rmax_q;
       const int32_t a = (int16_t)(dv & 0xffff), b = dv >> 16;
@@ -905,47 +889,109 @@ __global__ __launch_bounds__(kIntThreads) void k_csm_integrate(
         const int64_t tx = ((int64_t)ex0 + ((int64_t)nx << 16)) * bb;   // barred x crossing (scaled)
         const int64_t ty = ((int64_t)ey0 + ((int64_t)ny << 16)) * aa;   // barred y crossing (scaled)
         if (tx <= ty) {   // stops at the x crossing: the y crossings strictly before it
-          const int64_t X = tx - (int64_t)ey0 * aa, den = (int64_t)aa << 16;
+          const int64_t X = tx - (int64_t)ey0 * aa;   // ceil(X / (65536 aa)) of them
           kx = nx;
-          ky = X <= 0 ? 0 : (int32_t)min<int64_t>(ny, (X + den - 1) / den);
+          ky = X <= 0 ? 0 : min(ny, floor_div((int32_t)((X - 1) >> 16), aa) + 1);
           at_limit = !gx;
         } else {          // stops at the y crossing: the x crossings at or before it
-          const int64_t Y = ty - (int64_t)ex0 * bb, den = (int64_t)bb << 16;
+          const int64_t Y = ty - (int64_t)ex0 * bb;   // floor(Y / (65536 bb)) + 1 of them
           ky = ny;
-          kx = Y < 0 ? 0 : (int32_t)min<int64_t>(nx, Y / den + 1);
+          kx = Y < 0 ? 0 : min(nx, floor_div((int32_t)(Y >> 16), bb) + 1);
           at_limit = !gy;
         }
       }
       const int32_t n = valid ? kx + ky : 0;
       const int32_t sxw = a > 0 ? 1 : -1, syw = b > 0 ? rowbits : -rowbits;
-      const int32_t w0 = (cy0 - by0) * rowbits + cx0;   // bit of the origin cell (may lie outside the band)
-      int32_t D = aa == 0 ? 1 : (bb == 0 ? -1 : ex0 * bb - ey0 * aa);
-      const int32_t dX = bb == 0 ? 0 : bb << 16, dY = aa == 0 ? 0 : aa << 16;
-      if (valid && (uint32_t)w0 < band_bits) atomicOr(&miss[w0 >> 5], 1u << (w0 & 31));
-      int32_t nmax = n, nmin = n;
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
-        nmax = max(nmax, __shfl_xor(nmax, o, 64));
-        nmin = min(nmin, __shfl_xor(nmin, o, 64));
-      }
-      if (!one_band) nmin = 0;
-      int32_t wi = w0, i = 0;
-      for (; i < nmin; ++i) {
-        const bool stepx = D <= 0;
-        wi += stepx ? sxw : syw;
-        D += stepx ? dX : -dY;
-        atomicOr(&miss[wi >> 5], 1u << (wi & 31));
-      }
-      for (; i < nmax; ++i) {
-        const bool stepx = D <= 0;
-        wi += stepx ? sxw : syw;
-        D += stepx ? dX : -dY;
-        if (i < n && (uint32_t)wi < band_bits) atomicOr(&miss[wi >> 5], 1u << (wi & 31));
-      }
       const int32_t we = w0 + kx * sxw + ky * syw;   // the end cell
       if (valid && rho >= 0 && at_limit && (uint32_t)we < band_bits) atomicOr(&hitm[we >> 5], 1u << (we & 31));
+      s_d0[threadIdx.x] = aa == 0 ? 1 : (bb == 0 ? -1 : ex0 * bb - ey0 * aa);
+      s_dir[threadIdx.x] = dv;
+      s_n[threadIdx.x] = n;
+      // the list of segments: the full ones, then the rays' last ones; longer segments where it would not fit
+      int32_t seg = kIntSeg, full, part;
+      for (;;) {
+        full = floor_div(n, seg);
+        part = n - full * seg > 0 ? 1 : 0;
+        const uint32_t own = (uint32_t)full | ((uint32_t)part << 20);
+        uint32_t sum = own;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const uint32_t t = __shfl_up(sum, o, 64);
+          if ((int)(threadIdx.x & 63) >= o) sum += t;
+        }
+        if ((threadIdx.x & 63) == 63) s_sum[threadIdx.x >> 6] = sum;
+        __syncthreads();
+        uint32_t before = sum - own, total = 0;
+#pragma unroll
+        for (int w = 0; w < kIntThreads / 64; ++w) {
+          before += w < (int)(threadIdx.x >> 6) ? s_sum[w] : 0u;
+          total += s_sum[w];
+        }
+        __syncthreads();
+        const int32_t nfull = (int32_t)(total & 0xfffffu), npart = (int32_t)(total >> 20);
+        if (nfull + npart > kIntItems) {   // once: at most kIntItems - kIntThreads full ones then
+          seg = kIntSeg * ((nfull + kIntItems - kIntThreads) / (kIntItems - kIntThreads));
+          continue;
+        }
+        for (int q = 0; q < full; ++q) s_item[(before & 0xfffffu) + q] = threadIdx.x | ((uint32_t)q << 9);
+        if (part) s_item[nfull + (int32_t)(before >> 20)] = threadIdx.x | ((uint32_t)full << 9);
+        full = nfull;
+        part = npart;
+        break;
+      }
+      __syncthreads();
+      // the start of segment `item`: its ray's D, the bit of the cell before its first step, and the steps' increments
+      struct Walk {
+        int32_t D, wi, dX, dY, sx, sy, n;
+      };
+      auto begin = [&](uint32_t item) {
+        const int32_t k = item & (kIntThreads - 1), i = (int32_t)(item >> 9) * seg;
+        const int32_t d = s_dir[k], D0 = s_d0[k];
+        const int32_t wa = (int16_t)(d & 0xffff), wb = d >> 16, waa = abs(wa), wbb = abs(wb);
+        const int32_t x = i > 0 ? walk_x_steps(i, D0, waa, wbb) : 0;
+        Walk w;
+        w.sx = wa > 0 ? 1 : -1;
+        w.sy = wb > 0 ? rowbits : -rowbits;
+        w.dX = wbb == 0 ? 0 : wbb << 16;
+        w.dY = waa == 0 ? 0 : waa << 16;
+        w.D = D0 + (int32_t)((uint32_t)x * (uint32_t)w.dX - (uint32_t)(i - x) * (uint32_t)w.dY);
+        w.wi = w0 + x * w.sx + (i - x) * w.sy;
+        w.n = s_n[k] - i;
+        return w;
+      };
+      auto advance = [&](Walk& w) {
+        const bool stepx = w.D <= 0;
+        w.wi += stepx ? w.sx : w.sy;
+        w.D += stepx ? w.dX : -w.dY;
+      };
+      if (one_band) {
+        for (int e = threadIdx.x; e < full; e += kIntThreads) {
+          Walk w = begin(s_item[e]);
+#pragma unroll 4
+          for (int i = 0; i < seg; ++i) {
+            advance(w);
+            atomicOr(&miss[w.wi >> 5], 1u << (w.wi & 31));
+          }
+        }
+        for (int e = threadIdx.x; e < part; e += kIntThreads) {
+          Walk w = begin(s_item[full + e]);
+          for (int i = 0; i < w.n; ++i) {
+            advance(w);
+            atomicOr(&miss[w.wi >> 5], 1u << (w.wi & 31));
+          }
+        }
+      } else {
+        for (int e = threadIdx.x; e < full + part; e += kIntThreads) {
+          Walk w = begin(s_item[e]);
+          const int32_t len = min(w.n, seg);
+          for (int i = 0; i < len; ++i) {
+            advance(w);
+            if ((uint32_t)w.wi < band_bits) atomicOr(&miss[w.wi >> 5], 1u << (w.wi & 31));
+          }
+        }
+      }
+      __syncthreads();   // the lists are read before the next rays' take their place
     }
-    __syncthreads();
     // apply: octet o covers cells 8 (o mod 4nw) .. + 7 of band row o / 4nw
     const int32_t opr = 4 * nw, total = rows * opr;
     int16_t* band_base = belief + base + (int64_t)by0 * s;
@@ -959,7 +1005,7 @@ __global__ __launch_bounds__(kIntThreads) void k_csm_integrate(
         hit[u] = 0u;
         off[u] = 0;
         if (o < total) {
-          const int32_t row = o / opr, oc = o - row * opr, sh = (oc & 3) * 8;
+          const int32_t row = floor_div(o, opr), oc = o - row * opr, sh = (oc & 3) * 8;
           const uint32_t wm = miss[row * nw + (oc >> 2)], wh = hitm[row * nw + (oc >> 2)];
           hit[u] = (wh >> sh) & 0xffu;
           any[u] = ((wm >> sh) & 0xffu) | hit[u];
@@ -1110,7 +1156,7 @@ hipError_t launch_csm_integrate(const int32_t* tab, int16_t* belief_dev, const i
   if (n <= 0) return hipSuccess;
   // bitmaps of one band holding the largest grid whole, within [16 KB, 64 KB]
   const int64_t nw_max = ((int64_t)std::min(max_side, kIntMaxSide) + 31) >> 5;
-  const int words = (int)std::min<int64_t>(kIntLdsMaxWords, std::max<int64_t>(kIntLdsMinWords, 2 * nw_max * max_side));
+  const int words = (int)std::min<int64_t>(kIntLdsMaxWords, std::max<int64_t>(kIntLdsMinWords, (2 * nw_max * max_side + 3) & ~(int64_t)3));
   const int bytes = (int)sizeof(uint32_t) * words;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_csm_integrate),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, bytes);

@@ -277,6 +277,14 @@ def test_integrate_bands_and_max_side():
     _integrate_case(44, [300, 64, 200, 96], 90, 2, 2, 65536, 64, 120 * 65536, max_side=64)
 
 
+@pytest.mark.parametrize("sides,R", [([600, 96], 700), ([64, 300], 513), ([128, 40], 1)])
+def test_integrate_walk_segments(sides, R):
+    """Walks cut into segments: more segments than are listed at a time (long walks of many rays, in one band and in
+    bands), rays in more than one group of 512, a single ray: the oracle's grids (exact)."""
+    say(f"[slam] integrate segments sides={sides} R={R}")
+    _integrate_case(45 + R, sides, R, 1, 1, 65536, 64, 500 * 65536)
+
+
 def test_integrate_many_rays_and_no_count():
     """More rays than the length sort takes (2100 > 2048: rays in their own order), and the call without
     the coded-cell output: same exact grids as the oracle."""
