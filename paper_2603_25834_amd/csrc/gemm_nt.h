@@ -166,7 +166,8 @@ __device__ __forceinline__ void mma(const unsigned char* buf, int fx, int fw, f3
 }
 
 // Epilogue contract: store4(z, m, n0, v): columns n0 .. n0 + 3 (n0 a multiple of 4) of row m < M, slice z
-// (product p's slice s at z = p * slices + s).  N is a multiple of kBN.
+// (product p's slice s at z = p * slices + s; kSum: the three products' sum, in their order, at slice z).  N is a
+// multiple of kBN.
 template <int NP, class EPI>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gemm_nt(Operands o, EPI epi,
                                                                                                int k_split) {
@@ -235,10 +236,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     const int m = m0 + wm * 64 + i * 16 + lr;
     if (m >= o.M) continue;
 #pragma unroll
-    for (int p = 0; p < NP; ++p)
+    for (int j = 0; j < 4; ++j) {
+      const int n = n0 + wn * 64 + j * 16 + 4 * lg;
+      if constexpr (EPI::kSum) {
+        epi.store4(tile.tz, m, n, acc[0][j][i] + acc[1][j][i] + acc[2][j][i]);
+      } else {
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        epi.store4(p * slices + tile.tz, m, n0 + wn * 64 + j * 16 + 4 * lg, acc[p][j][i]);
+        for (int p = 0; p < NP; ++p) epi.store4(p * slices + tile.tz, m, n, acc[p][j][i]);
+      }
+    }
   }
 }
 
@@ -256,14 +262,20 @@ hipError_t run(const Operands& o, const EPI& epi, int k_split, hipStream_t st) {
 
 // Split-K partial sums: slice z of a [slices][M][ld] FP32 buffer.
 struct EpiPartial {
+  static constexpr bool kSum = false;
   float* part; int64_t ld, slice;
   __device__ __forceinline__ void store4(int z, int m, int n0, const f32x4& v) const {
     *reinterpret_cast<f32x4*>(part + (int64_t)z * slice + (int64_t)m * ld + n0) = v;
   }
 };
 
+struct EpiSum : EpiPartial {
+  static constexpr bool kSum = true;
+};
+
 // out = bf16(relu(v + bias))
 struct EpiBiasRelu {
+  static constexpr bool kSum = false;
   uint16_t* out; const float* bias; int64_t ld;
   __device__ __forceinline__ void store4(int, int m, int n0, const f32x4& v) const {
     uint16_t h[4];

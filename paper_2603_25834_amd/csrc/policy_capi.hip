@@ -134,8 +134,8 @@ int64_t part_need(const aslam_policy* p) {
   need = std::max<int64_t>(need, (int64_t)kConvBwdGrid * kConvPart);   // encoder backward partials
   need = std::max<int64_t>(need, (int64_t)kBiasBlocks * 256);
   need = std::max<int64_t>(need, (int64_t)kFc1MinBlocks * 64 * kHid);   // FC1 forward split-K: S * B <= 512 * 64
-  if (p->prec)   // the three products of a split FC1, over z (S * B <= 512 * 64 each)
-    need = std::max<int64_t>(need, 3 * (int64_t)kFc1MinBlocks * 64 * kHid);
+  if (p->prec)   // the three products of a split FC1, over z (S * B <= 512 * 64 each, or one slice of more rows)
+    need = std::max<int64_t>(need, 3 * std::max<int64_t>((int64_t)kFc1MinBlocks * 64, p->max_b) * kHid);
   return need;
 }
 
@@ -241,8 +241,20 @@ int encode_fc1(aslam_policy* P, const float* prm, const int16_t* crop, const flo
   const int tiles = ((B + 127) / 128) * (kHid / 128);
   int S = std::max(1, std::min(32, kFc1MinBlocks / tiles));
   if (P->prec && tiles < 32) S = std::max(1, std::min(32, kFc1MinBlocks / (3 * tiles)));
-  const int nz = slices_used(K1, S, 64);
   const int64_t slice = (int64_t)B * kHid;
+  if (P->prec && !training) {
+    // Forward only: the three products summed by the workgroup, so that a slice is a third of the partial sums, and as
+    // many slices of at least 128 k as give every CU a workgroup (128 x 128 tiles with each product in slices of its
+    // own, GEMM and reduction: 14 us at 16 rows, 34 at 750, 75 at 2000, 228 at 8000; this: 12, 28, 43, 137).  The
+    // training pass keeps its slices: its ReLU signs, and so its gradients, follow their rounding.
+    const int64_t rt = (B + 127) / 128;
+    const int k_split = (int)std::min<int64_t>(P->k1p, std::max<int64_t>(128, (K1 * rt / 256 + 63) / 64 * 64));
+    PCHK(gemm_nt::run<3>(gemm_nt::Operands{P->x, P->x_lo, P->w1b, P->w1b_lo, P->k1p, P->k1p, B, kHid, P->k1p},
+                         gemm_nt::EpiSum{{P->part, kHid, slice}}, k_split, st));
+    *S_used = (int)((P->k1p + k_split - 1) / k_split);
+    return ASL_OK;
+  }
+  const int nz = slices_used(K1, S, 64);
   // The wide kernel (128 x 256 tiles, one workgroup per CU) while its tiles and slices come near a round of
   // the CUs; below that (a rollout step: 84 workgroups at 750 rows, 38 us) the 128 x 128 tiles with each
   // product in slices of its own are faster (27 us).
@@ -319,12 +331,11 @@ int act_core(aslam_policy* P, const float* prm, bool prepared, const int16_t* cr
     S = 0;
   }
   const int tail_blocks = (B + kTailRows - 1) / kTailRows;
-  if (P->prec)
-    k_fwd_tail<true><<<tail_blocks, 256, 0, st>>>(prm, P->off, P->part, S, P->h1, P->h1_lo, P->w2b, P->w2b_lo, B, mu,
-                                                  value, sample, eps, act, logp);
-  else
-    k_fwd_tail<false><<<tail_blocks, 256, 0, st>>>(prm, P->off, P->part, S, P->h1, nullptr, P->w2b, nullptr, B, mu,
-                                                   value, sample, eps, act, logp);
+  const bool many = B >= kTailManyRows;
+  (P->prec ? (many ? k_fwd_tail<true, 4> : k_fwd_tail<true, 16>)
+           : (many ? k_fwd_tail<false, 4> : k_fwd_tail<false, 16>))<<<tail_blocks, many ? 256 : 1024, 0, st>>>(
+      prm, P->off, P->part, S, P->h1, P->prec ? P->h1_lo : nullptr, P->w2b, P->prec ? P->w2b_lo : nullptr, B, mu, value,
+      sample, eps, act, logp);
   PCHK(hipGetLastError());
   return ASL_OK;
 }

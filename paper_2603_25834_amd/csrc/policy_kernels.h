@@ -694,22 +694,44 @@ constexpr int kTailLdZ = kHid + 4;   // FP32 z2 rows in LDS, padded
 //
 // PREC (split operands): h1's lo parts ride along (h1lo rows, or formed from the slice sums) and FC2 is
 // h1_hi W2_hi + h1_hi W2_lo + h1_lo W2_hi (w2lo the lo parts of the weights), k step by k step.
-template <bool PREC>
-__global__ __launch_bounds__(256) void k_fwd_tail(const float* prm, Offsets o, const float* part, int S,
+//
+// What bounds it is latency: there are B / 16 workgroups (47 for a rollout step of 750 robots), and with four waves
+// each read 64 columns of W2, then took four rows' head sums in turn.  Sixteen waves read 16 columns each, before h1
+// is there, and take one row.  750 rows, split precision: 16.1 -> 11.3 us, 2000 rows 16.1 -> 11.5.
+constexpr int kTailManyRows = 6144;   // rows from which four waves a workgroup fill the chip (16 there: 27 -> 31 us at 16384)
+
+template <bool PREC, int NW>
+__global__ __launch_bounds__(64 * NW) void k_fwd_tail(const float* prm, Offsets o, const float* part, int S,
                                                   const uint16_t* h1, const uint16_t* h1lo, const uint16_t* w2b,
                                                   const uint16_t* w2lo, int B, float* mu_out, float* v_out,
                                                   bool sample, ActDraws eps, float* act, float* logp) {
+  constexpr int kTailThreads = 64 * NW, kTailFrags = kHid / 16 / NW, kTailPer = kTailRows / NW;   // a wave's columns / 16, rows
+  constexpr bool kAhead = NW == kTailRows;
   __shared__ __align__(16) uint16_t s_h[(PREC ? 2 : 1) * kTailRows * kTailLdH];
   __shared__ __align__(16) float s_z[kTailRows * kTailLdZ];
   uint16_t* const s_hl = s_h + (PREC ? kTailRows * kTailLdH : 0);
   const int row0 = blockIdx.x * kTailRows;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, lr = lane & 15, lg = lane >> 4;
   const float* b1 = prm + o.f1b;
-  // the sample's normals of the wave's rows (4 w .. 4 w + 3, two each), one per lane 0..7, drawn up
-  // front: a library draw is a long dependent chain that the loads and MFMAs below can hide
+  // W2's fragments of the wave's columns
+  const int n0w = 16 * kTailFrags * wave + lr;
+  auto weight = [&](const uint16_t* w, int j, int k) {
+    return *reinterpret_cast<const gemm::u32x4*>(w + (int64_t)(n0w + 16 * j) * kHid + 32 * k + 8 * lg);
+  };
+  gemm::u32x4 bf[kHid / 32], bfl[kHid / 32];
+  if (kAhead) {
+#pragma unroll
+    for (int k = 0; k < kHid / 32; ++k) {
+      bf[k] = weight(w2b, 0, k);
+      if (PREC) bfl[k] = weight(w2lo, 0, k);
+    }
+  }
+  // the sample's normals of the wave's rows (two each), one per lane, drawn up front: a library draw is a
+  // long dependent chain that the loads and MFMAs below can hide
+  const int wrow = kTailPer * wave;
   float my_eps = 0.0f;
-  if (sample && lane < 8 && row0 + 4 * wave + (lane >> 1) < B) my_eps = eps(row0 + 4 * wave + (lane >> 1), lane & 1);
-  for (int g = threadIdx.x; g < kTailRows * (kHid / 8); g += 256) {
+  if (sample && lane < 2 * kTailPer && row0 + wrow + (lane >> 1) < B) my_eps = eps(row0 + wrow + (lane >> 1), lane & 1);
+  for (int g = threadIdx.x; g < kTailRows * (kHid / 8); g += kTailThreads) {
     const int r = g / (kHid / 8), n0 = (g % (kHid / 8)) * 8;
     const int64_t m = row0 + r;
     uint4 v = make_uint4(0u, 0u, 0u, 0u), vl = v;
@@ -737,40 +759,34 @@ __global__ __launch_bounds__(256) void k_fwd_tail(const float* prm, Offsets o, c
     if (PREC) *reinterpret_cast<uint4*>(s_hl + r * kTailLdH + n0) = vl;
   }
   __syncthreads();
-  // FC2: wave w owns columns 64 w .. 64 w + 63 (four 16-column fragments)
-  gemm::f32x4 acc[4];
+  gemm::f32x4 acc[kTailFrags];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) acc[j] = gemm::f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int j = 0; j < kTailFrags; ++j) acc[j] = gemm::f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int k0 = 0; k0 < kHid; k0 += 32) {
+  for (int k = 0; k < kHid / 32; ++k) {
     const gemm::bf16x8 af =
-        __builtin_bit_cast(gemm::bf16x8, *reinterpret_cast<const uint4*>(s_h + lr * kTailLdH + k0 + 8 * lg));
+        __builtin_bit_cast(gemm::bf16x8, *reinterpret_cast<const uint4*>(s_h + lr * kTailLdH + 32 * k + 8 * lg));
     gemm::bf16x8 afl = af;
     if (PREC)
-      afl = __builtin_bit_cast(gemm::bf16x8, *reinterpret_cast<const uint4*>(s_hl + lr * kTailLdH + k0 + 8 * lg));
+      afl = __builtin_bit_cast(gemm::bf16x8, *reinterpret_cast<const uint4*>(s_hl + lr * kTailLdH + 32 * k + 8 * lg));
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = 64 * wave + 16 * j + lr;
-      const gemm::bf16x8 bf =
-          __builtin_bit_cast(gemm::bf16x8, *reinterpret_cast<const uint4*>(w2b + (int64_t)n * kHid + k0 + 8 * lg));
-      acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bf, acc[j], 0, 0, 0);
+    for (int j = 0; j < kTailFrags; ++j) {
+      const gemm::bf16x8 b = __builtin_bit_cast(gemm::bf16x8, kAhead ? bf[k] : weight(w2b, j, k));
+      acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, b, acc[j], 0, 0, 0);
       if (PREC) {
-        const gemm::bf16x8 bfl =
-            __builtin_bit_cast(gemm::bf16x8, *reinterpret_cast<const uint4*>(w2lo + (int64_t)n * kHid + k0 + 8 * lg));
-        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bfl, acc[j], 0, 0, 0);
-        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afl, bf, acc[j], 0, 0, 0);
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, __builtin_bit_cast(gemm::bf16x8, kAhead ? bfl[k] : weight(w2lo, j, k)), acc[j], 0, 0, 0);
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afl, b, acc[j], 0, 0, 0);
       }
     }
   }
-  const float* b2 = prm + o.f2b;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int c = 64 * wave + 16 * j + lr;
+  for (int j = 0; j < kTailFrags; ++j) {
+    const int c = n0w + 16 * j;
+    const float b2 = prm[o.f2b + c];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) s_z[(4 * lg + i) * kTailLdZ + c] = acc[j][i] + b2[c];
+    for (int i = 0; i < 4; ++i) s_z[(4 * lg + i) * kTailLdZ + c] = acc[j][i] + b2;
   }
-  __syncthreads();
-  // heads: wave w takes rows 4 w .. 4 w + 3, lane l holds z2 columns 4 l .. 4 l + 3 (as k_heads)
+  // heads: a wave takes kTailPer rows, lane l holds z2 columns 4 l .. 4 l + 3 (as k_heads)
   float wmu0[4], wmu1[4], wv[4];
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
@@ -778,12 +794,12 @@ __global__ __launch_bounds__(256) void k_fwd_tail(const float* prm, Offsets o, c
     wmu1[e] = prm[o.muw + kHid + lane * 4 + e];
     wv[e] = prm[o.vw + lane * 4 + e];
   }
+  __syncthreads();
   const float bmu0 = prm[o.mub], bmu1 = prm[o.mub + 1], bv = prm[o.vb];
-  for (int rr = 0; rr < kTailRows / 4; ++rr) {
-    const int r = 4 * wave + rr;
-    const int64_t row = row0 + r;
-    if (row >= B) break;
-    const float4 zz = *reinterpret_cast<const float4*>(s_z + r * kTailLdZ + lane * 4);
+#pragma unroll
+  for (int rr = 0; rr < kTailPer; ++rr) {
+    const int64_t row = row0 + wrow + rr;
+    const float4 zz = *reinterpret_cast<const float4*>(s_z + (wrow + rr) * kTailLdZ + lane * 4);
     const float z[4] = {zz.x, zz.y, zz.z, zz.w};
     float s0 = 0, s1 = 0, sv = 0;
 #pragma unroll
@@ -800,7 +816,7 @@ __global__ __launch_bounds__(256) void k_fwd_tail(const float* prm, Offsets o, c
       sv += __shfl_xor(sv, off, 64);
     }
     const float e0 = __shfl(my_eps, 2 * rr, 64), e1 = __shfl(my_eps, 2 * rr + 1, 64);
-    if (lane == 0) {
+    if (lane == 0 && row < B) {
       const float m0 = s0 + bmu0, m1 = s1 + bmu1;
       if (mu_out) {
         mu_out[2 * row] = m0;

@@ -438,6 +438,29 @@ def test_forward_unsplit_fc1_sampled_rows():
     assert eb < 2e-3
 
 
+@pytest.mark.parametrize("B,rays", [(1, R), (129, R), (2049, 257), (6143, 1), (35001, R)])
+def test_split_forward_fc1_slices_sampled_rows(B, rays):
+    """The split forward's FC1 slices from 67 down to one (35001 rows: one slice of all rows), rows past a tile and
+    columns past a stage, both widths of the tail: up to 64 sampled rows against the exact FP64 network, per
+    element within the split forward's 1e-4."""
+    from paper_2603_25834_amd.policy import Policy
+    theta = synth.init_policy_params(rays, 15)
+    d = synth.policy_batch(B, rays, 15)
+    say(f"[policy] split forward B={B} rays={rays} (sampled rows)")
+    pol = Policy(rays, max_batch=B, precision=1)
+    mu, value = pol.forward(torch.from_numpy(theta).cuda(), *(torch.from_numpy(d[k]).cuda() for k in ("crop", "scan", "state")))
+    torch.cuda.synchronize()
+    rows = np.sort(np.random.default_rng(15).choice(B, min(B, 64), replace=False))
+    rows[-1] = B - 1
+    sub = {k: torch.from_numpy(d[k][rows]) for k in ("crop", "scan", "state")}
+    with torch.no_grad():
+        m, _, v = PR.forward(torch.from_numpy(theta).double(), sub["crop"], sub["scan"], sub["state"],
+                             PR.PolicyShape(n_scan=rays))
+    for got, want in ((mu, m), (value, v)):
+        err, ok = _elementwise(got.cpu().numpy()[rows], want.numpy(), 1e-4)
+        assert ok, err
+
+
 def test_backward_rows_equals_gathered_backward():
     """A minibatch given as rows of rollout-sized arrays gives bit-identical gradients and loss terms to the
     same minibatch gathered into its own arrays first."""
