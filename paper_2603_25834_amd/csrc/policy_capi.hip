@@ -581,7 +581,7 @@ int aslam_policy_backward_rows(aslam_policy* P, const float* params, const int16
   // heads + loss -> dz2, head / fc2-bias / log-std partial sums
   const int nb = (B + kHeadRows - 1) / kHeadRows;
   LossCoef lc{P->cfg.clip_eps, P->cfg.c_value, P->cfg.c_entropy, 1.0f / (float)B};
-  k_heads<true><<<nb, 256, 0, st>>>(params, o, P->z2, B, nullptr, nullptr, act, old_logp, adv, ret, rows, lc, P->dz2,
+  k_heads<true><<<nb, kHeadThreads, 0, st>>>(params, o, P->z2, B, nullptr, nullptr, act, old_logp, adv, ret, rows, lc, P->dz2,
                                     P->hpart);
   PCHK(hipGetLastError());
   PCHK(launch_reduce_heads(P->hpart, nb, params, o, grads, loss, P->cfg.c_value, P->cfg.c_entropy, st));
@@ -790,7 +790,7 @@ int aslam_policy_backward_seq(aslam_policy* P, const float* params, const int16_
   // heads + loss on every sample -> dh (FP32), head / log-std partial sums
   const int nh = (B + kHeadRows - 1) / kHeadRows;
   LossCoef lc{P->cfg.clip_eps, P->cfg.c_value, P->cfg.c_entropy, 1.0f / (float)B};
-  k_heads<true, true><<<nh, 256, 0, st>>>(params, o, P->hst, B, nullptr, nullptr, act, old_logp, adv, ret, P->rows,
+  k_heads<true, true><<<nh, kHeadThreads, 0, st>>>(params, o, P->hst, B, nullptr, nullptr, act, old_logp, adv, ret, P->rows,
                                           lc, nullptr, P->hpart, P->dh_head);
   PCHK(hipGetLastError());
   PCHK(launch_reduce_heads(P->hpart, nh, params, o, grads, loss, P->cfg.c_value, P->cfg.c_entropy, st));

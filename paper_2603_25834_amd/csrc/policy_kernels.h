@@ -180,16 +180,19 @@ struct LossCoef {
 // the head parameter gradients, dlog_std and the loss terms, in `part`:
 // [Wmu 512 | bmu 2 | wv 256 | bv 1 | dlogstd 2 | db2 256 | loss 4] floats.
 constexpr int kHeadPart = 512 + 2 + 256 + 1 + 2 + 256 + 4;
-constexpr int kHeadRows = 64;   // rows per workgroup (16 per wave)
+// What bounds it is a row's chain of six shuffle rounds and the loss: sixteen waves take four rows each, interleaved
+// (four waves of sixteen rows one after another: 15.7 us at 96 rows and 18.2 at 9000; this: 8.7 and 11.4).
+constexpr int kHeadRows = 64;   // rows per workgroup
+constexpr int kHeadWaves = 16, kHeadThreads = 64 * kHeadWaves;
 
 // RECUR: the heads read the GRU state directly (no ReLU) and, with GRAD, write its gradient dh (FP32)
 // to dh_out instead of the masked BF16 dz2.
 template <bool GRAD, bool RECUR = false>
-__global__ __launch_bounds__(256) void k_heads(const float* prm, Offsets o, const float* z2, int B, float* mu_out,
+__global__ __launch_bounds__(kHeadThreads) void k_heads(const float* prm, Offsets o, const float* z2, int B, float* mu_out,
                                                float* v_out, const float* act, const float* old_logp,
                                                const float* adv, const float* ret, const int32_t* rows, LossCoef lc,
                                                uint16_t* dz2, float* part, float* dh_out = nullptr) {
-  __shared__ float acc[4][kHeadPart];
+  __shared__ float acc[kHeadWaves][kHeadPart];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   float wmu0[4], wmu1[4], wv[4];
 #pragma unroll
@@ -203,9 +206,9 @@ __global__ __launch_bounds__(256) void k_heads(const float* prm, Offsets o, cons
   float gw0[4] = {0, 0, 0, 0}, gw1[4] = {0, 0, 0, 0}, gwv[4] = {0, 0, 0, 0}, gb2[4] = {0, 0, 0, 0};
   float gbm0 = 0, gbm1 = 0, gbv = 0, gls0 = 0, gls1 = 0, lclip = 0, lval = 0;
   const float log2pi = 1.8378770664093453f;
-  // the wave's 16 rows: lane j < 16 fetches row j's rollout data up front (handed out by shuffles), and
-  // all 16 rows of z2 are loaded up front (one memory round trip for the wave)
-  constexpr int kWaveRows = kHeadRows / 4;
+  // the wave's rows: lane j fetches row j's rollout data up front (handed out by shuffles), and all rows of
+  // z2 are loaded up front (one memory round trip for the wave); rows past B add zeros
+  constexpr int kWaveRows = kHeadRows / kHeadWaves;
   const int wrow0 = blockIdx.x * kHeadRows + wave * kWaveRows;
   float q_a0 = 0.f, q_a1 = 0.f, q_olp = 0.f, q_adv = 0.f, q_ret = 0.f;
   if (GRAD && lane < kWaveRows && wrow0 + lane < B) {
@@ -223,8 +226,8 @@ __global__ __launch_bounds__(256) void k_heads(const float* prm, Offsets o, cons
 #pragma unroll
   for (int rr = 0; rr < kWaveRows; ++rr) {
     const int row = wrow0 + rr;
-    if (row >= B) break;
-    const float4 zz = zr[rr];
+    const bool in = row < B;
+    const float4 zz = in ? zr[rr] : make_float4(0.f, 0.f, 0.f, 0.f);
     const float z[4] = {zz.x, zz.y, zz.z, zz.w};
     float h[4], s0 = 0, s1 = 0, sv = 0;
 #pragma unroll
@@ -242,7 +245,7 @@ __global__ __launch_bounds__(256) void k_heads(const float* prm, Offsets o, cons
     }
     const float m0 = s0 + bmu0, m1 = s1 + bmu1, val = sv + bv;
     if (!GRAD) {
-      if (lane == 0) {
+      if (lane == 0 && in) {
         mu_out[2 * (int64_t)row] = m0;
         mu_out[2 * (int64_t)row + 1] = m1;
         v_out[row] = val;
@@ -260,10 +263,10 @@ __global__ __launch_bounds__(256) void k_heads(const float* prm, Offsets o, cons
     const float surr = fminf(ratio * A, clipped * A);
     // d(-surr)/dlogp is -A*ratio when the unclipped term is the minimum, else 0
     const bool active = ratio * A <= clipped * A;
-    const float g_logp = active ? -A * ratio * lc.inv_b : 0.0f;
-    const float dm0 = g_logp * (u0 * is0), dm1 = g_logp * (u1 * is1);
-    const float dV = lc.c_v * 2.0f * (val - rt) * lc.inv_b;
-    if (lane == 0) {
+    const float g_logp = active && in ? -A * ratio * lc.inv_b : 0.0f;
+    const float dm0 = in ? g_logp * (u0 * is0) : 0.0f, dm1 = in ? g_logp * (u1 * is1) : 0.0f;
+    const float dV = in ? lc.c_v * 2.0f * (val - rt) * lc.inv_b : 0.0f;
+    if (lane == 0 && in) {
       gls0 += g_logp * (u0 * u0 - 1.0f);
       gls1 += g_logp * (u1 * u1 - 1.0f);
       gbm0 += dm0;
@@ -286,6 +289,7 @@ __global__ __launch_bounds__(256) void k_heads(const float* prm, Offsets o, cons
       gb2[e] += bf2f((uint16_t)bits);  // the bias gradient sums the same BF16 values the GEMMs consume
       if (e & 1) dzp[e >> 1] |= bits << 16; else dzp[e >> 1] = bits;
     }
+    if (!in) continue;
     if (RECUR)
       *reinterpret_cast<float4*>(dh_out + (int64_t)row * kHid + lane * 4) = make_float4(dhv[0], dhv[1], dhv[2], dhv[3]);
     else
@@ -305,8 +309,12 @@ __global__ __launch_bounds__(256) void k_heads(const float* prm, Offsets o, cons
     a[1029] = lclip; a[1030] = lval; a[1031] = 0.0f; a[1032] = 0.0f;
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < kHeadPart; i += 256)
-    part[(int64_t)blockIdx.x * kHeadPart + i] = acc[0][i] + acc[1][i] + acc[2][i] + acc[3][i];
+  for (int i = threadIdx.x; i < kHeadPart; i += kHeadThreads) {
+    float sum = acc[0][i];
+#pragma unroll
+    for (int w = 1; w < kHeadWaves; ++w) sum += acc[w][i];
+    part[(int64_t)blockIdx.x * kHeadPart + i] = sum;
+  }
 }
 
 // Sum of split-K partials part[z * slice + i], z < S, in a fixed order, added
