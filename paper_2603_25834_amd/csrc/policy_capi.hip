@@ -146,11 +146,13 @@ int64_t part_need(const aslam_policy* p) {
   } while (0)
 
 // The MLP policy's weight preparation in one launch, the jobs taken by workgroup ranges in this order:
-// kPrepW1 workgroups convert W1 (and its lo part), kPrepW2 convert W2, then with `transposed` the
-// 32 x 32 tiles of W1's conv-feature columns and of W2 transposed, and the last workgroup forms the
-// encoder's fragments (the forward's, with PREC their lo parts, with `transposed` the backward's phase
-// fragments).  Each job does what its own kernel (k_convert_bf16, k_transpose_bf16, k_conv_frags,
-// k_conv_bwd_frags) does, value for value; one launch instead of up to seven per parameter update.
+// kPrepFrags form the encoder's fragments, an element a thread (the forward's, with PREC their lo parts, with
+// `transposed` the backward's phase fragments: gathers, so they start first; as one last workgroup's loop they
+// were the launch's tail: 15.5 us, now 9), kPrepW1 convert W1 (and its lo part), kPrepW2 convert W2, then with
+// `transposed` the 32 x 32 tiles of W1's conv-feature columns and of W2 transposed.  Each job does what its own
+// kernel (k_convert_bf16, k_transpose_bf16, k_conv_frags, k_conv_bwd_frags) does, value for value; one launch
+// instead of up to seven per parameter update.
+constexpr int kPrepFrags = (64 * (2 * kConvFrags + kConvPhaseFrags) + 255) / 256;
 constexpr int kPrepW1 = 1024, kPrepW2 = 256;
 constexpr int kPrepT1 = (kFeat / 32) * (kHid / 32), kPrepT2 = (kHid / 32) * (kHid / 32);
 
@@ -159,6 +161,18 @@ __global__ __launch_bounds__(256) void k_prep_mlp(const float* __restrict__ prm,
                                                   uint16_t* w1t, uint16_t* w2t, uint4* cfrag, int transposed) {
   __shared__ float tile[32][33];
   int b = blockIdx.x;
+  if (b < kPrepFrags) {
+    int t = b * 256 + threadIdx.x;
+    if (t < 64 * kConvFrags) {
+      conv_frag_elem<false>(prm, o, cfrag, t);
+    } else if ((t -= 64 * kConvFrags) < 64 * kConvFrags) {
+      if (w1b_lo) conv_frag_elem<true>(prm, o, cfrag + 64 * kConvLoFrag, t);
+    } else if ((t -= 64 * kConvFrags) < 64 * kConvPhaseFrags) {
+      if (transposed) conv_bwd_frag_elem(prm, o, cfrag, t);
+    }
+    return;
+  }
+  b -= kPrepFrags;
   if (b < kPrepW1) {
     convert_bf16_part(prm + o.f1w, o.k1, kHid, o.k1, w1b, k1p, w1b_lo, b, kPrepW1);
     return;
@@ -175,16 +189,8 @@ __global__ __launch_bounds__(256) void k_prep_mlp(const float* __restrict__ prm,
       return;
     }
     b -= kPrepT1;
-    if (b < kPrepT2) {
-      transpose_bf16_tile(prm + o.f2w, kHid, kHid, kHid, w2t, kHid, tile, b % (kHid / 32), b / (kHid / 32));
-      return;
-    }
+    transpose_bf16_tile(prm + o.f2w, kHid, kHid, kHid, w2t, kHid, tile, b % (kHid / 32), b / (kHid / 32));
   }
-  for (int t = threadIdx.x; t < 64 * kConvFrags; t += 256) conv_frag_elem<false>(prm, o, cfrag, t);
-  if (w1b_lo)
-    for (int t = threadIdx.x; t < 64 * kConvFrags; t += 256) conv_frag_elem<true>(prm, o, cfrag + 64 * kConvLoFrag, t);
-  if (transposed)
-    for (int t = threadIdx.x; t < 64 * kConvPhaseFrags; t += 256) conv_bwd_frag_elem(prm, o, cfrag, t);
 }
 
 // BF16 copies of W1 (rows padded to k1p) and W2 and the encoder's weight fragments that the forward
@@ -214,7 +220,7 @@ int convert_weights(aslam_policy* P, const float* prm, hipStream_t st, bool tran
     P->prepared = true;
     return ASL_OK;
   }
-  const int blocks = kPrepW1 + kPrepW2 + (transposed ? kPrepT1 + kPrepT2 : 0) + 1;
+  const int blocks = kPrepFrags + kPrepW1 + kPrepW2 + (transposed ? kPrepT1 + kPrepT2 : 0);
   k_prep_mlp<<<blocks, 256, 0, st>>>(prm, o, P->k1p, P->w1b, P->prec ? P->w1b_lo : nullptr, P->w2b,
                                      P->prec ? P->w2b_lo : nullptr, P->w1t, P->w2t, P->cfrag, transposed ? 1 : 0);
   PCHK(hipGetLastError());
