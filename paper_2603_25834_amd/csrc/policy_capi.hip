@@ -112,27 +112,37 @@ int weight_slices(int64_t rows, int T, int tiles, int64_t max_slices) {
   return best;
 }
 
-// dst[n][k] += sum_m d[m][n] x[m][k].  256 x 256 tiles read FC1's large operand once, but leave the chip idle
+// Gradient at `off`, [n][k] += sum_m d[m][n] x[m][k], its partial sums in `part` for `red`.  256 x 256 tiles read FC1's large operand once, but leave the chip idle
 // where there are few of them or few rows (GEMM and reduction, us, small / large tiles: FC1's weight 19 / 28 at 96 rows,
 // 27 / 29 at 750, 37 / 43 at 3000, 81 / 74 at 9000; FC2's at 9000 rows 16 / 22, one of the GRU's 21 / 24).
-hipError_t weight_grad(aslam_policy* P, const gemm_tn::Operands& g, int64_t max_slices, float* dst, hipStream_t st) {
+hipError_t weight_grad(const gemm_tn::Operands& g, int64_t max_slices, float* part, int64_t off, Reducer& red,
+                       hipStream_t st) {
   constexpr int kLargeTiles = 32, kLargeRows = 6144;
   const int T = gemm_tn::tiles(g.N, g.K, 256) >= kLargeTiles && g.M >= kLargeRows ? 256 : 128;
   const int S = weight_slices(g.M, T, gemm_tn::tiles(g.N, g.K, T), max_slices);
-  const hipError_t e = gemm_tn::run(g, P->part, T, S, st);
-  if (e != hipSuccess) return e;
-  const int64_t n = (int64_t)g.N * g.K;
-  return launch_reduce(P->part, gemm_tn::slices(g.M, S), n, dst, 0, n, st);
+  red.add(part, gemm_tn::slices(g.M, S), (int64_t)g.N * g.K, off);
+  return gemm_tn::run(g, part, T, S, st);
+}
+
+// Where a backward pass leaves the partial sums of its weight and bias gradients (reduced in one launch at its
+// end): FC1's weight, FC2's or the GRU's W_ih, W_hh, the GRU's biases, FC1's bias, the encoder's.
+struct PartRegions {
+  int64_t w1, w2, whh, gb, b1, conv, total;
+};
+
+PartRegions part_regions(const aslam_policy* p) {
+  PartRegions r{};
+  r.w2 = kFc1Splits * 256 * p->off.k1;
+  r.whh = r.w2 + kFc2Splits * (p->rec ? kGates : kHid) * kHid;
+  r.gb = r.whh + (p->rec ? (int64_t)kFc2Splits * kGates * kHid : 0);
+  r.b1 = r.gb + (p->rec ? std::max<int64_t>(256, (p->max_b + 15) / 16) * 2 * kGates : 0);
+  r.conv = r.b1 + (int64_t)kBiasBlocks * 256;
+  r.total = r.conv + (int64_t)kConvBwdGrid * kConvPart;
+  return r;
 }
 
 int64_t part_need(const aslam_policy* p) {
-  const int64_t k1 = p->off.k1;
-  int64_t need = kFc1Splits * 256 * k1;                      // FC1 weight partials
-  need = std::max<int64_t>(need, kFc2Splits * kHid * kHid);   // FC2 weight partials
-  if (p->rec) need = std::max<int64_t>(need, (int64_t)kFc2Splits * kGates * kHid);   // GRU weight partials
-  if (p->rec) need = std::max<int64_t>(need, std::max<int64_t>(256, (p->max_b + 15) / 16) * 2 * kGates);   // GRU bias partials
-  need = std::max<int64_t>(need, (int64_t)kConvBwdGrid * kConvPart);   // encoder backward partials
-  need = std::max<int64_t>(need, (int64_t)kBiasBlocks * 256);
+  int64_t need = part_regions(p).total;
   need = std::max<int64_t>(need, (int64_t)kFc1MinBlocks * 64 * kHid);   // FC1 forward split-K: S * B <= 512 * 64
   if (p->prec)   // the three products of a split FC1, over z (S * B <= 512 * 64 each, or one slice of more rows)
     need = std::max<int64_t>(need, 3 * std::max<int64_t>((int64_t)kFc1MinBlocks * 64, p->max_b) * kHid);
@@ -347,7 +357,7 @@ int act_core(aslam_policy* P, const float* prm, bool prepared, const int16_t* cr
 }
 
 int backward_fc1_encoder(aslam_policy* P, const float* params, const int16_t* crop, const int32_t* rows, int B,
-                         float* grads, hipStream_t st);
+                         Reducer& red, float* grads, hipStream_t st);
 
 }  // namespace
 
@@ -591,13 +601,14 @@ int aslam_policy_backward_rows(aslam_policy* P, const float* params, const int16
                                     P->hpart);
   PCHK(hipGetLastError());
   PCHK(launch_reduce_heads(P->hpart, nb, params, o, grads, loss, P->cfg.c_value, P->cfg.c_entropy, st));
-  float* part = P->part;
   // FC2 weight: dW2[out][in] = sum_b dz2[b][out] h1[b][in]
-  PCHK(weight_grad(P, gemm_tn::Operands{P->dz2, kHid, kHid, P->h1, kHid, kHid, B}, kFc2Splits, grads + o.f2w, st));
+  const PartRegions pr = part_regions(P);
+  Reducer red;
+  PCHK(weight_grad(gemm_tn::Operands{P->dz2, kHid, kHid, P->h1, kHid, kHid, B}, kFc2Splits, P->part + pr.w2, o.f2w, red, st));
   // dh1 -> dz1 = (dz2 W2) * [h1 > 0]
   PCHK((gemm::run<128, 128, 64, 2, 2>(LdBF16K{P->dz2, kHid, B, kHid}, LdBF16K{P->w2t, kHid, kHid, kHid},
                                      EpiReluGradBF16{P->dz1, P->h1, kHid, kHid}, B, kHid, kHid, 1, st)));
-  return backward_fc1_encoder(P, params, crop, rows, B, grads, st);
+  return backward_fc1_encoder(P, params, crop, rows, B, red, grads, st);
 }
 
 }  // extern "C"
@@ -607,29 +618,29 @@ namespace {
 // Everything below the FC1 output gradient dz1 (BF16, already masked by FC1's ReLU): the FC1 bias and
 // weight gradients, the conv-feature gradient and the encoder backward.
 int backward_fc1_encoder(aslam_policy* P, const float* params, const int16_t* crop, const int32_t* rows, int B,
-                         float* grads, hipStream_t st) {
+                         Reducer& red, float* grads, hipStream_t st) {
   const Offsets& o = P->off;
-  float* part = P->part;
+  const PartRegions pr = part_regions(P);
   // FC1 bias
-  k_bias_rows<<<kBiasBlocks, 256, 0, st>>>(P->dz1, B, kHid, part);
+  k_bias_rows<<<kBiasBlocks, 256, 0, st>>>(P->dz1, B, kHid, P->part + pr.b1);
   PCHK(hipGetLastError());
-  PCHK(launch_reduce(part, kBiasBlocks, kHid, grads + o.f1b, 0, kHid, st));
+  red.add(P->part + pr.b1, kBiasBlocks, kHid, o.f1b);
   // FC1 weight: dW1[out][k] = sum_b dz1[b][out] X[b][k]
-  PCHK(weight_grad(P, gemm_tn::Operands{P->dz1, kHid, kHid, P->x, P->k1p, o.k1, B}, kFc1Splits, grads + o.f1w, st));
+  PCHK(weight_grad(gemm_tn::Operands{P->dz1, kHid, kHid, P->x, P->k1p, o.k1, B}, kFc1Splits, P->part + pr.w1, o.f1w, red, st));
   // dA2 -> dz2c = (dz1 W1[:, :8192]) * [a2 > 0]
   PCHK(gemm_nt::feature_grad(P->dz1, P->w1t, reinterpret_cast<const uint8_t*>(P->amask), P->dz2c, B, kFeat, st));
   // encoder: conv2 / conv1 weight and bias gradients in one pass over the minibatch
   {
     const int grid = std::min(B, kConvBwdGrid);
     if (P->prec)
-      k_conv_bwd<true><<<grid, kBwdThreads, 0, st>>>(params, o, P->cfrag, crop, rows, P->dz2c, B, part);
+      k_conv_bwd<true><<<grid, kBwdThreads, 0, st>>>(params, o, P->cfrag, crop, rows, P->dz2c, B, P->part + pr.conv);
     else
-      k_conv_bwd<false><<<grid, kBwdThreads, 0, st>>>(params, o, P->cfrag, crop, rows, P->dz2c, B, part);
+      k_conv_bwd<false><<<grid, kBwdThreads, 0, st>>>(params, o, P->cfrag, crop, rows, P->dz2c, B, P->part + pr.conv);
     PCHK(hipGetLastError());
-    // the four gradient blocks of the encoder's partials in one reduction
     const ReduceSegs sg{{kConvPartW2, kConvPartW1, kC1, kC2}, {1, 2, 0, 0}, {o.c2w, o.c1w, o.c1b, o.c2b}};
-    PCHK(launch_reduce_segs(part, grid, grads, sg, kConvPart, st));
+    red.add(P->part + pr.conv, grid, kConvPart, sg);
   }
+  PCHK(red.launch(grads, st));
   return ASL_OK;
 }
 
@@ -801,21 +812,21 @@ int aslam_policy_backward_seq(aslam_policy* P, const float* params, const int16_
   PCHK(hipGetLastError());
   PCHK(launch_reduce_heads(P->hpart, nh, params, o, grads, loss, P->cfg.c_value, P->cfg.c_entropy, st));
   // backpropagation through time, and the GRU biases' column sums
-  float* part = P->part;
+  const PartRegions pr = part_regions(P);
+  Reducer red;
   uint16_t* const dgi = P->dg;
   uint16_t* const dgh = P->dg + (int64_t)B * kGates;
-  a.whh = P->whht; a.dh_head = P->dh_head; a.dgi = dgi; a.dgh = dgh; a.part = part;
+  a.whh = P->whht; a.dh_head = P->dh_head; a.dgi = dgi; a.dgh = dgh; a.part = P->part + pr.gb;
   (rpl == 1 ? k_gru_seq_bwd<1> : rpl == 2 ? k_gru_seq_bwd<2> : k_gru_seq_bwd<4>)<<<tiles, kGruSeqThreads, kGruSeqBwdLds, st>>>(a);
   PCHK(hipGetLastError());
-  PCHK(launch_reduce_segs(part, (int)tiles, grads, ReduceSegs{{kGates, kGates, 0, 0}, {0, 0, 0, 0}, {o.gbi, o.gbh, 0, 0}},
-                          2 * kGates, st));
+  red.add(P->part + pr.gb, (int)tiles, 2 * kGates, ReduceSegs{{kGates, kGates, 0, 0}, {0, 0, 0, 0}, {o.gbi, o.gbh, 0, 0}});
   // GRU weights: dW_ih = sum_s dgi[s] h1[s]^T, dW_hh = sum_s dgh[s] hp[s]^T
-  PCHK(weight_grad(P, gemm_tn::Operands{dgi, kGates, kGates, P->h1, kHid, kHid, B}, kFc2Splits, grads + o.gih, st));
-  PCHK(weight_grad(P, gemm_tn::Operands{dgh, kGates, kGates, P->hp_bf, kHid, kHid, B}, kFc2Splits, grads + o.ghh, st));
+  PCHK(weight_grad(gemm_tn::Operands{dgi, kGates, kGates, P->h1, kHid, kHid, B}, kFc2Splits, P->part + pr.w2, o.gih, red, st));
+  PCHK(weight_grad(gemm_tn::Operands{dgh, kGates, kGates, P->hp_bf, kHid, kHid, B}, kFc2Splits, P->part + pr.whh, o.ghh, red, st));
   // FC1 output gradient: dz1 = (dgi W_ih) * [h1 > 0]
   PCHK((gemm::run<128, 128, 64, 2, 2>(LdBF16K{dgi, kGates, B, kGates}, LdBF16K{P->wiht, kGates, kHid, kGates},
                                      EpiReluGradBF16{P->dz1, P->h1, kHid, kHid}, B, kHid, kGates, 1, st)));
-  return backward_fc1_encoder(P, params, crop, P->rows, B, grads, st);
+  return backward_fc1_encoder(P, params, crop, P->rows, B, red, grads, st);
 }
 
 }  // extern "C"
