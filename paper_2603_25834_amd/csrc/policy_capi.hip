@@ -310,10 +310,7 @@ int forward_core(aslam_policy* P, const float* prm, const int16_t* crop, const f
   rc = encode_fc1(P, prm, crop, scan, state, rows, B, st, &S, true);
   if (rc) return rc;
   if (S > 0) {
-    const int64_t groups = (int64_t)B * (kHid / 8);
-    k_reduce_bias_relu_bf16<<<(int)std::min<int64_t>(4096, (groups + 255) / 256), 256, 0, st>>>(
-        P->part, S, B, kHid, prm + o.f1b, P->h1, kHid, P->prec ? P->h1_lo : nullptr);
-    PCHK(hipGetLastError());
+    PCHK(launch_reduce_relu(P->part, S, B, prm + o.f1b, P->h1, P->prec ? P->h1_lo : nullptr, st));
   }
   const LdBF16K ha{P->h1, kHid, B, kHid}, wb{P->w2b, kHid, kHid, kHid};
   if (P->prec) {
@@ -785,10 +782,7 @@ int aslam_policy_backward_seq(aslam_policy* P, const float* params, const int16_
   rc = encode_fc1(P, params, crop, scan, state, P->rows, B, st, &S, true);
   if (rc) return rc;
   if (S > 0) {
-    const int64_t groups = (int64_t)B * (kHid / 8);
-    k_reduce_bias_relu_bf16<<<(int)std::min<int64_t>(4096, (groups + 255) / 256), 256, 0, st>>>(
-        P->part, S, B, kHid, params + o.f1b, P->h1, kHid);
-    PCHK(hipGetLastError());
+    PCHK(launch_reduce_relu(P->part, S, B, params + o.f1b, P->h1, nullptr, st));
   }
   // the GRU over the T steps: the input products of every sample at once, then the recurrence, keeping
   // what the backward reads
