@@ -215,7 +215,7 @@ int plan_lds(aslam_env* e, const aslam_exec_config& ex, LdsPlan& L) {
   const int32_t lc = e->P.lclamp;
   const int32_t rhat_cells = e->P.rhat_cells;
   L.off_lut = 0;
-  L.off_rho = (int32_t)align_up((2 * lc + 1) * 4, 16);
+  L.off_rho = (int32_t)align_up((2 * lc + 2) * 4, 16);   // EnvParams::miss_tab
   L.off_perm = L.off_rho + (int32_t)align_up(e->cfg.n_rays * 4, 16);
   L.off_seg = L.off_perm + (int32_t)align_up(e->cfg.n_rays * 4, 16);
   L.off_hist = L.off_seg + (int32_t)align_up(e->cfg.n_rays * 4, 16);
@@ -235,27 +235,28 @@ int plan_lds(aslam_env* e, const aslam_exec_config& ex, LdsPlan& L) {
   const int64_t free_bytes = budget - L.off_union;
   if (world_max > free_bytes)
     return fail(ASL_ENOTIMPL, "world window of the largest grid does not fit the LDS budget");
-  // bitmap: band x nw words, cleared with 16-byte stores (+16 B slack), then the waves' octet lists.  A
-  // budget holds a band of 8 rows when 64 bytes for each word of a row are left.
-  const int64_t list_bytes = (int64_t)(ex.threads / 64) * kApplyList * 2;
-  const int64_t fit = std::max<int64_t>((free_bytes - list_bytes - 32) / (4 * nw_max), (free_bytes - 16) / (8 * nw_max));
-  int64_t band = std::min<int64_t>({ex.band_rows > 0 ? (int64_t)ex.band_rows : fit, fit, rows_max});
-  if (band < 8 || 64 * nw_max + 16 > free_bytes)
-    return fail(ASL_EINVAL, "band_rows does not fit the LDS budget (need >= 8 rows)");
+  // One band's bitmap (band x nw words, whole 16-byte vectors) and the waves' octet lists.  The lists lie over
+  // perm and seg where those are free by then (the segmented walk) and large enough, else after the bitmap: a
+  // word lists at most four octets, so a band of few words needs no more than 8 bytes a word.  The largest band
+  // within the budget: where the world rows fit, 8 rows (96 bytes a word of a row) do.
+  const int64_t list_max = (int64_t)(ex.threads / 64) * kApplyList * 2;
+  const bool over = ex.mark_seg > 0 && L.off_hist - L.off_perm >= list_max;
+  auto bits_of = [&](int64_t rows) { return align_up(4 * rows * nw_max, 16); };
+  auto need = [&](int64_t rows) { return bits_of(rows) + (over ? 0 : std::min(list_max, 8 * rows * nw_max)); };
+  int64_t band = ex.band_rows > 0 ? std::min<int64_t>(ex.band_rows, rows_max) : rows_max;
+  while (band >= 8 && need(band) > free_bytes) --band;
+  if (band < 8) return fail(ASL_EINVAL, "band_rows does not fit the LDS budget (need >= 8 rows)");
   L.band_rows = (int32_t)band;
-  // The octet lists lie over perm and seg where those are free by then (the segmented walk) and large
-  // enough, else after the bitmap.  The bitmap takes the world rows' place, or its own where three
-  // workgroups still share a CU (their most: 80 registers a lane): cleared before the march then, a phase
-  // less between the march and the walk.
-  const int64_t bits = align_up(4 * band * nw_max, 16), world = align_up(world_max, 16);
-  const bool over = ex.mark_seg > 0 && L.off_hist - L.off_perm >= list_bytes;
-  const int64_t tail = bits + (over ? 0 : list_bytes);
+  // The bitmap takes the world rows' place, or its own where three workgroups still share a CU (their most: 80
+  // registers a lane): cleared before the march then, a phase less between the march and the walk.
+  const int64_t bits = bits_of(band), tail = need(band), world = align_up(world_max, 16);
   L.cleared = L.off_union + world + tail <= std::min<int64_t>(budget, e->lds_max / 3 / 1280 * 1280) ? 1 : 0;
   L.off_bits = L.off_union + (L.cleared ? (int32_t)world : 0);
   L.off_list = over ? L.off_perm : L.off_bits + (int32_t)bits;
   L.clear_vecs = (int32_t)(bits / 16);
   L.union_bytes = (int32_t)(L.cleared ? world + tail : std::max<int64_t>(world_max, tail));
   L.total = L.off_union + L.union_bytes;
+  if (L.total > budget) return fail(ASL_EINVAL, "the LDS plan exceeds its budget");
   L.record = ex.record_rays;
   L.mark_seg = ex.mark_seg;
   return ASL_OK;

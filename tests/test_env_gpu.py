@@ -247,3 +247,46 @@ def test_map_update_forms(monkeypatch, over, exec_kw):
         o = pr.step()
         if t % 3 == 0 or t == 29:
             pr.compare(o)
+
+
+@pytest.mark.parametrize("threads,mark_seg", [(512, 0), (128, 0), (512, 32), (256, 8)])
+def test_exec_lds_budget(monkeypatch, threads, mark_seg):
+    """The plan stays within the LDS budget that is asked for: every budget that holds the table, the rays and the
+    largest grid's world rows is taken (a smaller one refused), what get_exec reports is no more than the budget and
+    gives the same plan when it is set again, and the tightest budget's steps are the oracle's."""
+    from paper_2603_25834_amd import _lib
+    monkeypatch.setitem(synth.WORKLOADS, "mixed_12x32", synth.Workload(
+        "mixed_12x32", 12, (32, 64, 96), 0.25, 90, 10.0, 30, 0, rects=(2, 4), rect_side=(3, 8), thin_walls=(0, 0),
+        thin_len=(0, 0), scale_counts=False))
+    pr = Pair("mixed_12x32", 3, exec_kw=dict(form=1, threads=threads, record_rays=1), steps=16)
+    fixed = 7184 + 3 * 368 + 512                       # table, three arrays of 90 rays, sort buckets and shared state
+    least = fixed + (87 * 3 + 2 * 28) * 4              # 87 rows of 96 cells (40 of range, 3 more, both ways), the guards
+    tight = None
+    for budget in range(least - 64, least + 6000, 16):
+        kw = dict(form=1, threads=threads, record_rays=1, mark_seg=mark_seg, lds_bytes=budget)
+        if budget < least:
+            with pytest.raises(_lib.AslamError):
+                pr.env.set_exec(**kw)
+            continue
+        pr.env.set_exec(**kw)
+        got = pr.env.get_exec()
+        assert got["lds_bytes"] <= budget and got["band_rows"] >= 8, (budget, got)
+        pr.env.set_exec(**got)
+        assert pr.env.get_exec() == got, (budget, got)
+        tight = tight or got
+    for kw in (tight, dict(tight, band_rows=8)):
+        pr.env.set_exec(**kw)
+        say(f"[lds] {pr.env.get_exec()}")
+        for _ in range(8):
+            pr.compare(pr.step())
+
+
+def test_exec_lds_device_limit():
+    """The widest log-odds table and 2304 rays leave 4.5 KB of the device's LDS: the default plan stays within it and
+    its steps are the oracle's."""
+    from paper_2603_25834_amd.env import device_info
+    pr = Pair("small_16x64", 2, robots=np.arange(4), exec_kw=dict(form=1, threads=512, record_rays=1), steps=4,
+              params_over=dict(l_clamp=64.0, n_rays=2304))
+    assert pr.env.get_exec()["lds_bytes"] <= device_info()[0]
+    for _ in range(4):
+        pr.compare(pr.step())
