@@ -141,6 +141,57 @@ def test_match_far_centres_and_offsets():
     assert got[3][5] == int(np.sum(rho[3] >= 0))        # the far rays count as used rays
 
 
+@pytest.mark.parametrize("sides,max_side,W,V,R", [([300, 64, 128], None, 4, 5, 360), ([256, 64, 200, 96], 16, 4, 5, 360),
+                                                  ([100, 64, 37, 300], 48, 2, 1, 90), ([64, 300, 4096], 1, 1, 0, 70)],
+                         ids=["grid_too_big_for_lds", "many_bands", "sides_not_multiple_of_8", "global_rows"])
+def test_match_fractional_steps_staged_and_global(sides, max_side, W, V, R):
+    """Lattices of fractional-cell steps, at most 9 translations per axis: grids staged whole, in bands of rows, with
+    sides of any residue, or read from global memory (a box row wider than the LDS sized for max_side): the oracle's
+    answers (exact)."""
+    sxy, sh = 40000, 64
+    grids, belief, cell_off, side, pose, rho, a_off = _batch(29 + R, sides, R, W, V, sxy, sh)
+    if max_side == 1:
+        rho[2] = (np.random.default_rng(3).uniform(100.0, 3000.0, R) * 65536).astype(np.int32)   # a wide box
+        pose[2, :2] = 2048 * 65536 + 300
+    cfg = slam.csm_config(W, V, sxy, sh)
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    say(f"[slam] csm step {sxy} sides={sides} max_side={max_side}")
+    got = slam.csm_match(d(belief), d(cell_off), d(side), d(pose), d(rho), d(a_off), cfg, max_side=max_side)
+    torch.cuda.synchronize()
+    got = got.cpu().numpy()
+    trig = S._trig()
+    for r in range(len(sides)):
+        want = S.csm_match(grids[r], int(pose[r, 0]), int(pose[r, 1]), int(pose[r, 2]), rho[r], a_off, W, V, sxy, sh,
+                           trig)
+        assert tuple(int(v) for v in got[r]) == want, (r, got[r], want)
+
+
+@pytest.mark.parametrize("sxy", [65536, 40000])
+def test_match_far_centres_lattice_on_the_grid(sxy):
+    """Robots scored in 64 bits (centre beyond 2^28, offsets beyond 2^29) whose candidates' end cells do lie on their
+    grid: a centre past cell 4096 of a larger grid, one off the grid whose long rays reach back to it, rays without a
+    return among them; ordinary robots beside them (exact)."""
+    W, V, sh, R = 4, 3, 64, 97
+    sides = [4224, 96, 128, 4224, 64]
+    grids, belief, cell_off, side, pose, rho, a_off = _batch(92, sides, R, W, V, sxy, sh, invalid_p=0.2)
+    pose[0, :2] = (4150 * 65536 + 17, 4200 * 65536 + 40000)
+    pose[3, :2] = (4221 * 65536, 3 * 65536)
+    pose[1] = (9000 * 65536, 48 * 65536, NANG // 2)          # looks back at its grid from 9000 cells away
+    rho[1] = ((9000 - np.linspace(0, 96, R)) * 65536).astype(np.int32)
+    rho[1, 5::9] = -1
+    grids[1] = np.abs(grids[1])                               # its best candidate is one that sees the grid
+    belief[cell_off[1]:cell_off[2]] = grids[1].reshape(-1)
+    a_off = (a_off // 2000).astype(np.int32)                  # within a fifth of a degree of the heading
+    say(f"[slam] csm far centres on the grid step={sxy}")
+    got, _ = _gpu_match(belief, cell_off, side, pose, rho, a_off, W, V, sxy, sh)
+    trig = S._trig()
+    for r in range(len(sides)):
+        want = S.csm_match(grids[r], int(pose[r, 0]), int(pose[r, 1]), int(pose[r, 2]), rho[r], a_off, W, V, sxy, sh,
+                           trig)
+        assert tuple(int(v) for v in got[r]) == want, (r, got[r], want)
+        assert r not in (0, 1, 3) or want[3] != 0, r          # the far robots do score cells
+
+
 def test_factor_matches_oracle_exactly():
     W, V, sxy, sh, R = 4, 5, 32768, 48, 90
     sides = [64, 96, 128, 256, 32, 64]
