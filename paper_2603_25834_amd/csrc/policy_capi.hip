@@ -112,6 +112,23 @@ int weight_slices(int64_t rows, int T, int tiles, int64_t max_slices) {
   return best;
 }
 
+// k of an FC1 slice for the split forward with rt tiles of 128 rows: the workgroups (one per CU) take their rounds'
+// time, 64 k by 64 k, and 80 tiles of partial sums cost as much as such a step.  A length that only fills the CUs on
+// average leaves a few workgroups for a round of their own: the actor's call took 95 us with 448 k (260 workgroups)
+// at 1664 rows and 76 with 512 (221), 382 and 306 with 2176 and 2880 at 8320, 541 and 410 with 3264 and 1728 (two full
+// rounds) at 12288.  The partial sums stay within part_need's 3 x 32768 rows, or are one slice.
+int split_fc1_chunk(int k1p, int rt) {
+  constexpr int kSlots = 256, kTilesPerStep = 80, kMinChunk = 128, kMaxTiles = 3 * kFc1MinBlocks * 64 / 128;
+  int best = k1p, best_cost = INT_MAX;
+  for (int s = 1; s == 1 || (s * rt <= kMaxTiles && s * kMinChunk <= k1p + kMinChunk); ++s) {
+    const int chunk = std::max(kMinChunk, ((k1p + s - 1) / s + 63) / 64 * 64);
+    const int tiles = rt * ((k1p + chunk - 1) / chunk);
+    const int cost = kTilesPerStep * ((tiles + kSlots - 1) / kSlots) * (chunk / 64) + tiles;
+    if (cost < best_cost) { best = chunk; best_cost = cost; }
+  }
+  return std::min(best, k1p);
+}
+
 // Gradient at `off`, [n][k] += sum_m d[m][n] x[m][k], its partial sums in `part` for `red`.  256 x 256 tiles read FC1's large operand once, but leave the chip idle
 // where there are few of them or few rows (GEMM and reduction, us, small / large tiles: FC1's weight 19 / 28 at 96 rows,
 // 27 / 29 at 750, 37 / 43 at 3000, 81 / 74 at 9000; FC2's at 9000 rows 16 / 22, one of the GRU's 21 / 24).
@@ -259,12 +276,11 @@ int encode_fc1(aslam_policy* P, const float* prm, const int16_t* crop, const flo
   if (P->prec && tiles < 32) S = std::max(1, std::min(32, kFc1MinBlocks / (3 * tiles)));
   const int64_t slice = (int64_t)B * kHid;
   if (P->prec && !training) {
-    // Forward only: the three products summed by the workgroup, so that a slice is a third of the partial sums, and as
-    // many slices of at least 128 k as give every CU a workgroup (128 x 128 tiles with each product in slices of its
-    // own, GEMM and reduction: 14 us at 16 rows, 34 at 750, 75 at 2000, 228 at 8000; this: 12, 28, 43, 137).  The
-    // training pass keeps its slices: its ReLU signs, and so its gradients, follow their rounding.
-    const int64_t rt = (B + 127) / 128;
-    const int k_split = (int)std::min<int64_t>(P->k1p, std::max<int64_t>(128, (K1 * rt / 256 + 63) / 64 * 64));
+    // Forward only: the three products summed by the workgroup, so that a slice is a third of the partial sums (128 x
+    // 128 tiles with each product in slices of its own, GEMM and reduction: 14 us at 16 rows, 34 at 750, 75 at 2000,
+    // 228 at 8000; this: 12, 28, 43, 137).  The training pass keeps its slices: its ReLU signs, and so its gradients,
+    // follow their rounding.
+    const int k_split = split_fc1_chunk(P->k1p, (B + 127) / 128);
     PCHK(gemm_nt::run<3>(gemm_nt::Operands{P->x, P->x_lo, P->w1b, P->w1b_lo, P->k1p, P->k1p, B, kHid, P->k1p},
                          gemm_nt::EpiSum{{P->part, kHid, slice}}, k_split, st));
     *S_used = (int)((P->k1p + k_split - 1) / k_split);

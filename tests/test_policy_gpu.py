@@ -461,6 +461,13 @@ def test_split_forward_fc1_slices_sampled_rows(B, rays):
         assert ok, err
 
 
+@pytest.mark.parametrize("B,rays", [(1601, R), (8321, R), (16500, 180), (32700, R)])
+def test_split_forward_fc1_slices_in_rounds(B, rays):
+    """Row counts whose FC1 slices take one full round of workgroups, two (7 slices), three (5) and one slice of all
+    rows: the same bar."""
+    test_split_forward_fc1_slices_sampled_rows(B, rays)
+
+
 def test_backward_rows_equals_gathered_backward():
     """A minibatch given as rows of rollout-sized arrays gives bit-identical gradients and loss terms to the
     same minibatch gathered into its own arrays first."""
