@@ -336,6 +336,15 @@ def test_integrate_walk_segments(sides, R):
     _integrate_case(45 + R, sides, R, 1, 1, 65536, 64, 500 * 65536)
 
 
+@pytest.mark.parametrize("R", [64, 65, 449, 512, 1025])
+@pytest.mark.parametrize("max_side", [None, 48], ids=["one_band", "bands"])
+def test_integrate_ray_groups(R, max_side):
+    """Rays spread over the lanes and the groups (one band) or in their order (bands), at the edges of a wave, of a
+    group's waves and of a group: the oracle's grids (exact)."""
+    say(f"[slam] integrate ray groups R={R} max_side={max_side}")
+    _integrate_case(61 + R, [64, 320], R, 1, 0, 65536, 64, 60 * 65536, max_side=max_side)
+
+
 def test_integrate_many_rays_and_no_count():
     """More rays than the length sort takes (2100 > 2048: rays in their own order), and the call without
     the coded-cell output: same exact grids as the oracle."""
