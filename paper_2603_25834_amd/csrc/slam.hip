@@ -1154,9 +1154,9 @@ hipError_t launch_csm_match(const int32_t* tab, const int16_t* belief_dev, const
     const int64_t part_cells = (2 * (int64_t)ncand * chunks + 7) & ~(int64_t)7;
     if (step_xy_q == 65536 && W > 0) {
       // the whole grid between its zeros, the end cells beside it
-      const int64_t list_bytes = (int64_t)(2 * V + 1) * R * 4, pitch = ((max_side + 7) & ~7) + kCellPad;
+      const int64_t list_bytes = (int64_t)(2 * V + 1) * R * 4, pitch = (((int64_t)max_side + 7) & ~(int64_t)7) + kCellPad;
       const int64_t room = ((kCsmCellsBudget - list_bytes) / 2) & ~(int64_t)7;
-      const int64_t whole = (int64_t)(max_side + 4 * W + 1) * (pitch + ((pitch & 31) == 0 ? 8 : 0)) + kCellPad;
+      const int64_t whole = ((int64_t)max_side + 4 * W + 1) * (pitch + ((pitch & 31) == 0 ? 8 : 0)) + kCellPad;
       const int64_t cap_cells = std::max(part_cells, std::min(whole, room));
       const int bytes = (int)(2 * cap_cells + list_bytes);
       auto kernel = W == 1 ? k_csm_cells<1> : W == 2 ? k_csm_cells<2> : W == 3 ? k_csm_cells<3> : k_csm_cells<4>;

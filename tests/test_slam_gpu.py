@@ -166,6 +166,24 @@ def test_match_fractional_steps_staged_and_global(sides, max_side, W, V, R):
         assert tuple(int(v) for v in got[r]) == want, (r, got[r], want)
 
 
+@pytest.mark.parametrize("max_side", [0, 1, 2**31 - 8, 2**31 - 1])
+def test_match_any_bound_on_the_sides(max_side):
+    """max_side sizes the LDS only: no bound, one below the sides, and the largest give the oracle's answers (exact)."""
+    W, V, sxy, sh, R = 2, 1, 65536, 64, 70
+    sides = [64, 96, 37]
+    grids, belief, cell_off, side, pose, rho, a_off = _batch(93, sides, R, W, V, sxy, sh)
+    cfg = slam.csm_config(W, V, sxy, sh)
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    say(f"[slam] csm max_side={max_side}")
+    got = slam.csm_match(d(belief), d(cell_off), d(side), d(pose), d(rho), d(a_off), cfg, max_side=max_side)
+    torch.cuda.synchronize()
+    got, trig = got.cpu().numpy(), S._trig()
+    for r in range(len(sides)):
+        want = S.csm_match(grids[r], int(pose[r, 0]), int(pose[r, 1]), int(pose[r, 2]), rho[r], a_off, W, V, sxy, sh,
+                           trig)
+        assert tuple(int(v) for v in got[r]) == want, (r, got[r], want)
+
+
 @pytest.mark.parametrize("sxy", [65536, 40000])
 def test_match_far_centres_lattice_on_the_grid(sxy):
     """Robots scored in 64 bits (centre beyond 2^28, offsets beyond 2^29) whose candidates' end cells do lie on their
