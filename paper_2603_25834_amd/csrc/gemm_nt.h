@@ -414,12 +414,13 @@ inline hipError_t feature_grad(const uint16_t* dz, const uint16_t* wt, const uin
   if (M < 1 || N < kBN || N % kBN) return hipErrorInvalidValue;
   // Workgroups of 64, 128 or 256 features: few row tiles leave the chip idle with the wide ones, many reread
   // their rows in every slice.  64 / 128 / 256 features took 5.8 / 6.5 / 13 us at 96 rows, 7.0 / 7.6 / 14 at
-  // 200, 12 / 9.1 / 15 at 400, 20 / 15.4 / 16.6 at 800, 125 / 77 / 59 at 9000.
-  constexpr int kDxNarrow = 2, kDxMid = 4;
-  const int groups = std::min(8, (M + kBM - 1) / kBM);
-  if (groups <= kDxNarrow)
+  // 200, 12 / 9.1 / 15 at 400, 20 / 15.4 / 16.6 at 800, 125 / 77 / 59 at 9000; a whole minibatch 128.9 / 129.3 at 200
+  // rows and 135.7 / 133.3 at 257 (64 / 128 features), 161.8 / 162.5 at 800 and 169.4 / 168.2 at 1025 (128 / 256).
+  constexpr int kNarrowTiles = 2, kMidTiles = 7;
+  const int tiles = (M + kBM - 1) / kBM, groups = std::min(8, tiles);
+  if (tiles <= kNarrowTiles)
     k_feature_grad<1><<<(unsigned)(N / 64 * groups), 128, 0, st>>>(dz, wt, mask, out, M, N, groups);
-  else if (groups <= kDxMid)
+  else if (tiles <= kMidTiles)
     k_feature_grad<2><<<(unsigned)(N / 128 * groups), 256, 0, st>>>(dz, wt, mask, out, M, N, groups);
   else
     k_feature_grad<4><<<(unsigned)(N / kBN * groups), kThreads, 0, st>>>(dz, wt, mask, out, M, N, groups);

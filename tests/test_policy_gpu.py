@@ -231,6 +231,13 @@ def test_split_gradient_is_the_mean_of_its_pieces(b, pieces, rays):
         assert v < 1e-2, (k, v)
 
 
+@pytest.mark.parametrize("b", [640, 896, 897])
+def test_split_gradient_at_feature_width_edges(b):
+    """Pieces of five, seven and eight row tiles, around the last change of the feature gradient's workgroup width:
+    the same bar."""
+    test_split_gradient_is_the_mean_of_its_pieces(b, 2, R)
+
+
 def test_split_backward_against_central_differences_per_coordinate():
     """Split forward, random advantages, 64 samples: 64 sampled coordinates of every tensor (all of a
     smaller one) against FP64 central differences of the exact loss: the sampled sub-vector within
