@@ -731,11 +731,6 @@ __global__ __launch_bounds__(256) void k_transpose_bf16(const float* src, int64_
   transpose_bf16_tile(src, ld_src, rows, cols, dst, ld_dst, tile, blockIdx.x, blockIdx.y);
 }
 
-// Forward tail of a tile of kTailRows rows, for the forward-only calls: the FC1 split-K sum (slices in
-// order) + bias + ReLU rounded to BF16 (or the BF16 h1 rows when S == 0), FC2 on MFMA with the k
-// chunks in the GEMM engine's order, + bias, then the heads and, when eps is given, the Gaussian
-// action sample.  Every value is formed by the same operations in the same order as the unfused
-// sequence (split-K reduce, FC2 GEMM, k_heads, k_sample), so the outputs are bit-identical to it.
 // Standard normals of the Gaussian action sample: the caller's eps [B,2], or the library's own draw
 // of row b, dimension d at counter (counter, b, d) under key (seed, action domain).
 struct ActDraws {
@@ -750,14 +745,23 @@ constexpr int kTailRows = 16;
 constexpr int kTailLdH = kHid + 8;   // BF16 h1 rows in LDS, padded
 constexpr int kTailLdZ = kHid + 4;   // FP32 z2 rows in LDS, padded
 
+// Forward tail of a tile of kTailRows rows, for the forward-only calls: the sum of FC1's slices in their order + bias
+// + ReLU rounded to BF16 (or the BF16 h1 rows when S == 0: many slices are summed before, by
+// k_reduce_bias_relu_bf16_q, quarter by quarter), FC2 on MFMA with the k chunks in the GEMM engine's order, + bias,
+// then the heads and, when eps is given, the Gaussian action sample.  From h1 on every value is formed by the same
+// operations in the same order as in the training pass (FC2 GEMM, k_heads) and k_sample; FC1's sums are those of the
+// slices that the forward takes, for the split forward other ones than the training pass's.
 //
 // PREC (split operands): h1's lo parts ride along (h1lo rows, or formed from the slice sums) and FC2 is
 // h1_hi W2_hi + h1_hi W2_lo + h1_lo W2_hi (w2lo the lo parts of the weights), k step by k step.
 //
 // What bounds it is latency: there are B / 16 workgroups (47 for a rollout step of 750 robots), and with four waves
 // each read 64 columns of W2, then took four rows' head sums in turn.  Sixteen waves read 16 columns each, before h1
-// is there, and take one row.  750 rows, split precision: 16.1 -> 11.3 us, 2000 rows 16.1 -> 11.5.
-constexpr int kTailManyRows = 6144;   // rows from which four waves a workgroup fill the chip (16 there: 27 -> 31 us at 16384)
+// is there, and take one row.  750 rows, split precision: 16.1 -> 11.3 us, 2000 rows 16.1 -> 11.5.  From
+// kTailManyRows rows on four waves a workgroup fill the chip too (four / sixteen waves, split: 16.3 / 12.0 at 3000
+// rows, 28.5 / 23.5 at 8192, 34.2 / 32.2 at 12288, 43.5 / 42.3 at 16384; BF16: 10.2 / 8.0, 19.8 / 19.6, 24.1 / 23.8,
+// 31.4 / 31.4, where the best of 30 calls takes 26.6 with four and 29.0 with sixteen).
+constexpr int kTailManyRows = 12288;
 
 template <bool PREC, int NW>
 __global__ __launch_bounds__(64 * NW) void k_fwd_tail(const float* prm, Offsets o, const float* part, int S,
