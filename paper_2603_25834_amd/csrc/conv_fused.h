@@ -109,9 +109,8 @@ __device__ __forceinline__ void conv_frag_elem(const float* prm, const Offsets& 
   frag[idx] = __builtin_bit_cast(uint4, v);
 }
 
-template <bool LO = false>
 __global__ __launch_bounds__(64 * kConvFrags) void k_conv_frags(const float* prm, Offsets o, uint4* frag) {
-  conv_frag_elem<LO>(prm, o, frag, threadIdx.x);
+  conv_frag_elem(prm, o, frag, threadIdx.x);
 }
 
 // A 64x64 int16 crop is 512 vectors of eight cells (row y = v / 8, columns
@@ -131,11 +130,11 @@ __device__ __forceinline__ void load_crop(const int16_t* src, CropRegs<NT>& r) {
   for (int i = 0; i < CropRegs<NT>::kPer; ++i) r.v[i] = s4[threadIdx.x + i * NT];
 }
 
-// Crop registers into LDS, space-to-depth, as BF16(L / 256) (with LO its lo part).  Block (Y, X)
+// The lo parts of the crop registers' BF16(L / 256) into LDS, space-to-depth.  Block (Y, X)
 // sits at ((Y + 1) * 33 + X + 1) * 4; the row and column of index 0 are the
 // zero padding and are never written here.
-template <int NT, bool LO = false>
-__device__ __forceinline__ void store_crop(const CropRegs<NT>& r, uint16_t* s_crop) {
+template <int NT>
+__device__ __forceinline__ void store_crop_lo(const CropRegs<NT>& r, uint16_t* s_crop) {
 #pragma unroll
   for (int i = 0; i < CropRegs<NT>::kPer; ++i) {
     const int v = threadIdx.x + i * NT;
@@ -148,7 +147,7 @@ __device__ __forceinline__ void store_crop(const CropRegs<NT>& r, uint16_t* s_cr
       const float hi = (float)(int16_t)(w[q] >> 16) * (1.0f / 256.0f);
       const int X = (x0 >> 1) + q;
       *reinterpret_cast<uint32_t*>(s_crop + ((Y + 1) * kBlk + X + 1) * 4 + 2 * dy) =
-          (uint32_t)bf16_part<LO>(lo) | ((uint32_t)bf16_part<LO>(hi) << 16);
+          (uint32_t)bf16_part<true>(lo) | ((uint32_t)bf16_part<true>(hi) << 16);
     }
   }
 }
@@ -612,7 +611,7 @@ __global__ __launch_bounds__(kBwdThreads) __attribute__((amdgpu_waves_per_eu(2, 
 
   for (int b = blockIdx.x; b < B; b += gridDim.x) {
     // ---- stage the crop and dz2
-    if (PREC) store_crop<kBwdThreads, true>(cr, s_cropl);
+    if (PREC) store_crop_lo(cr, s_cropl);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const int32_t w[4] = {cr.v[i].x, cr.v[i].y, cr.v[i].z, cr.v[i].w};

@@ -72,23 +72,6 @@ constexpr int64_t kFc1Splits = 12, kFc2Splits = 64;
 constexpr int kFc1MinBlocks = 512;   // FC1 forward: resident workgroups (two per CU) that its K splits fill
 constexpr int kFc1WideBlocks = 160;  // workgroups from which FC1 takes the 128 x 256 tiles
 
-int64_t splits_for(int64_t K, int64_t min_chunk, int64_t max_splits) {
-  return std::max<int64_t>(1, std::min<int64_t>(max_splits, K / min_chunk));
-}
-
-// K splits of a split-K GEMM with `tiles` output tiles: the count that minimises (rounds of
-// `slots` resident workgroups) x (BK steps per workgroup), the smaller on ties.
-int64_t splits_balanced(int64_t K, int BK, int64_t tiles, int64_t slots, int64_t max_splits) {
-  int64_t best = 1, best_cost = -1;
-  for (int64_t s = 1; s <= max_splits; ++s) {
-    const int64_t rounds = (tiles * s + slots - 1) / slots;
-    const int64_t steps = (K + s * BK - 1) / (s * BK);
-    const int64_t cost = rounds * steps;
-    if (best_cost < 0 || cost < best_cost) { best = s; best_cost = cost; }
-  }
-  return best;
-}
-
 // Number of K slices gemm::run launches for `splits` requested splits (chunks rounded up to BK).
 int slices_used(int64_t K, int64_t splits, int BK) {
   int64_t chunk = (K + splits - 1) / splits;
