@@ -11,7 +11,9 @@
 // 256 x 256 of C (128 x 64 a wave), one per CU, so that N = 256 reads X, the large operand, once.  T = 128: four
 // waves of 64 x 64, two workgroups per CU, for few rows or small matrices.  FC1's weight (N = 256, K = 8564), GEMM
 // alone: 140 -> 57 us at M = 9000, 227 -> 92 at 16384 (42 % of the matrix cores' time; what bounds it is the way from
-// HBM, 281 MB of X and 61 MB of partial sums), 62 -> 26 at 3000, 16 -> 10 at 96.  The fragments want eight rows of one column a lane: ds_read_b64_tr_b16 gives four (of a group's 16 lanes, lane
+// HBM, 281 MB of X and 61 MB of partial sums), 62 -> 26 at 3000, 16 -> 10 at 96.
+//
+// The fragments want eight rows of one column a lane: ds_read_b64_tr_b16 gives four (of a group's 16 lanes, lane
 // 4 r + c reads columns 4 c .. of row r, lane i receives column i of the four rows).  The rows of a stage are
 // dealt to the MFMA's k index as 16 t + 4 g + r (lane group g, read t), the same for both operands; the 32-byte
 // column blocks of row r lie permuted by r % 8, so that 32 lanes' eight rows cover all banks.

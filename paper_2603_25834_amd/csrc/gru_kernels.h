@@ -181,11 +181,11 @@ __global__ __launch_bounds__(256) void k_gru_heads(const float* prm, Offsets o, 
 // (two 16-column tiles), so a lane keeps the (robot, unit) pairs (E lg + e, 32 w + 16 j + lr), e < E,
 // for the whole sequence (row 4 lg + e of the 16-row MFMA tile; the rows e >= E stay empty) and the state
 // (or its gradient) never leaves its registers except as the BF16 rows that the next step's product
-// reads from LDS.  E is 4, 2 or 1 (gru_seq_rows): a step's length is mostly the gate math of its
-// rows, so while there are CUs left a tile is filled with fewer robots rather than with empty CUs.  W_hh stays on the CU: most fragments in registers, the
-// rest in LDS in fragment order (16 bytes per lane, conflict-free).  What bounds it: a step is a serial
-// chain (product, gate math, exchange) whose launch per step, which this replaces, read the 384 KB of
-// weights and the rows back from L2 every time.
+// reads from LDS.  E is 4, 2 or 1 (gru_seq_rows): a step's length is mostly the gate math of its rows, so while there
+// are CUs left a tile is filled with fewer robots rather than with empty CUs.  W_hh stays on the CU: most fragments in
+// registers, the rest in LDS in fragment order (16 bytes per lane, conflict-free).  What bounds it: a step is a serial
+// chain (product, gate math, exchange) whose launch per step, which this replaces, read the 384 KB of weights and the
+// rows back from L2 every time.
 // T = 24, 375 robots: forward 256 us in 24 launches -> 58 us (+ 15 us for the input products as one
 // GEMM), backward 304 -> 71 us; with 16 robots a workgroup (E = 4) they took 156 and 170 us.
 struct GruSeqArgs {

@@ -69,7 +69,7 @@ constexpr int kConvGridPrec = 512; // the split-precision encoder forward holds 
 constexpr int kConvFragsAll = kConvLoFrag + kConvFrags;   // forward, backward phase and lo fragments
 constexpr int kConvBwdGrid = 512;  // encoder backward: two workgroups per CU (LDS)
 constexpr int64_t kFc1Splits = 12, kFc2Splits = 64;
-constexpr int kFc1MinBlocks = 512;   // FC1 forward: resident workgroups (two per CU) that its K splits fill
+constexpr int kFc1MinBlocks = 512;   // FC1: resident 128 x 128 workgroups (two per CU) that its K splits fill
 constexpr int kFc1WideBlocks = 160;  // workgroups from which FC1 takes the 128 x 256 tiles
 
 // Number of K slices gemm::run launches for `splits` requested splits (chunks rounded up to BK).
@@ -112,9 +112,10 @@ int split_fc1_chunk(int k1p, int rt) {
   return std::min(best, k1p);
 }
 
-// Gradient at `off`, [n][k] += sum_m d[m][n] x[m][k], its partial sums in `part` for `red`.  256 x 256 tiles read FC1's large operand once, but leave the chip idle
-// where there are few of them or few rows (GEMM and reduction, us, small / large tiles: FC1's weight 19 / 28 at 96 rows,
-// 27 / 29 at 750, 37 / 43 at 3000, 81 / 74 at 9000; FC2's at 9000 rows 16 / 22, one of the GRU's 21 / 24).
+// Gradient at `off`, [n][k] += sum_m d[m][n] x[m][k], its partial sums in `part` for `red`.  256 x 256 tiles read FC1's
+// large operand once, but leave the chip idle where there are few of them or few rows (GEMM and reduction, us, small /
+// large tiles: FC1's weight 19 / 28 at 96 rows, 27 / 29 at 750, 37 / 43 at 3000, 81 / 74 at 9000; FC2's at 9000 rows
+// 16 / 22, one of the GRU's 21 / 24).
 hipError_t weight_grad(const gemm_tn::Operands& g, int64_t max_slices, float* part, int64_t off, Reducer& red,
                        hipStream_t st) {
   constexpr int kLargeTiles = 32, kLargeRows = 6144;
@@ -124,8 +125,10 @@ hipError_t weight_grad(const gemm_tn::Operands& g, int64_t max_slices, float* pa
   return gemm_tn::run(g, part, T, S, st);
 }
 
-// Where a backward pass leaves the partial sums of its weight and bias gradients (reduced in one launch at its
-// end): FC1's weight, FC2's or the GRU's W_ih, W_hh, the GRU's biases, FC1's bias, the encoder's.
+// Where a backward pass leaves the partial sums of its weight and bias gradients, side by side, as they are reduced in
+// one launch at its end: FC1's weight, FC2's or the GRU's W_ih, W_hh, the GRU's biases, FC1's bias, the encoder's.  At
+// 360 rays 132 MB a handle (217 with the GRU), also of one that only runs forward; one region for all in turn took
+// 105, and a launch for each.
 struct PartRegions {
   int64_t w1, w2, whh, gb, b1, conv, total;
 };
@@ -250,10 +253,10 @@ int encode_fc1(aslam_policy* P, const float* prm, const int16_t* crop, const flo
   PCHK(hipGetLastError());
   // FC1: [B x k1] x [k1 x 256] (both operands zero-padded from k1 to k1p)
   const int K1 = (int)((P->off.k1 + 7) / 8 * 8);
-  // as many K splits as keep the grid within one round of kFc1MinBlocks resident workgroups; with the
-  // three split-precision products and few row tiles (a rollout step) a third of that: the products
-  // fill the round themselves, and more slices would only add partial-sum traffic (at 750 rows, 32
-  // splits of 3 products wrote and re-read 74 MB of partial sums per call)
+  // as many K splits as keep the grid within one round of kFc1MinBlocks resident workgroups; with the three
+  // split-precision products of a training pass and few row tiles a third of that: the products fill the round
+  // themselves, and more slices would only add partial-sum traffic (at 750 rows, 32 splits of 3 products wrote and
+  // re-read 74 MB of partial sums per call)
   const int tiles = ((B + 127) / 128) * (kHid / 128);
   int S = std::max(1, std::min(32, kFc1MinBlocks / tiles));
   if (P->prec && tiles < 32) S = std::max(1, std::min(32, kFc1MinBlocks / (3 * tiles)));
@@ -270,9 +273,11 @@ int encode_fc1(aslam_policy* P, const float* prm, const int16_t* crop, const flo
     return ASL_OK;
   }
   const int nz = slices_used(K1, S, 64);
-  // The wide kernel (128 x 256 tiles, one workgroup per CU) while its tiles and slices come near a round of
-  // the CUs; below that (a rollout step: 84 workgroups at 750 rows, 38 us) the 128 x 128 tiles with each
-  // product in slices of its own are faster (27 us).
+  // The wide kernel (128 x 256 tiles, one workgroup per CU) from where its tiles and slices come near a round of the
+  // CUs; below that the 128 x 128 tiles, with each split-precision product in slices of its own.  Engine / wide, us: a
+  // BF16 forward 39.8 / 39.9 at 400 rows (128 workgroups), 41.9 / 40.1 at 513 (160), 57.2 / 53.3 at 2000; a split
+  // minibatch, whose six slices leave the wide tiles few, 192 / 206 at 750 rows (36 workgroups), 239 / 265 at 1600
+  // (78), 280 / 268 at 2000 (256).
   if (S == 1 || (B + 127) / 128 * nz >= kFc1WideBlocks) {
     const gemm_nt::Operands fc1{P->x, P->x_lo, P->w1b, P->w1b_lo, P->k1p, P->k1p, B, kHid, P->k1p};
     const int k_split = ((K1 + S - 1) / S + 63) / 64 * 64;
@@ -386,7 +391,8 @@ int aslam_policy_create(const aslam_policy_config* cfg, aslam_policy** out) {
   struct A { void** ptr; size_t bytes; } al[] = {
       {(void**)&p->x, 2 * (size_t)Bm * p->k1p},  {(void**)&p->h1, 2 * (size_t)Bm * kHid},
       {(void**)&p->dz2, 2 * (size_t)Bm * kHid},  {(void**)&p->dz1, 2 * (size_t)Bm * kHid},
-      {(void**)&p->dz2c, 2 * (size_t)Bm * kFeat}, {(void**)&p->amask, (size_t)Bm * kFeat / 8}, {(void**)&p->z2, 4 * (size_t)Bm * kHid},
+      {(void**)&p->dz2c, 2 * (size_t)Bm * kFeat}, {(void**)&p->amask, (size_t)Bm * kFeat / 8},
+      {(void**)&p->z2, 4 * (size_t)Bm * kHid},
       {(void**)&p->part, 4 * (size_t)p->part_floats},
       {(void**)&p->hpart, 4 * (size_t)((Bm + kHeadRows - 1) / kHeadRows) * kHeadPart},
       {(void**)&p->w1b, 2 * (size_t)kHid * p->k1p}, {(void**)&p->w1t, 2 * (size_t)kFeat * kHid},
@@ -600,7 +606,8 @@ int aslam_policy_backward_rows(aslam_policy* P, const float* params, const int16
   // FC2 weight: dW2[out][in] = sum_b dz2[b][out] h1[b][in]
   const PartRegions pr = part_regions(P);
   Reducer red;
-  PCHK(weight_grad(gemm_tn::Operands{P->dz2, kHid, kHid, P->h1, kHid, kHid, B}, kFc2Splits, P->part + pr.w2, o.f2w, red, st));
+  PCHK(weight_grad(gemm_tn::Operands{P->dz2, kHid, kHid, P->h1, kHid, kHid, B}, kFc2Splits, P->part + pr.w2, o.f2w, red,
+                   st));
   // dh1 -> dz1 = (dz2 W2) * [h1 > 0]
   PCHK((gemm::run<128, 128, 64, 2, 2>(LdBF16K{P->dz2, kHid, B, kHid}, LdBF16K{P->w2t, kHid, kHid, kHid},
                                      EpiReluGradBF16{P->dz1, P->h1, kHid, kHid}, B, kHid, kHid, 1, st)));
@@ -622,7 +629,8 @@ int backward_fc1_encoder(aslam_policy* P, const float* params, const int16_t* cr
   PCHK(hipGetLastError());
   red.add(P->part + pr.b1, kBiasBlocks, kHid, o.f1b);
   // FC1 weight: dW1[out][k] = sum_b dz1[b][out] X[b][k]
-  PCHK(weight_grad(gemm_tn::Operands{P->dz1, kHid, kHid, P->x, P->k1p, o.k1, B}, kFc1Splits, P->part + pr.w1, o.f1w, red, st));
+  PCHK(weight_grad(gemm_tn::Operands{P->dz1, kHid, kHid, P->x, P->k1p, o.k1, B}, kFc1Splits, P->part + pr.w1, o.f1w, red,
+                   st));
   // dA2 -> dz2c = (dz1 W1[:, :8192]) * [a2 > 0]
   PCHK(gemm_nt::feature_grad(P->dz1, P->w1t, reinterpret_cast<const uint8_t*>(P->amask), P->dz2c, B, kFeat, st));
   // encoder: conv2 / conv1 weight and bias gradients in one pass over the minibatch
@@ -795,7 +803,8 @@ int aslam_policy_backward_seq(aslam_policy* P, const float* params, const int16_
   const unsigned tiles = (unsigned)((nb + 4 * rpl - 1) / (4 * rpl));
   PCHK((gemm::run<128, 128, 64, 2, 2>(LdBF16K{P->h1, kHid, B, kHid}, LdBF16K{P->wihb, kHid, kGates, kHid},
                                      EpiPartial{reinterpret_cast<float*>(P->dg), kGates, 0}, B, kGates, kHid, 1, st)));
-  (rpl == 1 ? k_gru_seq_fwd<1> : rpl == 2 ? k_gru_seq_fwd<2> : k_gru_seq_fwd<4>)<<<tiles, kGruSeqThreads, kGruSeqFwdLds, st>>>(a);
+  (rpl == 1 ? k_gru_seq_fwd<1>
+            : rpl == 2 ? k_gru_seq_fwd<2> : k_gru_seq_fwd<4>)<<<tiles, kGruSeqThreads, kGruSeqFwdLds, st>>>(a);
   PCHK(hipGetLastError());
   // heads + loss on every sample -> dh (FP32), head / log-std partial sums
   const int nh = (B + kHeadRows - 1) / kHeadRows;
@@ -810,12 +819,16 @@ int aslam_policy_backward_seq(aslam_policy* P, const float* params, const int16_
   uint16_t* const dgi = P->dg;
   uint16_t* const dgh = P->dg + (int64_t)B * kGates;
   a.whh = P->whht; a.dh_head = P->dh_head; a.dgi = dgi; a.dgh = dgh; a.part = P->part + pr.gb;
-  (rpl == 1 ? k_gru_seq_bwd<1> : rpl == 2 ? k_gru_seq_bwd<2> : k_gru_seq_bwd<4>)<<<tiles, kGruSeqThreads, kGruSeqBwdLds, st>>>(a);
+  (rpl == 1 ? k_gru_seq_bwd<1>
+            : rpl == 2 ? k_gru_seq_bwd<2> : k_gru_seq_bwd<4>)<<<tiles, kGruSeqThreads, kGruSeqBwdLds, st>>>(a);
   PCHK(hipGetLastError());
-  red.add(P->part + pr.gb, (int)tiles, 2 * kGates, ReduceSegs{{kGates, kGates, 0, 0}, {0, 0, 0, 0}, {o.gbi, o.gbh, 0, 0}});
+  red.add(P->part + pr.gb, (int)tiles, 2 * kGates,
+          ReduceSegs{{kGates, kGates, 0, 0}, {0, 0, 0, 0}, {o.gbi, o.gbh, 0, 0}});
   // GRU weights: dW_ih = sum_s dgi[s] h1[s]^T, dW_hh = sum_s dgh[s] hp[s]^T
-  PCHK(weight_grad(gemm_tn::Operands{dgi, kGates, kGates, P->h1, kHid, kHid, B}, kFc2Splits, P->part + pr.w2, o.gih, red, st));
-  PCHK(weight_grad(gemm_tn::Operands{dgh, kGates, kGates, P->hp_bf, kHid, kHid, B}, kFc2Splits, P->part + pr.whh, o.ghh, red, st));
+  PCHK(weight_grad(gemm_tn::Operands{dgi, kGates, kGates, P->h1, kHid, kHid, B}, kFc2Splits, P->part + pr.w2, o.gih, red,
+                   st));
+  PCHK(weight_grad(gemm_tn::Operands{dgh, kGates, kGates, P->hp_bf, kHid, kHid, B}, kFc2Splits, P->part + pr.whh, o.ghh,
+                   red, st));
   // FC1 output gradient: dz1 = (dgi W_ih) * [h1 > 0]
   PCHK((gemm::run<128, 128, 64, 2, 2>(LdBF16K{dgi, kGates, B, kGates}, LdBF16K{P->wiht, kGates, kHid, kGates},
                                      EpiReluGradBF16{P->dz1, P->h1, kHid, kHid}, B, kHid, kGates, 1, st)));

@@ -523,7 +523,8 @@ __global__ __launch_bounds__(256) void k_reduce_bias_relu_bf16_2(const float* pa
 }
 
 // h1 of M rows from FC1's slices.  Two columns a thread while eight would leave most CUs idle (96 rows, 96 slices:
-// 10.4 -> 7.1 us).
+// 10.4 -> 7.1 us; a split minibatch with eight / two columns 186.6 / 186.0 at 600 rows, 194.0 / 192.9 at 900, 212.6 /
+// 213.5 at 1200, 237.9 / 239.4 at 1600).
 inline hipError_t launch_reduce_relu(const float* part, int S, int M, const float* bias, uint16_t* h1, uint16_t* h1_lo,
                                      hipStream_t st) {
   constexpr int kFewRows = 1024;
@@ -837,7 +838,8 @@ __global__ __launch_bounds__(64 * NW) void k_fwd_tail(const float* prm, Offsets 
       const gemm::bf16x8 b = __builtin_bit_cast(gemm::bf16x8, kAhead ? bf[k] : weight(w2b, j, k));
       acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, b, acc[j], 0, 0, 0);
       if (PREC) {
-        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, __builtin_bit_cast(gemm::bf16x8, kAhead ? bfl[k] : weight(w2lo, j, k)), acc[j], 0, 0, 0);
+        const gemm::bf16x8 bl = __builtin_bit_cast(gemm::bf16x8, kAhead ? bfl[k] : weight(w2lo, j, k));
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bl, acc[j], 0, 0, 0);
         acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afl, b, acc[j], 0, 0, 0);
       }
     }
