@@ -146,6 +146,8 @@ struct LdsPlan {
 // Entries of a wave's octet list (uint16): the octets of 64 bitmap words.
 constexpr int kApplyList = 256;
 
+struct ExecState;
+
 // Launchers (env_kernels.hip); all asynchronous on `stream`.
 hipError_t launch_reset(const EnvParams& P, const uint32_t* world_src, const float* init_pose,
                         const uint8_t* mask, int32_t max_side, hipStream_t stream);
