@@ -249,12 +249,14 @@ int plan_lds(aslam_env* e, const aslam_exec_config& ex, LdsPlan& L) {
   L.band_rows = (int32_t)band;
   // The bitmap takes the world rows' place, or its own where that leaves the CU the workgroups it can have at once:
   // cleared before the march then, a phase less between the march and the walk.  At once are three of 512 threads (24
-  // waves, at 80 registers a lane), more of fewer threads where there are as many robots.  Own place where it takes
-  // workgroups away, and the world's: 1600 grids of 256 x 256, 128 threads 211 and 166 us a step, 256 threads 165 and
-  // 156; 4000 of 128 x 128, 128 threads 170 and 167.  Where it takes none: 750 grids of 256 x 256, 512 threads, 93.9
-  // and 94.1, 128 threads with segmented walks 152 and 153.
+  // waves, at 80 registers a lane) and, where there are as many robots, more of up to 256 threads (a fourth of 384
+  // brought nothing: own place 418 us, the world's 436).  Own place where it takes workgroups away, and the world's:
+  // 1600 grids of 256 x 256, 128 threads 211 and 166 us a step, 256 threads 165 and 156; 4000 of 128 x 128, 128 threads
+  // 170 and 167.  Where it takes none: 750 grids of 256 x 256, 512 threads, 93.9 and 94.1, 128 threads with segmented
+  // walks 152 and 153.
   const int64_t bits = bits_of(band), tail = need(band), world = align_up(world_max, 16);
-  const int64_t at_once = std::max<int64_t>(3, std::min(24 / (ex.threads / 64), (e->n + e->cu_count - 1) / e->cu_count));
+  const int64_t most = ex.threads <= 256 ? 24 / (ex.threads / 64) : 3;
+  const int64_t at_once = std::max<int64_t>(3, std::min<int64_t>(most, (e->n + e->cu_count - 1) / e->cu_count));
   L.cleared = L.off_union + world + tail <= std::min<int64_t>(budget, e->lds_max / at_once / 1280 * 1280) ? 1 : 0;
   L.off_bits = L.off_union + (L.cleared ? (int32_t)world : 0);
   L.off_list = over ? L.off_perm : L.off_bits + (int32_t)bits;
