@@ -695,10 +695,11 @@ __global__ __launch_bounds__(kCsmLdsThreads) void k_csm_cells(
     }
   } else if (!empty) {
     // From global memory: the list holds the rays' directions (a far robot's cells need not fit 16 bits), formed once
-    // and not by every line (8 grids of 4608 x 4608 cells, 360 rays, W = 4: 145 us that way).  Six rays' reads are in
-    // flight (127.6 us, with four 129.5; the general kernel takes 126.8); a ray without a return and a cell off the grid
-    // add nothing.
-    constexpr int kRays = 6;
+    // and not by every line (8 grids of 4608 x 4608 cells, 360 rays, W = 4: 145 us that way, 129.5 this; the general
+    // kernel takes 126.8).  Four rays' reads are in flight; with six (127.6) the kernel takes 146 registers, which
+    // leaves small grids one workgroup on a CU instead of two.  A ray without a return and a cell off the grid add
+    // nothing.
+    constexpr int kRays = 4;
     for (int e = threadIdx.x; e < nk * R; e += kCsmLdsThreads) {
       const int k = e / R, q = e - k * R;
       s_list[e] = dirtab[heading_index(ph % kNang + (k - V) * step_h + a_off[q] % kNang)];
