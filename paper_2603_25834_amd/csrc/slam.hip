@@ -836,7 +836,7 @@ __global__ __launch_bounds__(kIntThreads) void k_csm_integrate(
     const int32_t* __restrict__ pose_q, const int32_t* __restrict__ rho_q, int R, const int32_t* __restrict__ a_off,
     const int32_t* __restrict__ dirtab, int32_t rmax_q, const int32_t* __restrict__ match, int step_xy, int step_h,
     double l_max, int l_hit, int l_miss, int l_clamp, int32_t* __restrict__ coded, int lds_words,
-    const int32_t* __restrict__ wq_in) {
+    const int32_t* __restrict__ wq_in, int groups, int waves) {
   extern __shared__ __align__(16) uint32_t bits[];
   __shared__ int32_t s_cnt[kIntThreads / 64];
   __shared__ uint32_t s_sum[kIntThreads / 64];     // full and (high half) partial segments of a wave's rays
@@ -872,15 +872,14 @@ __global__ __launch_bounds__(kIntThreads) void k_csm_integrate(
   uint32_t* hitm = bits + band * nw;
   // 16-byte accesses when every row starts on an 8-cell boundary
   const bool vec = ((base | s) & 7) == 0;
-  // The rays are taken a group at a time, this thread's from ray0 by ray_step.  In one band the groups are spread over
-  // the whole scan and the lanes of a wave over their group, because neighbouring rays mark the same words, one after
-  // another (2048 rays in their own order: 251 us, 118 this way, 140 sorted by length and a lane a ray; 360 rays: 53
-  // and 49).  In bands they keep their order: a wave of neighbours is in the band, or is not (100 grids of 1000 x
-  // 1000, 700 rays: 405 us, 440 spread).
-  const int groups = (R + kIntThreads - 1) / kIntThreads;
+  // The rays are taken a group at a time, this thread's from ray0 by ray_step; a group fills `waves` waves.  In one band
+  // the groups are spread over the whole scan and the lanes of a wave over their group, because neighbouring rays mark
+  // the same words, one after another (2048 rays in their own order: 251 us, 118 this way, 140 sorted by length and a
+  // lane a ray; 360 rays: 53 and 49).  In bands they keep their order: a wave of neighbours is in the band, or is not
+  // (100 grids of 1000 x 1000, 700 rays: 405 us, 440 spread; 373 with the walk's loop unrolled).
   int ray0 = threadIdx.x, ray_step = kIntThreads;
   if (band >= si) {
-    const int waves = ((R + groups - 1) / groups + 63) >> 6, wave = threadIdx.x >> 6;   // that a group fills
+    const int wave = threadIdx.x >> 6;
     ray0 = wave < waves ? ((int)(threadIdx.x & 63) * waves + wave) * groups : R;
     ray_step = 1;
   }
@@ -1022,6 +1021,7 @@ __global__ __launch_bounds__(kIntThreads) void k_csm_integrate(
         for (int e = threadIdx.x; e < full + part; e += kIntThreads) {
           Walk w = begin(s_item[e]);
           const int32_t len = min(w.n, seg);
+#pragma unroll 4
           for (int i = 0; i < len; ++i) {
             advance(w);
             if ((uint32_t)w.wi < band_bits) atomicOr(&miss[w.wi >> 5], 1u << (w.wi & 31));
@@ -1199,10 +1199,11 @@ hipError_t launch_csm_integrate(const int32_t* tab, int16_t* belief_dev, const i
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_csm_integrate),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
   if (e != hipSuccess) return e;
+  const int groups = (R + kIntThreads - 1) / kIntThreads, waves = ((R + groups - 1) / groups + 63) / 64;
   k_csm_integrate<<<n, kIntThreads, bytes, stream>>>(belief_dev, cell_off_dev, side_dev, pose_q_dev, rho_q_dev, R,
                                                      a_off_dev, tab, rmax_q, match_dev, step_xy, step_h,
                                                      match_dev ? l_max : 1.0, l_hit, l_miss, l_clamp, coded_dev,
-                                                     words, wq_dev);
+                                                     words, wq_dev, groups, waves);
   return hipGetLastError();
 }
 
