@@ -820,10 +820,11 @@ __device__ __forceinline__ int4 apply_octet(int4 v, uint32_t any, uint32_t hit, 
 //
 // What bounds it: the walks were 57 of 102 thousand cycles of a robot (three robots a CU) when a lane took a ray,
 // longest first: the longest walk's 280 steps in sequence, fourteen instructions each with their tests.  A segment
-// is an eighth of that and a full one needs no test.  Then the apply pass, 28 thousand, which moves the coded octets
-// (about 110 KB a robot) at the rate of the memory.  750 robots, 256 x 256 cells: 64 -> 50 us at 360 rays,
-// 51 -> 36 at 128 (segments of 16 or 64 steps: 51 and 53, 38 and 40; eight octets in flight in the apply pass take a third
-// of the resident workgroups away: 64 and 50).
+// is an eighth of that and a full one needs no test: 20 thousand, and 9.5 for their list.  Then the apply pass, 28
+// thousand, which moves the coded octets (about 110 KB a robot) at the rate of the memory.  750 robots, 256 x 256
+// cells: 64 -> 45 us at 360 rays, 51 -> 37 at 128 (before the rays' layout below 50 and 37.6; segments of 16 or 64
+// steps then: 51 and 53, 38 and 40; eight octets in flight in the apply pass take a third of the resident workgroups
+// away: 64 and 50).
 //
 // The walk: with (a, b) the Q14 direction and the origin's fractional position, the k-th x crossing lies
 // at axis distance ex0 + 65536 k and is within the range iff (ex0 + 65536 k) 2^14 <= rho |a|, so the
